@@ -211,6 +211,13 @@ aidw_status aidw_nn_statistic(const aidw_grid* g, const float* qx, const float* 
  * streamed through the chip in tiles shared by every query of a wavefront, the
  * per-tile float32 partial sums are folded into compensated (two-sum) pairs,
  * and the final numerator / denominator are combined in float64.
+ * Large jobs (from about n m = 2e9 pairs, levels <= 8) are summed hierarchically:
+ * points near a query pair by pair as above, distant squares of points through
+ * their moments to the order (at most 16) that keeps the neglected terms of a
+ * square below 2^-22 of the query's sums.  The sums then cost O((n + m) log n)
+ * instead of O(n m); their error is that of the float32 weights (measured
+ * against float64: root mean square 5e-8, as with every pair evaluated).
+ * aidw_set_interp_config with a launch shape of the caller's evaluates every pair.
  * A query with d1sq[j] == 0 coincides with data points and gets the mean z of
  * those points (the limit of Eq. 1).
  * Arguments: r_obs, d1sq as produced by aidw_knn (device, [m]); p->alpha,
@@ -277,6 +284,8 @@ aidw_status aidw_run(const float* x, const float* y, const float* z, int64_t n, 
  *     AIDW_ECAPACITY (about 100 bytes per data point plus query: n = m = 2^20
  *     fits).  The data axis of the pair kernel is split only as far as its
  *     float64 partials fit beside the rest.
+ *   - Every pair of Eq. 1 is evaluated (aidw_run sums large jobs hierarchically,
+ *     whose moments would not fit the array).
  *   - Every call on one GPU uses that GPU's single array: calls that overlap on
  *     one GPU (other streams, other host threads) race and give undefined
  *     results.  The array keeps the last call's contents; each call
@@ -292,10 +301,10 @@ aidw_status aidw_run_noalloc(const float* x, const float* y, const float* z, int
 typedef struct {
   float grid_ms;        /* bounds, binning, counting sort                  */
   float knn_ms;         /* query binning and kNN search with Eq. 3         */
-  float interp_ms;      /* the pair-evaluation kernel(s) of Eq. 1          */
+  float interp_ms;      /* the pair-evaluation kernel(s) of Eq. 1, or its hierarchical summation */
   float finish_ms;      /* split combine and coincident-query fix-up       */
   int32_t interp_q;     /* queries per lane used by the pair kernel        */
-  int32_t interp_split; /* data-axis splits used by the pair kernel        */
+  int32_t interp_split; /* data-axis splits used by the pair kernel (1 when summed hierarchically) */
 } aidw_timing;
 
 /* Enables (1) or disables (0) per-stage timing for aidw_run on the calling
@@ -311,7 +320,8 @@ aidw_status aidw_last_timing(aidw_timing* out);
  * (>= 1); 0 for either restores the built-in choice.  integer_powers = 0
  * evaluates every query with the general w = 2^(-(alpha/2) log2 t); 1 or -1
  * (the default) lets queries whose alpha equals an integer level p in 1..8
- * use w = rsq(t)^p (one transcendental instead of two). */
+ * use w = rsq(t)^p (one transcendental instead of two).  With any of the three
+ * overridden every pair is evaluated, whatever the size (see aidw_interpolate). */
 aidw_status aidw_set_interp_config(int32_t q, int32_t split, int32_t integer_powers);
 
 /*

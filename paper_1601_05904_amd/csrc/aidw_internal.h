@@ -8,6 +8,10 @@
 
 namespace aidw {
 
+namespace tree {
+struct Plan;
+}
+
 // Device-resident grid scalars, written by the finalize kernel (Section 4.1.1, Eq. 2).
 struct GridScalars {
   float minx, miny, maxx, maxy;
@@ -234,10 +238,12 @@ hipError_t launch_nn_statistic(const float* r_obs, int m, double r_exp, double c
 // requests the integer-power kernel for class p (the general kernel covers every other block).
 // x, y, z are the padded copies made by launch_pad_copy.
 // gs (may be null): a grid whose failed status makes the launch do nothing.
+// fallback (may be null): the plan of a hierarchical summation; the launch then only works where
+// that plan is off.
 hipError_t launch_interp(const float* x, const float* y, const float* z, int n, const float* qx, const float* qy,
                          const float* alpha_f, const float* d1sq, const uint32_t* perm, const uint32_t* skeys, int m,
                          uint32_t fast_mask, int q, int split, float* qz, double2* partial, const GridScalars* gs,
-                         hipStream_t s);
+                         hipStream_t s, const tree::Plan* fallback = nullptr);
 // The untiled pair kernel (per-lane global loads, general alpha form, one data range).
 hipError_t launch_interp_naive(const float* x, const float* y, const float* z, int n, const float* qx, const float* qy,
                                const float* alpha_f, const float* d1sq, int m, float* qz, hipStream_t s);
@@ -246,7 +252,32 @@ int interp_padded_len(int n);
 // zero_word (may be null) is cleared by the same launch.
 hipError_t launch_pad_copy(const float* x, const float* y, const float* z, int n, float* xp, float* yp, float* zp,
                            uint32_t* zero_word, hipStream_t s);
-hipError_t launch_combine(const double2* partial, int m, int split, float* qz, hipStream_t s);
+hipError_t launch_combine(const double2* partial, int m, int split, float* qz, hipStream_t s,
+                          const tree::Plan* fallback = nullptr);
+
+// ---- hierarchical summation (tree.hip, tree_core.h) ----
+namespace tree {
+int node_capacity(int64_t n);   // squares a job of n points may have
+int hilbert_bits(int64_t n);    // bits per axis of the query order's tiles
+int padded_points(int64_t n);   // length of the cell-ordered arrays tx, ty, tz
+size_t plan_bytes();
+size_t node_bytes(int64_t n);   // the squares' records
+}  // namespace tree
+// The squares of a grid's points: plan, the padded points in cell order and the moments.
+// *zero_word (may be null) is cleared on the way.
+hipError_t launch_tree_build(const GridScalars* gs, const int32_t* cell_start, const float* sx, const float* sy,
+                             const int32_t* sidx, const float* z, int n, tree::Plan* plan, float* tx,
+                             float* ty, float* tz, float* nodes, uint32_t* zero_word, hipStream_t s);
+// Sort keys: the queries' places along the Hilbert curve over 2^hbits x 2^hbits tiles.
+hipError_t launch_tree_keys(const tree::Plan* plan, const float* qx, const float* qy, int m, int hbits, uint32_t* keys,
+                            hipStream_t s);
+// qz of every query from the squares, the queries in the order perm.  max_level: the
+// largest alpha level.  Does nothing where the plan is off.
+hipError_t launch_tree_eval(tree::Plan* plan, const int32_t* cell_start, const float* tx, const float* ty,
+                            const float* tz, const float* nodes, const float* qx, const float* qy,
+                            const float* alpha_f, const float* d1sq, const uint32_t* perm, int m,
+                            uint32_t fast_mask, double max_level, float* qz, hipStream_t s);
+
 hipError_t launch_fixup_grid(const uint32_t* count, const uint32_t* list, const float* qx, const float* qy,
                              const GridScalars* gs, const int32_t* cell_start, const float* sx, const float* sy,
                              const int32_t* sidx, const float* z, float* qz, hipStream_t s);

@@ -35,6 +35,7 @@
 #include "aidw_internal.h"
 #include "knn_core.h"
 #include "pair_core.h"
+#include "tree_core.h"
 
 namespace aidw {
 
@@ -145,7 +146,9 @@ __global__ __launch_bounds__(kThreads) void k_interp(const float* __restrict__ x
                                                      const uint32_t* __restrict__ perm,
                                                      const uint32_t* __restrict__ skeys, int m, uint32_t fast_mask,
                                                      float* __restrict__ qz, double2* __restrict__ partial,
-                                                     const GridScalars* __restrict__ gs) {
+                                                     const GridScalars* __restrict__ gs,
+                                                     const tree::Plan* __restrict__ fallback) {
+  if (fallback && !tree::off(fallback)) return;  // summed hierarchically
   if (gs && gs->status != AIDW_OK) return;  // a failed grid build: no result to compute
   const int pos0 = blockIdx.x * kThreads * Q;
   const int posl = min(m, pos0 + kThreads * Q) - 1;
@@ -211,7 +214,9 @@ __global__ __launch_bounds__(256) void k_pad_copy(const float* __restrict__ x, c
 }
 
 __global__ __launch_bounds__(256) void k_combine(const double2* __restrict__ partial, int m, int split,
-                                                 float* __restrict__ qz) {
+                                                 float* __restrict__ qz,
+                                                 const tree::Plan* __restrict__ fallback) {
+  if (fallback && !tree::off(fallback)) return;
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= m) return;
   double num = 0.0, den = 0.0;
@@ -309,9 +314,9 @@ template <int Q>
 hipError_t launch_q(dim3 grid, hipStream_t s, const float* x, const float* y, const float* z, int n, int chunk,
                     const float* qx, const float* qy, const float* alpha_f, const float* d1sq, const uint32_t* perm,
                     const uint32_t* skeys, int m, uint32_t mask, float* qz, double2* partial,
-                    const GridScalars* gs) {
+                    const GridScalars* gs, const tree::Plan* fallback) {
   hipLaunchKernelGGL((k_interp<Q>), grid, dim3(kThreads), 0, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys,
-                     m, mask, qz, partial, gs);
+                     m, mask, qz, partial, gs, fallback);
   return hipGetLastError();
 }
 
@@ -320,17 +325,17 @@ hipError_t launch_q(dim3 grid, hipStream_t s, const float* x, const float* y, co
 hipError_t launch_interp(const float* x, const float* y, const float* z, int n, const float* qx, const float* qy,
                          const float* alpha_f, const float* d1sq, const uint32_t* perm, const uint32_t* skeys, int m,
                          uint32_t fast_mask, int q, int split, float* qz, double2* partial, const GridScalars* gs,
-                         hipStream_t s) {
+                         hipStream_t s, const tree::Plan* fallback) {
   if (m <= 0) return hipSuccess;
   int chunk = (n + split - 1) / split;
   chunk = (chunk + kChunk - 1) / kChunk * kChunk;
   const dim3 grid((m + kThreads * q - 1) / (kThreads * q), split);
   fast_mask &= ((1u << (kMaxIntPow + 1)) - 2u);
   switch (q) {
-    case 1: return launch_q<1>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs);
-    case 2: return launch_q<2>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs);
-    case 4: return launch_q<4>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs);
-    case 8: return launch_q<8>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs);
+    case 1: return launch_q<1>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs, fallback);
+    case 2: return launch_q<2>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs, fallback);
+    case 4: return launch_q<4>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs, fallback);
+    case 8: return launch_q<8>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs, fallback);
     default: return hipErrorInvalidValue;
   }
 }
@@ -352,9 +357,10 @@ hipError_t launch_pad_copy(const float* x, const float* y, const float* z, int n
   return hipGetLastError();
 }
 
-hipError_t launch_combine(const double2* partial, int m, int split, float* qz, hipStream_t s) {
+hipError_t launch_combine(const double2* partial, int m, int split, float* qz, hipStream_t s,
+                          const tree::Plan* fallback) {
   if (m <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_combine, dim3((m + 255) / 256), dim3(256), 0, s, partial, m, split, qz);
+  hipLaunchKernelGGL(k_combine, dim3((m + 255) / 256), dim3(256), 0, s, partial, m, split, qz, fallback);
   return hipGetLastError();
 }
 

@@ -1,0 +1,111 @@
+// Hierarchical summation of Eq. 1: the shared definitions of tree.hip and its callers.
+//
+// The sums num = sum_i w_i z_i and den = sum_i w_i, w_i = |q - p_i|^-alpha, run over all n data
+// points.  Points near the query are evaluated pair by pair; a distant square of points is
+// evaluated through its moments about the square's centre c (side h):
+//   with r = (p - c) / h and v = h (q - c) / |q - c|^2 (complex numbers),
+//   |q - p|^-alpha = |q - c|^-alpha  sum_{j,k} b_j b_k (r conj(v))^j conj(r conj(v))^k,
+//   b_j = (alpha/2)(alpha/2 + 1) ... (alpha/2 + j - 1) / j!,
+// the product of the two binomial series of (1 - u)^(-alpha/2) and its conjugate, u = r conj(v).
+// The moments sum_i {z_i, 1} r_i^j conj(r_i)^k do not contain alpha, so one set serves every query
+// whatever its alpha.  Collected by l = j - k >= 0 and m = k (order j + k = l + 2m <= kOrder):
+//   M[l][m] = (2 if l > 0) sum_i {z_i, 1} r_i^l |r_i|^(2m).
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "aidw_internal.h"
+
+namespace aidw {
+namespace tree {
+
+constexpr int kOrder = 16;               // highest order of the moments
+constexpr int kTiers = kOrder / 2;       // orders 2, 4, ..., kOrder are the evaluation's choices
+constexpr int kNear = 1;                 // squares within kNear of the query's are opened
+constexpr float kLogRim = 0.5574f;        // log2(1 + rho) at the largest rho = sqrt(1/2) / 1.5
+constexpr int kLeafPoints = 32;          // wanted mean points per leaf
+constexpr int kTopSide = 8;              // squares per side at which no further level is built
+constexpr int kLevels = 14;
+constexpr int kMaxSide = 1 << 14;         // squares per side (a stack entry holds 14 bits of each)
+// Opened squares of one wavefront: at most 64 from the list, and 48 more per level below it.
+constexpr int kStack = 64 + 48 * kLevels;
+constexpr int kCoefs = 81;               // (l, m) pairs
+constexpr int kRec = 320;                // floats per square: 4 + sum of 2 (order + 1), padded to 64 B
+constexpr int kGroup = 64;               // queries per group (one per lane)
+constexpr int kClasses = 9;              // alpha classes 0 (general), 1 .. 8
+constexpr int kSplitPoints = 6000;       // near points from which a group is worth splitting
+constexpr int kFarCost = 3000;           // a group's far squares in pair evaluations
+constexpr uint32_t kDenseLeaf = 1 << 14; // points in one leaf above which the direct sums are used
+
+// A square's record: count, sum |z|, centre x, centre y, then for each (l, m) the real numbers
+// (num, den) for l = 0, (num re, num im, den re, den im) for l > 0.  The first line (64 bytes) ends
+// with the orders l + 2m <= 2; the further ones follow by l, m ascending, the order in which they
+// are consumed: the scalar loads of one l are contiguous.
+__host__ __device__ constexpr int coef_first(int l) {  // m of the first coefficient past the first line
+  return l == 0 ? 2 : l <= 2 ? 1 : 0;
+}
+__host__ __device__ constexpr int coef_count(int l) { return (kOrder - l) / 2 + 1 - coef_first(l); }
+__host__ __device__ constexpr int coef_offset(int l, int m) {
+  if (m < coef_first(l)) return l == 0 ? (m == 0 ? 4 : 6) : l == 1 ? 8 : 12;
+  int at = 16;
+  for (int i = 1; i < l; ++i) at += 4 * coef_count(i);
+  if (l == 0) {
+    for (int i = 1; i <= kOrder; ++i) at += 4 * coef_count(i);
+    return at + 2 * (m - 2);
+  }
+  return at + 4 * (m - coef_first(l));
+}
+
+// Geometry of a job's squares, made on the device from the grid scalars: level 0 squares (leaves)
+// are 2^bs x 2^bs grid cells, a level l + 1 square is 2 x 2 squares of level l.
+struct Plan {
+  int32_t bad;       // the sums are formed directly (geometry or data out of the moments' range)
+  int32_t bs, levels;
+  int32_t ncol, nrow;
+  float minx, miny, inv;
+  int32_t nx[kLevels], ny[kLevels], off[kLevels];  // squares per row / column, first record
+  double h[kLevels];                               // side
+};
+
+// |z| from here on (or NaN) takes the direct sums: the moments' sums stay far from overflow.
+constexpr float kZLimit = 1.2676506002282294e30f;  // 2^100
+
+__device__ inline bool off(const Plan* p) { return p->bad != 0; }
+
+// Centre of a square, the same float32 values wherever they are needed.
+__device__ inline void centre(const Plan* p, int lvl, int ix, int iy, float& cx, float& cy) {
+  const double h = p->h[lvl];
+  cx = (float)((double)p->minx + ((double)ix + 0.5) * h);
+  cy = (float)((double)p->miny + ((double)iy + 0.5) * h);
+}
+
+// Index of (x, y) along the Hilbert curve over 2^bits x 2^bits tiles.
+__host__ __device__ inline uint32_t hilbert(int bits, uint32_t x, uint32_t y) {
+  uint32_t d = 0;
+  for (int i = bits - 1; i >= 0; --i) {
+    const uint32_t rx = (x >> i) & 1u, ry = (y >> i) & 1u;
+    d = (d << 2) | ((3u * rx) ^ ry);
+    const uint32_t mask = (1u << i) - 1u;
+    x &= mask;
+    y &= mask;
+    if (ry == 0) {
+      if (rx) {
+        x = mask - x;
+        y = mask - y;
+      }
+      const uint32_t t = x;
+      x = y;
+      y = t;
+    }
+  }
+  return d;
+}
+
+// log2 of the bounds of the orders: thr[c][t] bounds Q rho^(P + 1), P = 2 t + 2, for class c.
+struct Thresholds {
+  float v[kClasses][kTiers];
+};
+
+}  // namespace tree
+}  // namespace aidw
