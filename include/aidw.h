@@ -453,9 +453,11 @@ aidw_status aidw_learned_routes(const float* x, const float* y, int64_t n, const
  * data points) from a list ordered by decreasing cost until it is exhausted.
  * Every item writes its own float64 partial sums and a last pass adds a
  * query's partials in a fixed order, so results are bitwise reproducible.
- * Each job's outputs are those aidw_run gives for the job alone (bitwise when
- * aidw_run uses the same pair-kernel shape: q, and split = the job's number of
- * data ranges, see split_points).
+ * Jobs of at least 8192 data points and 256 queries (levels <= 8, with
+ * integer_powers) are summed hierarchically, as aidw_interpolate describes.
+ * Each job's outputs are those aidw_run gives for the job alone (bitwise, for a
+ * job whose every pair is evaluated, when aidw_run uses the same pair-kernel
+ * shape: q, and split = the job's number of data ranges, see split_points).
  *
  * A plan fixes the jobs (pointers and sizes) and the launch shape once: it
  * checks everything on the host, allocates one device workspace and uploads
@@ -492,7 +494,8 @@ typedef struct {
  *                   0 = a job's whole data set (one range per query block).
  *   workers_per_cu  persistent pair-kernel workgroups per compute unit, 1..32.
  *   integer_powers  1: a block of queries whose alpha is the same integer p in
- *                   1..8 uses w = rsq(t)^p; 0: every query the general form.
+ *                   1..8 uses w = rsq(t)^p; 0: every query the general form,
+ *                   and every pair is evaluated.
  *   use_graph       1: the first aidw_batch_run captures the pipeline into a
  *                   HIP graph (it needs a created stream, not the null stream)
  *                   and every run launches that graph. */

@@ -10,6 +10,7 @@ namespace aidw {
 
 namespace tree {
 struct Plan;
+struct Job;
 }
 
 // Device-resident grid scalars, written by the finalize kernel (Section 4.1.1, Eq. 2).
@@ -262,21 +263,28 @@ int hilbert_bits(int64_t n);    // bits per axis of the query order's tiles
 int padded_points(int64_t n);   // length of the cell-ordered arrays tx, ty, tz
 size_t plan_bytes();
 size_t node_bytes(int64_t n);   // the squares' records
+// The parts of a job that follow from its size and alpha levels (all <= 8).
+void fill_job(Job* j, int64_t n, const double* levels);
 }  // namespace tree
-// The squares of a grid's points: plan, the padded points in cell order and the moments.
+// The squares of a job's points: plan, the padded points in cell order and the moments.
 // *zero_word (may be null) is cleared on the way.
-hipError_t launch_tree_build(const GridScalars* gs, const int32_t* cell_start, const float* sx, const float* sy,
-                             const int32_t* sidx, const float* z, int n, tree::Plan* plan, float* tx,
-                             float* ty, float* tz, float* nodes, uint32_t* zero_word, hipStream_t s);
+hipError_t launch_tree_build(const tree::Job& job, const float* sx, const float* sy, const int32_t* sidx,
+                             const float* z, float* tx, float* ty, float* tz, uint32_t* zero_word, hipStream_t s);
 // Sort keys: the queries' places along the Hilbert curve over 2^hbits x 2^hbits tiles.
 hipError_t launch_tree_keys(const tree::Plan* plan, const float* qx, const float* qy, int m, int hbits, uint32_t* keys,
                             hipStream_t s);
-// qz of every query from the squares, the queries in the order perm.  max_level: the
-// largest alpha level.  Does nothing where the plan is off.
-hipError_t launch_tree_eval(tree::Plan* plan, const int32_t* cell_start, const float* tx, const float* ty,
-                            const float* tz, const float* nodes, const float* qx, const float* qy,
-                            const float* alpha_f, const float* d1sq, const uint32_t* perm, int m,
-                            uint32_t fast_mask, double max_level, float* qz, hipStream_t s);
+// qz of every query from the squares, the queries in the order perm.  Does nothing where the plan is off.
+hipError_t launch_tree_eval(const tree::Job& job, const float* tx, const float* ty, const float* tz, const float* qx,
+                            const float* qy, const float* alpha_f, const float* d1sq, const uint32_t* perm, float* qz,
+                            hipStream_t s);
+// The same for njobs jobs at once (jobs: device array, group0 ascending): the plans, then, with tz in
+// place, the moments and the float64 (num, den) of every query whose plan is not off.  max_n, max_levels:
+// the largest of the jobs; groups: of all jobs.
+hipError_t launch_tree_plans(const tree::Job* jobs, int njobs, hipStream_t s);
+hipError_t launch_tree_batch(const tree::Job* jobs, int njobs, int64_t max_n, int max_levels, int groups,
+                             const float* tx, const float* ty, const float* tz, const float* qx, const float* qy,
+                             const float* alpha_f, const float* d1sq, const uint32_t* perm, double2* partial,
+                             hipStream_t s);
 
 hipError_t launch_fixup_grid(const uint32_t* count, const uint32_t* list, const float* qx, const float* qy,
                              const GridScalars* gs, const int32_t* cell_start, const float* sx, const float* sy,

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "aidw_internal.h"
+#include "tree_core.h"
 
 using namespace aidw;
 
@@ -526,7 +527,6 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
   aidw_status st = [&]() -> aidw_status {
     const int hbits = tree::hilbert_bits(n);
     const int npad = tree::padded_points(n);
-    const uint32_t fast_mask = integer_levels(p);
     // the direct sums where the plan turns out to be off: enough ranges to fill the chip
     int split = 1;
     const int64_t blocks = (m + 255) / 256;
@@ -548,9 +548,14 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
       return hip_fail(e, "allocating summation buffers");
     tree::Plan* plan = reinterpret_cast<tree::Plan*>(plan_mem);
     if (ev_begin) HIP_TRY(hipEventRecord(ev_begin, s), "event");
-    HIP_TRY(launch_tree_build(points->dev, points->cell_start, points->sx, points->sy, points->sidx, z, (int)n, plan,
-                              tx, ty, tz, nodes, count, s),
-            "moments");
+    tree::Job job{};
+    tree::fill_job(&job, n, p->alpha);
+    job.gs = points->dev;
+    job.plan = plan;
+    job.cell_start = points->cell_start;
+    job.nodes = nodes;
+    job.m = (int32_t)m;
+    HIP_TRY(launch_tree_build(job, points->sx, points->sy, points->sidx, z, tx, ty, tz, count, s), "moments");
     const float* alpha_use = alpha_f;
     if (alpha_in) {
       alpha_use = alpha_in;
@@ -565,11 +570,7 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
     uint32_t *skeys = keys, *sperm = perm;
     HIP_TRY(radix_sort_pairs_to(keys, perm, tk, tv, (int)m, 2 * hbits, hist, scan, s, &skeys, &sperm),
             "query sort");
-    double max_level = 0.0;
-    for (int i = 0; i < 5; ++i) max_level = fmax(max_level, p->alpha[i]);
-    HIP_TRY(launch_tree_eval(plan, points->cell_start, tx, ty, tz, nodes, qx, qy, alpha_use, d1sq, sperm, (int)m,
-                             fast_mask, max_level, qz, s),
-            "hierarchical summation");
+    HIP_TRY(launch_tree_eval(job, tx, ty, tz, qx, qy, alpha_use, d1sq, sperm, qz, s), "hierarchical summation");
     const GridScalars* status = own ? nullptr : points->dev;
     // skeys are no class keys here: every block takes the general form
     HIP_TRY(launch_interp(tx, ty, tz, (int)n, qx, qy, alpha_use, d1sq, sperm, skeys, (int)m, 0, 1, split, qz, partial,

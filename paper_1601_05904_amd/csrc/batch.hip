@@ -36,6 +36,7 @@
 #include "grid_core.h"
 #include "knn_core.h"
 #include "pair_core.h"
+#include "tree_core.h"
 
 namespace aidw {
 namespace {
@@ -58,6 +59,7 @@ struct BatchJob {
   int32_t splits;  // data ranges per query block
   int32_t chunk;   // points per data range (a multiple of the pair loop's fetch)
   int64_t poff;    // first partial slot; the job has splits * m of them
+  int32_t tree;      // the job's hierarchical summation, -1: every pair is evaluated
   uint32_t intmask;  // bit p: the job has the integer level p, whose blocks may take the w = rsq(t)^p loop
   double area_in, cw_in, occ;
   double r_min, r_max, levels[5];
@@ -66,6 +68,12 @@ struct BatchJob {
 struct WorkItem {
   int32_t job, qblock, split, pad;
 };
+
+// Data points from which a job is summed hierarchically: a query's near points and squares cost as
+// much as about 3000 pairs, and the moments and the wider sort are shared launches (48 jobs of
+// 1024 to 65,536 points: 5.7 -> 1.85 ms a replay).
+constexpr int kTreePoints = 8192;
+constexpr int kTreeQueries = 256;
 
 constexpr int kBoundsPerBlock = 4096;  // elements of one job per bounds workgroup
 
@@ -204,6 +212,27 @@ __global__ __launch_bounds__(256) void k_b_query_keys(const BatchJob* __restrict
   vals[q] = (uint32_t)q;
 }
 
+// z in the cell order of all jobs' points, for the jobs' moments; the points past the last are zero.
+// A value beyond the moments' range turns its job's plan off.
+__global__ __launch_bounds__(256) void k_b_tree_z(const BatchJob* __restrict__ jobs, const int32_t* __restrict__ noff,
+                                                  int njobs, int sum_n, int npad, const int32_t* __restrict__ sidx,
+                                                  const float* __restrict__ zp, float* __restrict__ sx,
+                                                  float* __restrict__ sy, float* __restrict__ tz,
+                                                  const tree::Job* __restrict__ tjobs) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= npad) return;
+  if (e >= sum_n) {
+    sx[e] = sy[e] = tz[e] = 0.0f;
+    return;
+  }
+  const float v = zp[sidx[e]];
+  tz[e] = v;
+  if ((__float_as_uint(v) & 0x7fffffffu) >= __float_as_uint(tree::kZLimit)) {
+    const int t = jobs[find_seg(noff, njobs, e)].tree;
+    if (t >= 0) tjobs[t].plan->bad = 1;
+  }
+}
+
 // kNN + Eq. 3 for the queries at binned positions [t_begin, t_end); each lane searches its
 // own job's grid.  The jobs are ordered by the length of their register k-list, so each
 // length class is one range of positions and one launch.
@@ -237,28 +266,34 @@ __global__ __launch_bounds__(256) void k_b_knn(const BatchJob* __restrict__ jobs
   d1sq[q] = d1;
 }
 
-// Eq. 4-6 per query with its job's parameters; key = job * 16 + pair-kernel class.
+// Eq. 4-6 per query with its job's parameters; key = job << low_bits | (the query's tile along the
+// Hilbert curve if the job is summed hierarchically, else its pair-kernel class).
 __global__ __launch_bounds__(256) void k_b_alpha(const BatchJob* __restrict__ jobs, const int32_t* __restrict__ qoff,
                                                  int njobs, int sum_m, const GridScalars* __restrict__ gs,
-                                                 const float* __restrict__ r_obs, int integer_powers,
+                                                 const float* __restrict__ r_obs, int integer_powers, int low_bits,
+                                                 const tree::Job* __restrict__ tjobs, int hbits,
+                                                 const float* __restrict__ cqx, const float* __restrict__ cqy,
                                                  float* __restrict__ alpha_f, uint32_t* __restrict__ keys,
                                                  uint32_t* __restrict__ vals) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= sum_m) return;
   const int j = find_seg(qoff, njobs, q);
   const GridScalars& G = gs[j];
-  uint32_t cls = 0;
+  const BatchJob& J = jobs[j];
+  uint32_t low = 0;
   if (G.status != AIDW_OK) {
     alpha_f[q] = NAN;
   } else {
-    const BatchJob& J = jobs[j];
     const double R = (double)r_obs[q] / G.r_exp;                                                // Eq. 4
     const double alpha = pair::level_alpha(pair::fuzzy_mu(R, J.r_min, J.r_max), J.levels);  // Eq. 5, 6
     alpha_f[q] = (float)alpha;
-    if (integer_powers) cls = pair::alpha_class(alpha);
+    if (J.tree >= 0 && !tree::off(tjobs[J.tree].plan))
+      low = tree::tile(tjobs[J.tree].plan, hbits, cqx[q], cqy[q]);
+    else if (integer_powers)
+      low = pair::alpha_class(alpha);
   }
   if (keys) {
-    keys[q] = ((uint32_t)j << 4) | cls;
+    keys[q] = ((uint32_t)j << low_bits) | low;
     vals[q] = (uint32_t)q;
   }
 }
@@ -305,7 +340,7 @@ __global__ __launch_bounds__(pair::kThreads) void k_b_interp(
     const float* __restrict__ yp, const float* __restrict__ zp, const float* __restrict__ cqx,
     const float* __restrict__ cqy, const float* __restrict__ alpha_f, const float* __restrict__ d1sq,
     const uint32_t* __restrict__ perm, const uint32_t* __restrict__ skeys, uint32_t fast_mask,
-    double2* __restrict__ partial) {
+    const tree::Job* __restrict__ tjobs, double2* __restrict__ partial) {
   __shared__ int s_item;
   for (;;) {
     if (threadIdx.x == 0) s_item = (int)atomicAdd(counter, 1u);
@@ -317,12 +352,13 @@ __global__ __launch_bounds__(pair::kThreads) void k_b_interp(
     const int j = w.job;
     if (gs[j].status != AIDW_OK) continue;
     const BatchJob& J = jobs[j];
+    if (J.tree >= 0 && !tree::off(tjobs[J.tree].plan)) continue;  // summed hierarchically
     const int pos0 = J.qoff + w.qblock * pair::kThreads * Q;
     const int posend = min(J.qoff + J.m, pos0 + pair::kThreads * Q);
     const int lo = w.split * J.chunk;
     const int hi = min(J.n, lo + J.chunk);
     uint32_t cls = 0;
-    if (fast_mask) {
+    if (fast_mask && J.tree < 0) {  // (a hierarchical job's keys hold tiles)
       const uint32_t k0 = skeys[pos0] & 15u, kl = skeys[posend - 1] & 15u;
       if (k0 == kl && ((J.intmask >> k0) & 1u)) cls = k0;
     }
@@ -426,6 +462,12 @@ struct aidw_batch {
   float *r_obs = nullptr, *d1sq = nullptr, *alpha_f = nullptr;
   double2* partial = nullptr;
   uint32_t* counter = nullptr;
+  // hierarchical summation: jobs, the largest of them, and their groups of queries
+  int ntree = 0, tree_n = 0, tree_levels = 0, tree_groups = 0, hbits = 0, low_bits = 4;
+  tree::Job* tjobs = nullptr;
+  char* tplans = nullptr;
+  char* tnodes = nullptr;
+  float* tz = nullptr;
   // graph replay
   hipGraphExec_t exec = nullptr;
   // timing
@@ -491,6 +533,10 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   int kmax = 1;
   uint32_t mask = 0;  // union of the jobs' integer levels
   double pairs = 0.0;
+  std::vector<tree::Job> tj;
+  std::vector<int> tree_owner;
+  int64_t groups = 0, tree_n = 0;
+  int tree_levels = 0;
   const int qb = pair::kThreads * cfg.q;
   auto kclass = [](int k) { return knn_slots(k); };
   for (int j = 0; j < njobs; ++j) {
@@ -541,7 +587,25 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
     J.cbase = (int32_t)scap;
     const int64_t cap = cell_budget(a.n, a.params);
     J.ccap = (int32_t)std::min<int64_t>(cap, AIDW_MAX_CELLS);
-    int64_t chunk = cfg.split_points > 0 ? std::min<int64_t>(cfg.split_points, a.n) : a.n;
+    bool tree_job = cfg.integer_powers && a.n >= kTreePoints && a.m >= kTreeQueries;
+    for (int l = 0; l < 5; ++l) tree_job = tree_job && a.params.alpha[l] <= 8.0;
+    J.tree = -1;
+    if (tree_job) {
+      J.tree = (int32_t)tj.size();
+      tree::Job t{};
+      tree::fill_job(&t, a.n, a.params.alpha);
+      t.q0 = (int32_t)sm;
+      t.m = (int32_t)a.m;
+      t.group0 = (int32_t)groups;
+      t.out0 = spart - sm;
+      groups += (a.m + tree::kGroup - 1) / tree::kGroup;
+      tree_n = std::max<int64_t>(tree_n, a.n);
+      tree_levels = std::max(tree_levels, t.level_cap);
+      tj.push_back(t);
+      tree_owner.push_back(j);
+    }
+    // (a hierarchically summed job has one item per block of queries, for a plan that turns out off)
+    int64_t chunk = cfg.split_points > 0 && !tree_job ? std::min<int64_t>(cfg.split_points, a.n) : a.n;
     chunk = (chunk + pair::kChunk - 1) / pair::kChunk * pair::kChunk;
     J.chunk = (int32_t)chunk;
     J.splits = (int32_t)((a.n + chunk - 1) / chunk);
@@ -614,7 +678,14 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   b->sum_partial = spart;
   b->sum_pairs = pairs;
   b->cell_bits = bits_for(scap);
-  b->class_bits = bits_for(njobs) + 4;
+  b->ntree = (int)tj.size();
+  b->tree_n = (int)tree_n;
+  b->tree_levels = tree_levels;
+  b->tree_groups = (int)groups;
+  // the tiles of the largest job, as far as the 32-bit key has room beside the job number
+  b->hbits = tree_n > 0 ? std::min(tree::hilbert_bits(tree_n), (32 - bits_for(njobs)) / 2) : 0;
+  b->low_bits = std::max(4, 2 * b->hbits);
+  b->class_bits = bits_for(njobs) + b->low_bits;
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -649,8 +720,9 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
     b->hist = carve<uint32_t>(base, off, hist_words);
     b->scan_tmp = carve<uint32_t>(base, off, scan_words);
     b->cell_start = carve<int32_t>(base, off, scap + 1);
-    b->sx = carve<float>(base, off, sn);
-    b->sy = carve<float>(base, off, sn);
+    // (the pair loops of the hierarchical summation read a chunk past a run's end)
+    b->sx = carve<float>(base, off, sn + 16);
+    b->sy = carve<float>(base, off, sn + 16);
     b->sidx = carve<int32_t>(base, off, sn);
     b->qkeys = carve<uint32_t>(base, off, std::max<int64_t>(sm, 1));
     b->qperm = carve<uint32_t>(base, off, std::max<int64_t>(sm, 1));
@@ -661,6 +733,14 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
     b->alpha_f = carve<float>(base, off, std::max<int64_t>(sm, 1));
     b->partial = carve<double2>(base, off, std::max<int64_t>(spart, 1));
     b->counter = carve<uint32_t>(base, off, 1);
+    if (!tj.empty()) {
+      b->tjobs = carve<tree::Job>(base, off, tj.size());
+      b->tplans = carve<char>(base, off, tree::plan_bytes() * tj.size());
+      b->tz = carve<float>(base, off, sn + 16);
+      size_t bytes = 0;
+      for (const tree::Job& t : tj) bytes += tree::node_bytes(t.n);
+      b->tnodes = carve<char>(base, off, bytes);
+    }
     return off;
   };
   b->mem_bytes = layout(nullptr);
@@ -669,6 +749,16 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
     return hip_fail(e, "allocating the batch workspace");
   }
   layout(static_cast<char*>(b->mem));
+  {
+    size_t at = 0;
+    for (size_t t = 0; t < tj.size(); ++t) {
+      tj[t].gs = b->gs + tree_owner[t];
+      tj[t].plan = reinterpret_cast<tree::Plan*>(b->tplans + tree::plan_bytes() * t);
+      tj[t].cell_start = b->cell_start + hj[tree_owner[t]].cbase;
+      tj[t].nodes = reinterpret_cast<float*>(b->tnodes + at);
+      at += tree::node_bytes(tj[t].n);
+    }
+  }
   struct Up {
     void* dst;
     const void* src;
@@ -678,7 +768,8 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
              {b->noff, noff.data(), sizeof(int32_t) * (njobs + 1)},
              {b->qoff, qoff.data(), sizeof(int32_t) * (njobs + 1)},
              {b->bstart, bstart.data(), sizeof(int32_t) * (njobs + 1)},
-             {b->items, sorted.data(), sizeof(WorkItem) * sorted.size()}};
+             {b->items, sorted.data(), sizeof(WorkItem) * sorted.size()},
+             {b->tjobs, tj.data(), sizeof(tree::Job) * tj.size()}};
   for (const Up& u : ups) {
     if (u.bytes == 0) continue;
     if ((e = hipMemcpy(u.dst, u.src, u.bytes, hipMemcpyHostToDevice)) != hipSuccess) {
@@ -706,10 +797,10 @@ void launch_b_knn(const aidw_batch* b, int t_begin, int t_end, hipStream_t s) {
 
 template <int Q>
 void launch_b_interp(const aidw_batch* b, hipStream_t s) {
-  const uint32_t* perm = b->fast_mask ? b->cperm : nullptr;
+  const uint32_t* perm = b->fast_mask || b->ntree ? b->cperm : nullptr;
   hipLaunchKernelGGL(k_b_interp<Q>, dim3(b->workers), dim3(pair::kThreads), 0, s, b->jobs, b->items, b->nitems,
                      b->counter, b->gs, b->xp, b->yp, b->zp, b->cqx, b->cqy, b->alpha_f, b->d1sq, perm, b->ckeys,
-                     b->fast_mask, b->partial);
+                     b->fast_mask, b->tjobs, b->partial);
 }
 
 // Queues the whole pipeline on s: no allocation, no host synchronisation.
@@ -745,16 +836,26 @@ aidw_status enqueue(aidw_batch* b, hipStream_t s, bool timed) {
 #undef AIDW_B_KNN
     }
     STEP(hipSuccess, "kNN search");
-    const bool classes = b->fast_mask != 0;
+    if (b->ntree) {
+      STEP(launch_tree_plans(b->tjobs, b->ntree, s), "plans");
+      const int npad = b->sum_n + 16;
+      hipLaunchKernelGGL(k_b_tree_z, dim3(div_up(npad, 256)), dim3(256), 0, s, b->jobs, b->noff, nj, b->sum_n, npad,
+                         b->sidx, b->zp, b->sx, b->sy, b->tz, b->tjobs);
+    }
+    const bool classes = b->fast_mask != 0 || b->ntree;
     hipLaunchKernelGGL(k_b_alpha, dim3(gm), dim3(256), 0, s, b->jobs, b->qoff, nj, b->sum_m, b->gs, b->r_obs,
-                       (int)classes, b->alpha_f, classes ? b->ckeys : nullptr, classes ? b->cperm : nullptr);
+                       (int)(b->fast_mask != 0), b->low_bits, b->tjobs, b->hbits, b->cqx, b->cqy, b->alpha_f, classes ? b->ckeys : nullptr, classes ? b->cperm : nullptr);
     STEP(hipSuccess, "adaptive power");
     if (classes)
       STEP(radix_sort_pairs(b->ckeys, b->cperm, b->tkeys, b->tvals, b->sum_m, b->class_bits, b->hist, b->scan_tmp,
                             s),
            "ordering the queries by class");
     if (timed) STEP(hipEventRecord(b->ev[2], s), "recording an event");
-    // stage 2: the persistent pair kernel
+    // stage 2: the large jobs' hierarchical summation, then the persistent pair kernel
+    if (b->ntree)
+      STEP(launch_tree_batch(b->tjobs, b->ntree, b->tree_n, b->tree_levels, b->tree_groups, b->sx, b->sy, b->tz, b->cqx,
+                             b->cqy, b->alpha_f, b->d1sq, b->cperm, b->partial, s),
+           "hierarchical summation");
     hipLaunchKernelGGL(k_b_reset, dim3(1), dim3(64), 0, s, b->counter);
     if (b->cfg.q == 1)
       launch_b_interp<1>(b, s);

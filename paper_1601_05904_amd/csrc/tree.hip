@@ -66,12 +66,25 @@ constexpr TriTable make_tri() {
 __device__ constexpr TriTable kTriT = make_tri();
 __device__ inline int tri_row(int J) { return J * (kOrder + 1) - J * (J - 1) / 2; }  // first entry of row J
 
-// Geometry from the grid scalars.  Leaves of about kLeafPoints points: 2^bs cells a side, bs the
+// The jobs of a launch: one, passed by value, or an array.
+struct OneJob {
+  Job j;
+  __device__ const Job& operator[](int) const { return j; }
+};
+struct ManyJobs {
+  const Job* j;
+  __device__ const Job& operator[](int i) const { return j[i]; }
+};
+
+// Geometry from the grid scalars (one workgroup per job).  Leaves of about kLeafPoints points: 2^bs cells a side, bs the
 // nearest to log2 sqrt(kLeafPoints cells / points), then as much larger as the node budget needs.
-__global__ void k_tree_plan(const GridScalars* __restrict__ gs, int n, int node_cap, int level_cap, Plan* __restrict__ out, uint32_t* __restrict__ zero_word) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  if (zero_word) *zero_word = 0u;
-  const GridScalars g = *gs;
+template <typename Jobs>
+__global__ void k_tree_plan(Jobs jobs, uint32_t* __restrict__ zero_word) {
+  if (threadIdx.x != 0) return;
+  const Job& job = jobs[blockIdx.x];
+  if (zero_word && blockIdx.x == 0) *zero_word = 0u;
+  const GridScalars g = *job.gs;
+  const int n = job.n, node_cap = job.node_cap, level_cap = job.level_cap;
   Plan p{};
   p.ncol = g.ncol;
   p.nrow = g.nrow;
@@ -114,7 +127,7 @@ __global__ void k_tree_plan(const GridScalars* __restrict__ gs, int n, int node_
     }
   }
   p.bs = bs;
-  *out = p;
+  *job.plan = p;
 }
 
 // The cell-ordered points with room for a chunk's over-read.  A z beyond the limit (a NaN's bits are
@@ -259,13 +272,17 @@ __device__ inline void store_moments(float* __restrict__ rec, int q, double v) {
 // Levels 0 and 1 from the points: one workgroup per level-1 square, one wavefront per leaf of it.
 // Each wavefront adds its points about the leaf's centre and about the square's; the four shares of
 // the square are then added.
-__global__ __launch_bounds__(256, 5) void k_tree_p2m(Plan* __restrict__ plan, const int32_t* __restrict__ cell_start,
-                                                  const float* __restrict__ tx, const float* __restrict__ ty,
-                                                  const float* __restrict__ tz, float* __restrict__ nodes) {
+template <typename Jobs>
+__global__ __launch_bounds__(256, 5) void k_tree_p2m(Jobs jobs, const float* __restrict__ tx,
+                                                     const float* __restrict__ ty, const float* __restrict__ tz) {
   __shared__ float s_tab[4][kWaveLds];
   __shared__ double s_acc[4][4 * kCoefs];
   __shared__ double s_abs[4];
   __shared__ int s_cnt[4];
+  const Job& job = jobs[blockIdx.y];
+  Plan* const plan = job.plan;
+  const int32_t* __restrict__ cell_start = job.cell_start;
+  float* __restrict__ nodes = job.nodes;
   if (plan->bad) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const bool two = plan->levels > 1;
@@ -346,12 +363,15 @@ __global__ __launch_bounds__(256, 5) void k_tree_p2m(Plan* __restrict__ plan, co
 // and d = (c_child - c_parent) / h_parent, r' = lambda r + d, hence
 //   mu'_{JK} = sum_{j,k} C(J,j) lambda^j d^(J-j)  C(K,k) lambda^k conj(d)^(K-k)  mu_{jk},
 // first over j, then over k.  One wavefront per child, one workgroup per parent.
-__global__ __launch_bounds__(256) void k_tree_m2m(const Plan* __restrict__ plan, int lvl, float* __restrict__ nodes) {
+template <typename Jobs>
+__global__ __launch_bounds__(256) void k_tree_m2m(Jobs jobs, int lvl) {
   __shared__ double2 s_pow[4][kOrder + 1];  // d^i
   __shared__ float s_c[kTri];               // C(J,j) / 2^j at J (J + 1) / 2 + j
   __shared__ double s_t[4][kTri][4];        // the first stage
   __shared__ double s_m[4][kCoefs][4];      // child's mu, then its share of the parent's
   __shared__ float s_head[4][2];
+  const Plan* __restrict__ plan = jobs[blockIdx.y].plan;
+  float* __restrict__ nodes = jobs[blockIdx.y].nodes;
   if (plan->bad || lvl >= plan->levels) return;
   const int nx = plan->nx[lvl];
   const int all = nx * plan->ny[lvl];
@@ -463,11 +483,7 @@ __global__ __launch_bounds__(256) void k_tree_keys(const Plan* __restrict__ plan
                                                    uint32_t* __restrict__ keys) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= m) return;
-  // both axes in the same scale, the longer side spanning the curve
-  const float scale = (float)(1 << hbits) / (float)max(plan->ncol, plan->nrow);
-  const int tx = knn::clamp_cell((qx[q] - plan->minx) * plan->inv * scale, 1 << hbits);
-  const int ty = knn::clamp_cell((qy[q] - plan->miny) * plan->inv * scale, 1 << hbits);
-  keys[q] = hilbert(hbits, (uint32_t)tx, (uint32_t)ty);
+  keys[q] = tile(plan, hbits, qx[q], qy[q]);
 }
 
 // ---------------------------------------------------------------- evaluation
@@ -771,18 +787,17 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 // which four wavefronts a SIMD do not hide altogether (three, five and six were slower: 1.47 ms of
 // summation with four, 1.60 with three, 1.51 with five and six, whose registers spill).
 // Measured, whole summation: 2^20 uniform 209 -> 1.6 ms, 2^18 mixture 13.3 -> 0.9 ms.
-__global__ __launch_bounds__(512, 4) void k_tree_eval(const Plan* __restrict__ plan,
-                                                    const int32_t* __restrict__ cell_start,
-                                                    const float* __restrict__ tx, const float* __restrict__ ty,
-                                                    const float* __restrict__ tz, const float* __restrict__ nodes,
-                                                    const float* __restrict__ qx, const float* __restrict__ qy,
-                                                    const float* __restrict__ alpha_f,
-                                                    const float* __restrict__ d1sq,
-                                                    const uint32_t* __restrict__ perm, int m, uint32_t fast_mask,
-                                                    Thresholds thr, float* __restrict__ qz) {
+// Output: qz, or with PARTIAL the float64 (num, den).
+template <typename Jobs, bool PARTIAL>
+__global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, const float* __restrict__ tx,
+                                                      const float* __restrict__ ty, const float* __restrict__ tz,
+                                                      const float* __restrict__ qx, const float* __restrict__ qy,
+                                                      const float* __restrict__ alpha_f,
+                                                      const float* __restrict__ d1sq,
+                                                      const uint32_t* __restrict__ perm, Thresholds thr,
+                                                      float* __restrict__ qz, double2* __restrict__ partial) {
   // per wavefront: a record, the stack of opened squares, and with S > 1 the sums of its queries
   extern __shared__ __align__(16) unsigned char s_mem[];
-  if (off(plan)) return;
   const int lane = threadIdx.x & 63;
   const int wave = uniform((int)threadIdx.x >> 6);
   const int S = uniform((int)blockDim.x >> 6);
@@ -798,8 +813,22 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(const Plan* __restrict__ p
     const int base = grp / span * span, r = grp - base;
     if (base + span <= (int)gridDim.x) grp = base + (r & 7) * kChunkGroups + (r >> 3);
   }
-  const int p0 = grp * kGroup;
-  const int nq = min(kGroup, m - p0);
+  int at = 0;  // the group's job: the last one whose first group is not past it
+  for (int hi = njobs - 1; at < hi;) {
+    const int mid = (at + hi + 1) >> 1;
+    if (jobs[mid].group0 <= grp)
+      at = mid;
+    else
+      hi = mid - 1;
+  }
+  const Job& job = jobs[at];
+  const Plan* __restrict__ plan = job.plan;
+  if (off(plan)) return;
+  const int32_t* __restrict__ cell_start = job.cell_start;
+  const float* __restrict__ nodes = job.nodes;
+  const uint32_t fast_mask = job.fast_mask;
+  const int p0 = job.q0 + (grp - job.group0) * kGroup;
+  const int nq = min(kGroup, job.q0 + job.m - p0);
   const uint32_t q = perm[p0 + min(lane, nq - 1)];
   const float fx = qx[q], fy = qy[q], alpha = alpha_f[q], d1 = d1sq[q];
   // the group's class: the integer power that all its queries have, 0 if none has one; a mixed group
@@ -903,7 +932,6 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(const Plan* __restrict__ p
     const float amin = wave_min(counts ? alpha : INFINITY), amax = wave_max(counts ? alpha : 0.0f);
     // a square's share of a query's sums is at most (1 + rho)^alpha, rho < 0.4715
     const float lcap = amax * kLogRim;
-    const int cls = pw;
     for (int l0 = 0; l0 < levels; ++l0) {
       const float h0 = (float)plan->h[l0];
       // log2 of the largest weight per unit of a query's sums, for a square at distance h0
@@ -959,7 +987,7 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(const Plan* __restrict__ p
         int tier = kTiers;
 #pragma unroll
         for (int i = kTiers - 1; i >= 0; --i)
-          if (!(lq + (float)(2 * i + 3) * lrho > thr.v[cls][i])) tier = i;
+          if (!(lq + (float)(2 * i + 3) * lrho > (pw ? thr.v[pw][i] : job.thr0[i]))) tier = i;
         // the float32 roundings of the moments grow by (1 - rho)^-alpha: a square close by that holds
         // much of the sums is opened, its parts are relatively farther
         if (lrho > -2.0f && lq - amax * __builtin_amdgcn_logf(1.0f - __builtin_amdgcn_exp2f(lrho)) > 0.0f)
@@ -1005,7 +1033,12 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(const Plan* __restrict__ p
       }
       __syncthreads();
     }
-    if (in && wave == 0) qz[q] = (float)(num / den);
+    if (in && wave == 0) {
+      if constexpr (PARTIAL)
+        partial[job.out0 + q] = make_double2(num, den);
+      else
+        qz[q] = (float)(num / den);
+    }
   }
 }
 
@@ -1015,7 +1048,7 @@ inline int div_up(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 namespace tree {
 
-int node_capacity(int64_t n) { return (int)(n / 12 + 4096); }
+int node_capacity(int64_t n) { return (int)(n / 12 + 512); }
 
 int hilbert_bits(int64_t n) {
   int b = 1;
@@ -1031,60 +1064,107 @@ size_t node_bytes(int64_t n) { return sizeof(float) * (size_t)kRec * node_capaci
 
 }  // namespace tree
 
-// Thresholds of the truncation: the terms of order o of one square sum to at most
-// w0 C_o(alpha) rho^o times its count (or sum |z|), C_o = Gamma(o + alpha) / (Gamma(alpha) o!) the
-// Gegenbauer bound and rho = (half diagonal) / distance; they may reach 2^-22 of the query's sums.
-static Thresholds make_thresholds(double max_level) {
+// Bound of the truncation: the terms of order o of one square sum to at most w0 C_o(alpha) rho^o
+// times its count (or sum |z|), C_o = Gamma(o + alpha) / (Gamma(alpha) o!) the Gegenbauer bound and
+// rho = (half diagonal) / distance; they may reach 2^-22 of the query's sums.
+static float order_bound(double alpha, int tier) {
+  const int o = 2 * tier + 3;
+  return (float)(-22.0 - (lgamma(o + alpha) - lgamma(alpha) - lgamma(o + 1.0)) / M_LN2);
+}
+
+static Thresholds class_bounds() {
   Thresholds t{};
-  for (int c = 0; c < kClasses; ++c) {
-    const double a = c == 0 ? max_level : (double)c;
-    for (int i = 0; i < kTiers; ++i) {
-      const int o = 2 * i + 3;
-      t.v[c][i] = (float)(-22.0 - (lgamma(o + a) - lgamma(a) - lgamma(o + 1.0)) / M_LN2);
-    }
-  }
+  for (int c = 1; c < kClasses; ++c)
+    for (int i = 0; i < kTiers; ++i) t.v[c][i] = order_bound((double)c, i);
   return t;
 }
 
-hipError_t launch_tree_build(const GridScalars* gs, const int32_t* cell_start, const float* sx, const float* sy,
-                             const int32_t* sidx, const float* z, int n, tree::Plan* plan, float* tx,
-                             float* ty, float* tz, float* nodes, uint32_t* zero_word, hipStream_t s) {
-  const int cap = tree::node_capacity(n);
-  // levels of a square box's tree, and two more for other shapes; a longer strip's top level
-  // simply has more squares
-  int level_cap = 3;
-  while (level_cap < tree::kLevels && ((int64_t)(kLeafPoints / 2 * kTopSide * kTopSide) << (2 * (level_cap - 3))) < n)
-    ++level_cap;
-  hipLaunchKernelGGL(k_tree_plan, dim3(1), dim3(64), 0, s, gs, n, cap, level_cap, plan, zero_word);
-  const int npad = tree::padded_points(n);
-  hipLaunchKernelGGL(k_tree_gather, dim3(div_up(npad, 256)), dim3(256), 0, s, sx, sy, sidx, z, n, npad, tx, ty, tz,
-                     plan);
+void tree::fill_job(Job* j, int64_t n, const double* levels) {
+  j->n = (int32_t)n;
+  j->node_cap = node_capacity(n);
+  // levels of a square box's tree, and two more for other shapes; a longer strip's top level simply
+  // has more squares
+  j->level_cap = 3;
+  while (j->level_cap < kLevels && ((int64_t)(kLeafPoints / 2 * kTopSide * kTopSide) << (2 * (j->level_cap - 3))) < n)
+    ++j->level_cap;
+  double top = 0.0;
+  j->fast_mask = 0;
+  for (int i = 0; i < 5; ++i) {
+    top = fmax(top, levels[i]);
+    if (levels[i] >= 1.0 && levels[i] <= 8.0 && levels[i] == floor(levels[i])) j->fast_mask |= 1u << (int)levels[i];
+  }
+  for (int i = 0; i < kTiers; ++i) j->thr0[i] = order_bound(top, i);
+}
+
+namespace {
+
+template <typename Jobs>
+void launch_plan(const Jobs& jobs, int njobs, uint32_t* zero_word, hipStream_t s) {
+  hipLaunchKernelGGL(k_tree_plan<Jobs>, dim3(njobs), dim3(64), 0, s, jobs, zero_word);
+}
+
+// n, level_cap: of the largest job
+template <typename Jobs>
+void launch_moments(const Jobs& jobs, int njobs, int64_t n, int level_cap, const float* tx, const float* ty,
+                    const float* tz, hipStream_t s) {
   // squares of level 1 of a square box; a workgroup loops where a ragged shape has more
   int64_t blocks = n / (4 * kLeafPoints) + 64;
-  hipLaunchKernelGGL(k_tree_p2m, dim3((unsigned)blocks), dim3(256), 0, s, plan, cell_start, tx, ty, tz, nodes);
+  hipLaunchKernelGGL(k_tree_p2m<Jobs>, dim3((unsigned)blocks, njobs), dim3(256), 0, s, jobs, tx, ty, tz);
   for (int l = 2; l < level_cap; ++l) {
     blocks = blocks / 4 + 16;
-    hipLaunchKernelGGL(k_tree_m2m, dim3((unsigned)blocks), dim3(256), 0, s, plan, l, nodes);
+    hipLaunchKernelGGL(k_tree_m2m<Jobs>, dim3((unsigned)blocks, njobs), dim3(256), 0, s, jobs, l);
   }
+}
+
+template <typename Jobs, bool PARTIAL>
+void launch_eval(const Jobs& jobs, int njobs, int groups, const float* tx, const float* ty, const float* tz,
+                 const float* qx, const float* qy, const float* alpha_f, const float* d1sq, const uint32_t* perm,
+                 float* qz, double2* partial, hipStream_t s) {
+  int S = 1;
+  while (S < 8 && groups * S < 16384) S *= 2;  // wavefronts to fill the chip four times over
+  const size_t lds = (size_t)S * (4 * (kRec + kStack) + (S > 1 ? kGroup * (sizeof(double2) + sizeof(float)) : 0));
+  hipLaunchKernelGGL((k_tree_eval<Jobs, PARTIAL>), dim3(groups), dim3(64 * S), lds, s, jobs, njobs, tx, ty, tz, qx, qy,
+                     alpha_f, d1sq, perm, class_bounds(), qz, partial);
+}
+
+}  // namespace
+
+hipError_t launch_tree_build(const tree::Job& job, const float* sx, const float* sy, const int32_t* sidx,
+                             const float* z, float* tx, float* ty, float* tz, uint32_t* zero_word, hipStream_t s) {
+  launch_plan(OneJob{job}, 1, zero_word, s);
+  const int npad = tree::padded_points(job.n);
+  hipLaunchKernelGGL(k_tree_gather, dim3(div_up(npad, 256)), dim3(256), 0, s, sx, sy, sidx, z, job.n, npad, tx, ty, tz,
+                     job.plan);
+  launch_moments(OneJob{job}, 1, job.n, job.level_cap, tx, ty, tz, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_tree_eval(const tree::Job& job, const float* tx, const float* ty, const float* tz, const float* qx,
+                            const float* qy, const float* alpha_f, const float* d1sq, const uint32_t* perm, float* qz,
+                            hipStream_t s) {
+  launch_eval<OneJob, false>(OneJob{job}, 1, div_up(job.m, kGroup), tx, ty, tz, qx, qy, alpha_f, d1sq, perm, qz,
+                             nullptr, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_tree_plans(const tree::Job* jobs, int njobs, hipStream_t s) {
+  launch_plan(ManyJobs{jobs}, njobs, nullptr, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_tree_batch(const tree::Job* jobs, int njobs, int64_t max_n, int max_levels, int groups,
+                             const float* tx, const float* ty, const float* tz, const float* qx, const float* qy,
+                             const float* alpha_f, const float* d1sq, const uint32_t* perm, double2* partial,
+                             hipStream_t s) {
+  launch_moments(ManyJobs{jobs}, njobs, max_n, max_levels, tx, ty, tz, s);
+  launch_eval<ManyJobs, true>(ManyJobs{jobs}, njobs, groups, tx, ty, tz, qx, qy, alpha_f, d1sq, perm, nullptr, partial,
+                              s);
   return hipGetLastError();
 }
 
 hipError_t launch_tree_keys(const tree::Plan* plan, const float* qx, const float* qy, int m, int hbits, uint32_t* keys,
                             hipStream_t s) {
   hipLaunchKernelGGL(k_tree_keys, dim3(div_up(m, 256)), dim3(256), 0, s, plan, qx, qy, m, hbits, keys);
-  return hipGetLastError();
-}
-
-hipError_t launch_tree_eval(tree::Plan* plan, const int32_t* cell_start, const float* tx, const float* ty,
-                            const float* tz, const float* nodes, const float* qx, const float* qy,
-                            const float* alpha_f, const float* d1sq, const uint32_t* perm, int m,
-                            uint32_t fast_mask, double max_level, float* qz, hipStream_t s) {
-  const int groups = div_up(m, kGroup);
-  int S = 1;
-  while (S < 8 && groups * S < 16384) S *= 2;  // wavefronts to fill the chip four times over
-  const size_t lds = (size_t)S * (4 * (kRec + kStack) + (S > 1 ? kGroup * (sizeof(double2) + sizeof(float)) : 0));
-  hipLaunchKernelGGL(k_tree_eval, dim3(groups), dim3(64 * S), lds, s, plan, cell_start, tx, ty, tz, nodes, qx, qy,
-                     alpha_f, d1sq, perm, m, fast_mask, make_thresholds(max_level), qz);
   return hipGetLastError();
 }
 

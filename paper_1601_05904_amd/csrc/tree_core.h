@@ -16,6 +16,7 @@
 #include <stdint.h>
 
 #include "aidw_internal.h"
+#include "knn_core.h"
 
 namespace aidw {
 namespace tree {
@@ -73,6 +74,20 @@ constexpr float kZLimit = 1.2676506002282294e30f;  // 2^100
 
 __device__ inline bool off(const Plan* p) { return p->bad != 0; }
 
+// One job's share of the arrays that the jobs of a launch have in common.
+struct Job {
+  const GridScalars* gs;
+  Plan* plan;
+  const int32_t* cell_start;  // the job's cells; their entries index the common point arrays
+  float* nodes;               // node_cap records
+  int32_t n, node_cap, level_cap;
+  int32_t q0, m;              // its queries: positions [q0, q0 + m) of the query order
+  int32_t group0;             // its first group of kGroup queries
+  uint32_t fast_mask;         // integer alpha classes that have their own weights
+  int64_t out0;               // double2 output: query q at out0 + q
+  float thr0[kTiers];         // log2 bounds of the orders for a group of general alpha
+};
+
 // Centre of a square, the same float32 values wherever they are needed.
 __device__ inline void centre(const Plan* p, int lvl, int ix, int iy, float& cx, float& cy) {
   const double h = p->h[lvl];
@@ -102,10 +117,17 @@ __host__ __device__ inline uint32_t hilbert(int bits, uint32_t x, uint32_t y) {
   return d;
 }
 
-// log2 of the bounds of the orders: thr[c][t] bounds Q rho^(P + 1), P = 2 t + 2, for class c.
+// log2 of the bounds of the orders for the integer classes: v[c][t] bounds Q rho^(P + 1), P = 2 t + 2.
 struct Thresholds {
   float v[kClasses][kTiers];
 };
+
+// Hilbert index of a query's tile, both axes in the same scale, the longer side spanning the curve.
+__device__ inline uint32_t tile(const Plan* p, int hbits, float x, float y) {
+  const float scale = (float)(1 << hbits) / (float)max(p->ncol, p->nrow);
+  return hilbert(hbits, (uint32_t)knn::clamp_cell((x - p->minx) * p->inv * scale, 1 << hbits),
+                 (uint32_t)knn::clamp_cell((y - p->miny) * p->inv * scale, 1 << hbits));
+}
 
 }  // namespace tree
 }  // namespace aidw

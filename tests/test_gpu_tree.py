@@ -236,3 +236,51 @@ def test_streams_share_nothing(T):
         got = [aidw.run(*s, p, stream=st) for s, st in zip(sets, streams)]
         T.cuda.synchronize()
         assert all(T.equal(a, b) for a, b in zip(got, want))
+
+
+def test_batch_jobs(T):
+    """Jobs on both sides of the batched form's size rule in one plan, replayed as a graph after the
+    fields change, against Eq. 1 in float64: uneven kinds and levels, a job whose z holds a NaN, one
+    with a leaf of very many points, one without an area."""
+    aidw = aidw_mod()
+    import paper_1601_05904_amd.batch as B
+    specs = [(8191, 700, "uniform", {}), (8192, 256, "uniform", {}), (8192, 255, "mixture", {}), (20011, 9001, "mixture", {}),
+             (30000, 12000, "mixture", dict(levels=(0.5, 1.25, 2.0, 3.5, 7.0))), (40000, 3000, "uniform", dict(levels=(1, 2, 3, 4, 9))),
+             (10000, 5000, "uniform", {}), (40000, 2000, "uniform", {}), (9000, 500, "uniform", {}), (500, 30000, "uniform", {})]
+    jobs = []
+    for i, (n, m, kind, kw) in enumerate(specs):
+        d = make(n, m, 870 + i, kind)
+        if i == 6:
+            d[2][11] = np.nan
+        if i == 7:
+            d[0][:30000] = W.quantise(0.5 + 1e-4 * np.random.default_rng(1).random(30000))
+            d[1][:30000] = W.quantise(0.5 + 1e-4 * np.random.default_rng(2).random(30000))
+        if i == 8:
+            d[0][:] = d[3][:] = 0.25
+        jobs.append(B.Job(*(T.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to("cuda") for a in d),
+                          params=aidw.Params(k=10, **kw)))
+    plan = B.Plan(jobs, B.Config(use_graph=1), want_alpha=True)
+    side = T.cuda.Stream()
+    T.cuda.synchronize()
+    for rep in range(3):
+        if rep:
+            for jb in jobs:
+                jb.z.mul_(1.5).add_(0.125)
+            T.cuda.synchronize()
+        plan.run(side)
+        assert plan.status(side) == [aidw.OK] * 8 + [aidw.EDEGENERATE, aidw.OK]
+        for i, jb in enumerate(jobs):
+            if i == 8 or i == 6:
+                assert bool(T.isnan(plan.qz[i]).all())
+                continue
+            sel = T.arange(0, plan.qz[i].numel(), max(1, plan.qz[i].numel() // 100), device="cuda")
+            ref, norm = reference(T, jb.x, jb.y, jb.z, jb.qx, jb.qy, plan.alpha[i], sel)
+            e = (plan.qz[i][sel].double() - ref).abs() / T.maximum(ref.abs(), norm)
+            assert float(e.max()) <= MAX_TOL, (rep, i, float(e.max()))
+    direct = B.Plan(jobs, B.Config(), want_alpha=True)
+    direct.run()
+    T.cuda.synchronize()
+    for a, b in zip(plan.qz, direct.qz):
+        assert T.equal(a.nan_to_num(7.0), b.nan_to_num(7.0))
+    for p in (plan, direct):
+        p.close()
