@@ -340,9 +340,10 @@ size_t mlp_batch_scratch_floats(int B);
 // grad [AIDW_MLP_PARAMS + 1]: the batch gradient, then the batch's mean squared error.
 hipError_t launch_mlp_gradients(const MlpDevice& d, const float* feat, const float* target, const uint32_t* sel, int B,
                                 float* scratch, float* grad, hipStream_t s);
-hipError_t launch_adam(const MlpDevice& d, const float* grad, float lr, float b1, float b2, float eps, float bc1,
-                       float bc2, hipStream_t s);
-hipError_t launch_accumulate_loss(const float* grad, float* epoch_loss, int epoch, float scale, hipStream_t s);
+// One training step: the batch's gradient, Adam, the bf16 copies, and *epoch_loss += loss * loss_scale.
+hipError_t launch_mlp_step(const MlpDevice& d, const float* feat, const float* target, const uint32_t* sel, int B,
+                           float* scratch, float lr, float b1, float b2, float eps, float bc1, float bc2,
+                           float* epoch_loss, float loss_scale, hipStream_t s);
 // Pair-kernel class keys from a given alpha (alpha == p in 1..8 -> p, else 0) and the identity permutation;
 // the coincident-query list as launch_alpha_class.
 hipError_t launch_class_keys(const float* alpha_f, int m, uint32_t* keys, uint32_t* vals, const float* d1sq,

@@ -1226,13 +1226,12 @@ aidw_status aidw_mlp_train(aidw_mlp* mlp, const float* feat, const float* target
   const int nb = (N + B - 1) / B;
   Temps t(stream);
   uint32_t *keys, *vals, *tk, *tv, *hist, *scan;
-  float *scratch, *grad, *eloss;
+  float *scratch, *eloss;
   hipError_t e;
   if ((e = t.get(&keys, N)) != hipSuccess || (e = t.get(&vals, N)) != hipSuccess || (e = t.get(&tk, N)) != hipSuccess ||
       (e = t.get(&tv, N)) != hipSuccess || (e = t.get(&hist, radix_hist_words(N))) != hipSuccess ||
       (e = t.get(&scan, radix_scan_tmp_words(N))) != hipSuccess ||
-      (e = t.get(&scratch, mlp_batch_scratch_floats(B))) != hipSuccess || (e = t.get(&grad, kP + 1)) != hipSuccess ||
-      (e = t.get(&eloss, epochs)) != hipSuccess)
+      (e = t.get(&scratch, mlp_batch_scratch_floats(B))) != hipSuccess || (e = t.get(&eloss, epochs)) != hipSuccess)
     return hip_fail(e, "allocating training buffers");
   HIP_TRY(hipMemsetAsync(eloss, 0, sizeof(float) * epochs, stream), "clearing losses");
   const double b1 = 0.9, b2 = 0.999;
@@ -1241,12 +1240,11 @@ aidw_status aidw_mlp_train(aidw_mlp* mlp, const float* feat, const float* target
     HIP_TRY(radix_sort_pairs(keys, vals, tk, tv, N, 32, hist, scan, stream), "shuffle sort");
     for (int bi = 0; bi < nb; ++bi) {
       const int start = bi * B, cnt = N - start < B ? N - start : B;
-      HIP_TRY(launch_mlp_gradients(mlp->d, feat, target, vals + start, cnt, scratch, grad, stream), "gradient kernels");
       mlp->step += 1;
       const float bc1 = (float)(1.0 - pow(b1, (double)mlp->step)), bc2 = (float)(1.0 - pow(b2, (double)mlp->step));
-      HIP_TRY(launch_adam(mlp->d, grad, lr, (float)b1, (float)b2, 1e-8f, bc1, bc2, stream), "Adam kernel");
-      HIP_TRY(launch_mlp_repack(mlp->d, stream), "repack kernel");
-      HIP_TRY(launch_accumulate_loss(grad, eloss, ep, 1.0f / (float)nb, stream), "loss kernel");
+      HIP_TRY(launch_mlp_step(mlp->d, feat, target, vals + start, cnt, scratch, lr, (float)b1, (float)b2, 1e-8f, bc1,
+                              bc2, eloss + ep, 1.0f / (float)nb, stream),
+              "training step");
     }
   }
   if (epoch_loss) {

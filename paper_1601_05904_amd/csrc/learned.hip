@@ -10,10 +10,9 @@
 // the tanh form u / 2 (1 + tanh(sqrt(2 / pi) (u + 0.044715 u^3))).  Inference
 // (the learned run's fused front and aidw_mlp_forward) runs the network on the
 // matrix cores (see mlp_tile).  Training: per-sample forward and backward in one
-// kernel (one sample per lane, v_dot2c_f32_bf16 dot products whose weight pairs,
-// the same for every lane, are scalar operands), the weight gradients summed
-// over the batch in a fixed order, then Adam on the float32 master weights and a
-// repack of the bf16 copies.
+// kernel (one sample per wavefront, one hidden unit per lane, bf16 dot products
+// over the inputs in order), the weight gradients summed over the batch in a fixed
+// order, then Adam on the float32 master weights and the bf16 copies in one kernel.
 #include <float.h>
 
 #include "aidw_internal.h"
@@ -30,6 +29,7 @@ constexpr int kH = 64;
 constexpr int kHPairs = 32;
 
 typedef float float2v_t __attribute__((ext_vector_type(2)));
+typedef float float4v_t __attribute__((ext_vector_type(4)));
 
 // float32 -> bfloat16, round to nearest, ties to even (the hardware conversion)
 __device__ inline uint32_t bf16_bits(float f) { return (uint32_t)__builtin_bit_cast(unsigned short, (__bf16)f); }
@@ -161,155 +161,267 @@ constexpr int kOffW1 = 0, kOffB1 = 64 * 27, kOffW2 = kOffB1 + 64, kOffB2 = kOffW
               kOffB3 = kOffW3 + 64, kParams = kOffB3 + 1;
 static_assert(kParams == AIDW_MLP_PARAMS, "parameter layout");
 
-__device__ inline void load_x(const float* __restrict__ f, uint32_t* xp) {
+// One sample per wavefront, one hidden unit per lane: forward, loss term, and the per-sample
+// backward down to the pre-activation gradients; saves the operands of the weight gradients,
+// sample-major.  A lane keeps its rows of W1 and W2 and its column of W2 in registers over the
+// samples of its wavefront; the activations, each lane's own, reach the others as scalar operands
+// (readlane), so every dot product runs over its inputs in order, as one lane doing all units would.
+// What bounds it: the chain of about 300 dependent steps of a sample; with one lane doing a whole
+// sample it was 12,000 (1024 samples: 71 -> 6 us).
+constexpr int kSampleWaves = 4;
+__global__ __launch_bounds__(64 * kSampleWaves) void k_mlp_train_sample(
+    MlpWeights w, const float* __restrict__ feat, const float* __restrict__ target, const uint32_t* __restrict__ sel,
+    int B, float two_over_b, float* __restrict__ s_x, float* __restrict__ s_h1, float* __restrict__ s_h2,
+    float* __restrict__ s_da1, float* __restrict__ s_da2, float* __restrict__ s_dy, float* __restrict__ s_err2) {
+  const int o = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kSampleWaves + (threadIdx.x >> 6)));
+  if (wave >= B) return;
+  uint32_t w1[kInPairs], w2[kHPairs];
+  float w2c[kH];
 #pragma unroll
-  for (int p = 0; p < kInPairs; ++p) {
-    const float lo = f[2 * p];
-    const float hi = 2 * p + 1 < kIn ? f[2 * p + 1] : 0.0f;
-    xp[p] = pack_bf16(lo, hi);
-  }
-}
-
-// a1 = W1 x + b1 for one output row
-__device__ inline float layer1_row(const MlpWeights& w, const uint32_t* xp, int o) {
-  float acc = w.master[kOffB1 + o];
+  for (int p = 0; p < kInPairs; ++p) w1[p] = w.w1p[o * kInPairs + p];
 #pragma unroll
-  for (int p = 0; p < kInPairs; ++p) acc = dot2(w.w1p[o * kInPairs + p], xp[p], acc);
-  return acc;
-}
-__device__ inline float layer2_row(const MlpWeights& w, const uint32_t* hp, int o) {
-  float acc = w.master[kOffB2 + o];
+  for (int p = 0; p < kHPairs; ++p) w2[p] = w.w2p[o * kHPairs + p];
 #pragma unroll
-  for (int p = 0; p < kHPairs; ++p) acc = dot2(w.w2p[o * kHPairs + p], hp[p], acc);
-  return acc;
-}
-__device__ inline float layer3(const MlpWeights& w, const uint32_t* hp) {
-  float acc = w.master[kOffB3];
+  for (int i = 0; i < kH; ++i) w2c[i] = w.w2r[i * kH + o];
+  const float b1 = w.master[kOffB1 + o], b2 = w.master[kOffB2 + o], b3 = w.master[kOffB3], w3 = w.w3r[o];
+  // the bf16 pair that holds this lane's unit (units 2 p and 2 p + 1 in both lanes)
+  auto pair_of = [&](float h) {
+    const float other = __shfl_xor(h, 1, 64);
+    return pack_bf16((o & 1) ? other : h, (o & 1) ? h : other);
+  };
+  auto own = [&](uint32_t pr) { return __uint_as_float((o & 1) ? (pr & 0xFFFF0000u) : (pr << 16)); };
+  for (int b = wave; b < B; b += gridDim.x * kSampleWaves) {
+    const int j = sel ? (int)sel[b] : b;
+    const float* __restrict__ f = feat + (size_t)j * kIn;
+    float a1 = b1;
 #pragma unroll
-  for (int p = 0; p < kHPairs; ++p) acc = dot2(w.w3p[p], hp[p], acc);
-  return acc;
-}
-
-// One sample per lane: forward, loss term, and the per-sample backward down to the
-// pre-activation gradients; saves the operands of the weight gradients, sample-major.
-__global__ __launch_bounds__(64) void k_mlp_train_sample(MlpWeights w, const float* __restrict__ feat,
-                                                         const float* __restrict__ target,
-                                                         const uint32_t* __restrict__ sel, int B, float two_over_b,
-                                                         float* __restrict__ s_x, float* __restrict__ s_h1,
-                                                         float* __restrict__ s_h2, float* __restrict__ s_da1,
-                                                         float* __restrict__ s_da2, float* __restrict__ s_dy,
-                                                         float* __restrict__ s_err2) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const int j = sel ? (int)sel[b] : b;
-  uint32_t xp[kInPairs], h1p[kHPairs], h2p[kHPairs];
-  float a1[kH], a2[kH];
-  load_x(feat + (size_t)j * kIn, xp);
+    for (int p = 0; p < kInPairs; ++p)
+      a1 = dot2(w1[p], pack_bf16(f[2 * p], 2 * p + 1 < kIn ? f[2 * p + 1] : 0.0f), a1);
+    const uint32_t h1 = pair_of(gelu_f(a1));
+    float a2 = b2;
 #pragma unroll
-  for (int o = 0; o < kH; o += 2) {
-    a1[o] = layer1_row(w, xp, o);
-    a1[o + 1] = layer1_row(w, xp, o + 1);
-    h1p[o / 2] = pack_bf16(gelu_f(a1[o]), gelu_f(a1[o + 1]));
-  }
+    for (int p = 0; p < kHPairs; ++p) a2 = dot2(w2[p], (uint32_t)__builtin_amdgcn_readlane((int)h1, 2 * p), a2);
+    const uint32_t h2 = pair_of(gelu_f(a2));
+    float y = b3;
 #pragma unroll
-  for (int o = 0; o < kH; o += 2) {
-    a2[o] = layer2_row(w, h1p, o);
-    a2[o + 1] = layer2_row(w, h1p, o + 1);
-    h2p[o / 2] = pack_bf16(gelu_f(a2[o]), gelu_f(a2[o + 1]));
-  }
-  const float y = layer3(w, h2p);
-  const float err = y - target[j];
-  const float dy = two_over_b * err;
-  s_dy[b] = dy;
-  s_err2[b] = err * err;
-#pragma unroll
-  for (int p = 0; p < kInPairs; ++p) {
-    s_x[(size_t)b * 28 + 2 * p] = __uint_as_float(xp[p] << 16);
-    s_x[(size_t)b * 28 + 2 * p + 1] = __uint_as_float(xp[p] & 0xFFFF0000u);
-  }
-#pragma unroll
-  for (int p = 0; p < kHPairs; ++p) {
-    s_h1[(size_t)b * kH + 2 * p] = __uint_as_float(h1p[p] << 16);
-    s_h1[(size_t)b * kH + 2 * p + 1] = __uint_as_float(h1p[p] & 0xFFFF0000u);
-    s_h2[(size_t)b * kH + 2 * p] = __uint_as_float(h2p[p] << 16);
-    s_h2[(size_t)b * kH + 2 * p + 1] = __uint_as_float(h2p[p] & 0xFFFF0000u);
-  }
-  // da2 = dy * W3 * gelu'(a2)
-#pragma unroll
-  for (int i = 0; i < kH; ++i) {
-    a2[i] = dy * w.w3r[i] * gelu_grad_f(a2[i]);
-    s_da2[(size_t)b * kH + i] = a2[i];
-  }
-  // da1 = (W2^T da2) * gelu'(a1)
-#pragma unroll
-  for (int c = 0; c < kH; ++c) {
+    for (int p = 0; p < kHPairs; ++p) y = dot2(w.w3p[p], (uint32_t)__builtin_amdgcn_readlane((int)h2, 2 * p), y);
+    const float err = y - target[j];
+    const float dy = two_over_b * err;
+    if (o == 0) {
+      s_dy[b] = dy;
+      s_err2[b] = err * err;
+    }
+    if (o < 28) s_x[(size_t)b * 28 + o] = o < kIn ? bf16_round(f[o]) : 0.0f;
+    s_h1[(size_t)b * kH + o] = own(h1);
+    s_h2[(size_t)b * kH + o] = own(h2);
+    // da2 = dy * W3 * gelu'(a2)
+    const float da2 = dy * w3 * gelu_grad_f(a2);
+    s_da2[(size_t)b * kH + o] = da2;
+    // da1 = (W2^T da2) * gelu'(a1)
     float acc = 0.0f;
 #pragma unroll
-    for (int i = 0; i < kH; ++i) acc = __builtin_fmaf(w.w2r[i * kH + c], a2[i], acc);
-    s_da1[(size_t)b * kH + c] = acc * gelu_grad_f(a1[c]);
+    for (int i = 0; i < kH; ++i)
+      acc = __builtin_fmaf(w2c[i], __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(da2), i)), acc);
+    s_da1[(size_t)b * kH + o] = acc * gelu_grad_f(a1);
   }
 }
 
 // Weight gradients: grad[p] = sum over the batch of the parameter's two operands;
 // grad[kParams] = mean squared error of the batch.  The batch is cut into
 // kGradChunks contiguous chunks (blockIdx.y); each chunk's sum runs in sample
-// order, then k_mlp_wgrad_sum adds the chunks in chunk order.
+// order, then the chunks are added in chunk order.  blockIdx.x takes a quarter of
+// the hidden units (rows): wavefront 0 the rows of W2, 4 x 4 parameters per lane,
+// wavefront 1 those of W1 likewise, wavefront 2 the biases, W3 and the loss.  The
+// operands of 64 samples at a time are staged in LDS, so a value is loaded once per
+// workgroup instead of once per parameter (1024 samples: 20 -> 7 us).
 constexpr int kGradChunks = 16;
+constexpr int kGradParts = 4;
+constexpr int kGradRows = kH / kGradParts;
+constexpr int kGradTile = 64;
 
-__global__ __launch_bounds__(256) void k_mlp_wgrad(int B, const float* __restrict__ s_x,
+__global__ __launch_bounds__(192) void k_mlp_wgrad(int B, const float* __restrict__ s_x,
                                                    const float* __restrict__ s_h1, const float* __restrict__ s_h2,
                                                    const float* __restrict__ s_da1, const float* __restrict__ s_da2,
                                                    const float* __restrict__ s_dy, const float* __restrict__ s_err2,
                                                    float* __restrict__ part) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p > kParams) return;
+  __shared__ __align__(16) float t_h1[kGradTile][kH];
+  __shared__ __align__(16) float t_da2[kGradTile][kGradRows], t_da1[kGradTile][kGradRows], t_h2[kGradTile][kGradRows];
+  __shared__ __align__(16) float t_x[kGradTile][28];
+  __shared__ float t_dy[kGradTile], t_err[kGradTile];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int row0 = blockIdx.x * kGradRows;
   const int per = (B + kGradChunks - 1) / kGradChunks;
   const int b0 = blockIdx.y * per, b1 = min(B, b0 + per);
-  float acc = 0.0f;
-  if (p < kOffB1) {
-    const int o = p / kIn, i = p % kIn;
-    for (int b = b0; b < b1; ++b) acc = __builtin_fmaf(s_da1[(size_t)b * kH + o], s_x[(size_t)b * 28 + i], acc);
-  } else if (p < kOffW2) {
-    const int o = p - kOffB1;
-    for (int b = b0; b < b1; ++b) acc += s_da1[(size_t)b * kH + o];
-  } else if (p < kOffB2) {
-    const int o = (p - kOffW2) / kH, i = (p - kOffW2) % kH;
-    for (int b = b0; b < b1; ++b) acc = __builtin_fmaf(s_da2[(size_t)b * kH + o], s_h1[(size_t)b * kH + i], acc);
-  } else if (p < kOffW3) {
-    const int o = p - kOffB2;
-    for (int b = b0; b < b1; ++b) acc += s_da2[(size_t)b * kH + o];
-  } else if (p < kOffB3) {
-    const int i = p - kOffW3;
-    for (int b = b0; b < b1; ++b) acc = __builtin_fmaf(s_dy[b], s_h2[(size_t)b * kH + i], acc);
-  } else if (p == kOffB3) {
-    for (int b = b0; b < b1; ++b) acc += s_dy[b];
-  } else {
-    for (int b = b0; b < b1; ++b) acc += s_err2[b];
+  // wavefronts 0 and 1: rows r .. r + 3, columns c .. c + 3 of the part
+  const int cols = wave == 0 ? kH / 4 : 7;
+  const int r = 4 * (lane / cols), c = 4 * (lane % cols);
+  const bool tile_lane = wave == 0 || (wave == 1 && lane < 4 * 7);
+  float acc[4][4] = {};
+  float v = 0.0f;  // wavefront 2
+  for (int t0 = b0; t0 < b1; t0 += kGradTile) {
+    const int cnt = min(kGradTile, b1 - t0);
+    // a thread's loads are all in flight before the first is stored
+    constexpr int kT = 192, kNh = (kGradTile * kH / 4 + kT - 1) / kT, kNr = (kGradTile * kGradRows / 4 + kT - 1) / kT,
+                  kNx = (kGradTile * 7 + kT - 1) / kT;
+    float4v_t rh[kNh], r2[kNr], r1[kNr], rg[kNr], rx[kNx];
+    float rd = 0.0f, re = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kNh; ++u) {
+      const int i = min(tid + kT * u, cnt * (kH / 4) - 1);
+      rh[u] = reinterpret_cast<const float4v_t*>(s_h1 + (size_t)t0 * kH)[i];
+    }
+#pragma unroll
+    for (int u = 0; u < kNr; ++u) {
+      const int i = min(tid + kT * u, cnt * (kGradRows / 4) - 1);
+      const size_t at = ((size_t)(t0 + i / (kGradRows / 4)) * kH + row0) / 4 + i % (kGradRows / 4);
+      r2[u] = reinterpret_cast<const float4v_t*>(s_da2)[at];
+      r1[u] = reinterpret_cast<const float4v_t*>(s_da1)[at];
+      rg[u] = reinterpret_cast<const float4v_t*>(s_h2)[at];
+    }
+#pragma unroll
+    for (int u = 0; u < kNx; ++u) {
+      const int i = min(tid + kT * u, cnt * 7 - 1);
+      rx[u] = reinterpret_cast<const float4v_t*>(s_x + (size_t)t0 * 28)[i];
+    }
+    if (tid < cnt) {
+      rd = s_dy[t0 + tid];
+      re = s_err2[t0 + tid];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kNh; ++u)
+      if (tid + kT * u < cnt * (kH / 4)) reinterpret_cast<float4v_t*>(&t_h1[0][0])[tid + kT * u] = rh[u];
+#pragma unroll
+    for (int u = 0; u < kNr; ++u)
+      if (tid + kT * u < cnt * (kGradRows / 4)) {
+        reinterpret_cast<float4v_t*>(&t_da2[0][0])[tid + kT * u] = r2[u];
+        reinterpret_cast<float4v_t*>(&t_da1[0][0])[tid + kT * u] = r1[u];
+        reinterpret_cast<float4v_t*>(&t_h2[0][0])[tid + kT * u] = rg[u];
+      }
+#pragma unroll
+    for (int u = 0; u < kNx; ++u)
+      if (tid + kT * u < cnt * 7) reinterpret_cast<float4v_t*>(&t_x[0][0])[tid + kT * u] = rx[u];
+    if (tid < cnt) {
+      t_dy[tid] = rd;
+      t_err[tid] = re;
+    }
+    __syncthreads();
+    if (tile_lane) {
+#pragma unroll 4
+      for (int b = 0; b < cnt; ++b) {
+        const float4 d4 = *reinterpret_cast<const float4*>(wave == 0 ? &t_da2[b][r] : &t_da1[b][r]);
+        const float4 x4 = *reinterpret_cast<const float4*>(wave == 0 ? &t_h1[b][c] : &t_x[b][c]);
+        const float d[4] = {d4.x, d4.y, d4.z, d4.w}, x[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[i][k] = __builtin_fmaf(d[i], x[k], acc[i][k]);
+      }
+    } else if (wave == 2) {
+      if (lane < 16) {
+#pragma unroll 8
+        for (int b = 0; b < cnt; ++b) v += t_da1[b][lane];
+      } else if (lane < 32) {
+#pragma unroll 8
+        for (int b = 0; b < cnt; ++b) v += t_da2[b][lane - 16];
+      } else if (lane < 48) {
+#pragma unroll 8
+        for (int b = 0; b < cnt; ++b) v = __builtin_fmaf(t_dy[b], t_h2[b][lane - 32], v);
+      } else if (lane == 48) {
+#pragma unroll 8
+        for (int b = 0; b < cnt; ++b) v += t_dy[b];
+      } else if (lane == 49) {
+#pragma unroll 8
+        for (int b = 0; b < cnt; ++b) v += t_err[b];
+      }
+    }
   }
-  part[(size_t)blockIdx.y * (kParams + 1) + p] = acc;
+  float* out = part + (size_t)blockIdx.y * (kParams + 1);
+  if (tile_lane) {
+    const int off = wave == 0 ? kOffW2 : kOffW1, width = wave == 0 ? kH : kIn;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (c + k < width) out[off + (row0 + r + i) * width + c + k] = acc[i][k];
+  } else if (wave == 2) {
+    if (lane < 16)
+      out[kOffB1 + row0 + lane] = v;
+    else if (lane < 32)
+      out[kOffB2 + row0 + lane - 16] = v;
+    else if (lane < 48)
+      out[kOffW3 + row0 + lane - 32] = v;
+    else if (lane == 48 && blockIdx.x == 0)
+      out[kOffB3] = v;
+    else if (lane == 49 && blockIdx.x == 0)
+      out[kParams] = v;
+  }
+}
+
+// The chunks of a parameter's gradient (or of the loss) in chunk order.
+__device__ inline float chunk_sum(const float* __restrict__ part, int p) {
+  float v[kGradChunks];
+#pragma unroll
+  for (int c = 0; c < kGradChunks; ++c) v[c] = part[(size_t)c * (kParams + 1) + p];
+  float acc = 0.0f;
+#pragma unroll
+  for (int c = 0; c < kGradChunks; ++c) acc += v[c];
+  return acc;
 }
 
 __global__ __launch_bounds__(256) void k_mlp_wgrad_sum(int B, const float* __restrict__ part,
                                                        float* __restrict__ grad) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p > kParams) return;
-  float acc = 0.0f;
-  for (int c = 0; c < kGradChunks; ++c) acc += part[(size_t)c * (kParams + 1) + p];
+  const float acc = chunk_sum(part, p);
   grad[p] = p == kParams ? acc / (float)B : acc;
 }
 
-// Adam on the float32 masters.
-__global__ __launch_bounds__(256) void k_adam(float* __restrict__ master, const float* __restrict__ grad,
-                                              float* __restrict__ mom, float* __restrict__ vel, float lr, float b1,
-                                              float b2, float eps, float bc1, float bc2) {
+// The rest of a training step, one parameter per thread: its gradient's chunks, Adam on the float32
+// master, and its places in the bf16 copies (the layouts of k_mlp_repack and k_mlp_repack_mfma,
+// whose padding entries keep their zeros); the last thread adds the batch's loss to its epoch's.
+__global__ __launch_bounds__(64) void k_mlp_step(MlpDevice d, int B, const float* __restrict__ part, float lr, float b1,
+                                                 float b2, float eps, float bc1, float bc2,
+                                                 float* __restrict__ epoch_loss, float loss_scale) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= kParams) return;
-  const float g = grad[p];
-  const float mm = b1 * mom[p] + (1.0f - b1) * g;
-  const float vv = b2 * vel[p] + (1.0f - b2) * g * g;
-  mom[p] = mm;
-  vel[p] = vv;
-  master[p] -= lr * (mm / bc1) / (sqrtf(vv / bc2) + eps);
+  if (p > kParams) return;
+  const float g = chunk_sum(part, p);
+  if (p == kParams) {
+    *epoch_loss += g / (float)B * loss_scale;
+    return;
+  }
+  const float mm = b1 * d.mom[p] + (1.0f - b1) * g;
+  const float vv = b2 * d.vel[p] + (1.0f - b2) * g * g;
+  d.mom[p] = mm;
+  d.vel[p] = vv;
+  const float v = d.master[p] - lr * (mm / bc1) / (sqrtf(vv / bc2) + eps);
+  d.master[p] = v;
+  const uint16_t h = (uint16_t)bf16_bits(v);
+  // element e of 16-bit pairs: low half first
+  auto put = [&](uint32_t* base, int e) { reinterpret_cast<uint16_t*>(base)[e] = h; };
+  if (p < kOffB1) {
+    const int o = p / kIn, i = p % kIn;
+    put(d.w1p, o * 2 * kInPairs + i);
+    // W1 operand: tile o / 16, lane 16 (i / 8) + o % 16, pair (i % 8) / 2
+    put(d.w1a, 2 * ((o / 16) * 256 + ((i / 8) * 16 + o % 16) * 4) + i % 8);
+  } else if (p < kOffW2) {
+    d.b1f[p - kOffB1] = v;
+  } else if (p < kOffB2) {
+    const int o = (p - kOffW2) / kH, i = (p - kOffW2) % kH;
+    put(d.w2p, o * kH + i);
+    d.w2r[p - kOffW2] = bf16_round(v);
+    // W2 operand: column i = 16 (2 s + j / 4) + 4 g + j % 4 of tile o / 16, k-step s, lane 16 g + o % 16
+    const int s = i / 32, g4 = (i % 16) / 4, j = 4 * ((i % 32) / 16) + i % 4;
+    put(d.w2a, 2 * (((o / 16) * 2 + s) * 256 + (g4 * 16 + o % 16) * 4) + j);
+  } else if (p < kOffW3) {
+    d.b2f[p - kOffB2] = v;
+  } else if (p < kOffB3) {
+    const int i = p - kOffW3;
+    put(d.w3p, i);
+    d.w3r[i] = bf16_round(v);
+    d.w3f[i] = bf16_round(v);
+  }
 }
 
 // bf16 copies of the weights in the kernels' layout.
@@ -366,12 +478,6 @@ __global__ __launch_bounds__(256) void k_mlp_repack_mfma(const float* __restrict
     b2f[t] = master[kOffB2 + t];
     w3f[t] = bf16_round(master[kOffW3 + t]);
   }
-}
-
-// Loss of batch `step` into epoch_loss[epoch] (a single thread: fixed order).
-__global__ void k_accumulate_loss(const float* __restrict__ grad, float* __restrict__ epoch_loss, int epoch,
-                                  float scale) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) epoch_loss[epoch] += grad[kParams] * scale;
 }
 
 // ---- learned run: fallback decision -----------------------------------------------------
@@ -1060,8 +1166,10 @@ hipError_t launch_mlp_forward(const MlpDevice& d, const float* feat, int m, floa
 
 size_t mlp_batch_scratch_floats(int B) { return (size_t)B * (28 + 4 * kH + 2) + (size_t)kGradChunks * (kParams + 1); }
 
-hipError_t launch_mlp_gradients(const MlpDevice& d, const float* feat, const float* target, const uint32_t* sel, int B,
-                                float* scratch, float* grad, hipStream_t s) {
+namespace {
+// The batch's per-chunk gradient sums, queued on s; returns where they are in scratch.
+float* queue_chunk_gradients(const MlpDevice& d, const float* feat, const float* target, const uint32_t* sel, int B,
+                             float* scratch, hipStream_t s) {
   float* s_x = scratch;
   float* s_h1 = s_x + (size_t)B * 28;
   float* s_h2 = s_h1 + (size_t)B * kH;
@@ -1070,23 +1178,29 @@ hipError_t launch_mlp_gradients(const MlpDevice& d, const float* feat, const flo
   float* s_dy = s_da2 + (size_t)B * kH;
   float* s_err2 = s_dy + B;
   float* part = s_err2 + B;
-  hipLaunchKernelGGL(k_mlp_train_sample, dim3((B + 63) / 64), dim3(64), 0, s, weights(d), feat, target, sel, B,
-                     2.0f / (float)B, s_x, s_h1, s_h2, s_da1, s_da2, s_dy, s_err2);
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3((kParams + 1 + 255) / 256, kGradChunks), dim3(256), 0, s, B, s_x, s_h1, s_h2,
-                     s_da1, s_da2, s_dy, s_err2, part);
+  // a wavefront loads its 110 weights once: one sample each until the chip is full
+  const int blocks = (B + kSampleWaves - 1) / kSampleWaves;
+  hipLaunchKernelGGL(k_mlp_train_sample, dim3(blocks < 1024 ? blocks : 1024), dim3(64 * kSampleWaves), 0, s, weights(d),
+                     feat, target, sel, B, 2.0f / (float)B, s_x, s_h1, s_h2, s_da1, s_da2, s_dy, s_err2);
+  hipLaunchKernelGGL(k_mlp_wgrad, dim3(kGradParts, kGradChunks), dim3(192), 0, s, B, s_x, s_h1, s_h2, s_da1, s_da2, s_dy,
+                     s_err2, part);
+  return part;
+}
+}  // namespace
+
+hipError_t launch_mlp_gradients(const MlpDevice& d, const float* feat, const float* target, const uint32_t* sel, int B,
+                                float* scratch, float* grad, hipStream_t s) {
+  const float* part = queue_chunk_gradients(d, feat, target, sel, B, scratch, s);
   hipLaunchKernelGGL(k_mlp_wgrad_sum, dim3((kParams + 1 + 255) / 256), dim3(256), 0, s, B, part, grad);
   return hipGetLastError();
 }
 
-hipError_t launch_adam(const MlpDevice& d, const float* grad, float lr, float b1, float b2, float eps, float bc1,
-                       float bc2, hipStream_t s) {
-  hipLaunchKernelGGL(k_adam, dim3((kParams + 255) / 256), dim3(256), 0, s, d.master, grad, d.mom, d.vel, lr, b1, b2,
-                     eps, bc1, bc2);
-  return hipGetLastError();
-}
-
-hipError_t launch_accumulate_loss(const float* grad, float* epoch_loss, int epoch, float scale, hipStream_t s) {
-  hipLaunchKernelGGL(k_accumulate_loss, dim3(1), dim3(64), 0, s, grad, epoch_loss, epoch, scale);
+hipError_t launch_mlp_step(const MlpDevice& d, const float* feat, const float* target, const uint32_t* sel, int B,
+                           float* scratch, float lr, float b1, float b2, float eps, float bc1, float bc2,
+                           float* epoch_loss, float loss_scale, hipStream_t s) {
+  const float* part = queue_chunk_gradients(d, feat, target, sel, B, scratch, s);
+  hipLaunchKernelGGL(k_mlp_step, dim3((kParams + 1 + 63) / 64), dim3(64), 0, s, d, B, part, lr, b1, b2, eps, bc1, bc2,
+                     epoch_loss, loss_scale);
   return hipGetLastError();
 }
 
