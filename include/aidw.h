@@ -453,8 +453,9 @@ aidw_status aidw_learned_routes(const float* x, const float* y, int64_t n, const
  * data points) from a list ordered by decreasing cost until it is exhausted.
  * Every item writes its own float64 partial sums and a last pass adds a
  * query's partials in a fixed order, so results are bitwise reproducible.
- * Jobs of at least 8192 data points and 256 queries (levels <= 8, with
- * integer_powers) are summed hierarchically, as aidw_interpolate describes.
+ * Where it saves a plan from about 2e9 pairs, jobs of at least 8192 data points
+ * and several thousand queries (levels <= 8, with integer_powers) are summed
+ * hierarchically, as aidw_interpolate describes.
  * Each job's outputs are those aidw_run gives for the job alone (bitwise, for a
  * job whose every pair is evaluated, when aidw_run uses the same pair-kernel
  * shape: q, and split = the job's number of data ranges, see split_points).

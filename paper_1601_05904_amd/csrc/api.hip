@@ -498,13 +498,14 @@ uint32_t integer_levels(const aidw_params* p) {
 // Whether Eq. 1 is summed hierarchically (tree.hip): with the built-in launch shape, levels that the
 // expansion's error bounds cover, and enough pairs to pay for the moments and the query order.
 // The direct sums cost n m / 5.2e12 s; the hierarchical ones about 0.25 ms at the smallest sizes,
-// plus 1.2 us per 1000 data points (moments; uneven data cost most) and 1-3 us per 1000 queries.
+// plus 1.2 us per 1000 data points (moments; uneven data cost most) and 0.6-3 us per 1000 queries
+// (4096 x 465,649 in a mixture: 0.94 ms against 0.87 with every pair evaluated).
 bool tree_pays(int64_t n, int64_t m, const aidw_params* p) {
   if (g_cfg_q || g_cfg_split || !g_cfg_intpow || g_arena) return false;
   for (int i = 0; i < 5; ++i)
     if (p->alpha[i] > 8.0) return false;
   return n >= 4096 && m >= 64 && n <= (1 << 28) && m <= (1 << 28) &&
-         (double)n * (double)m >= 1.5e9 + 6000.0 * (double)n;
+         (double)n * (double)m >= 1.5e9 + 6000.0 * (double)n + 900.0 * (double)m;
 }
 
 // Eq. 1 by hierarchical summation.  points: the grid of exactly these data points (a run's own);

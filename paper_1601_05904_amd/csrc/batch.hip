@@ -69,11 +69,27 @@ struct WorkItem {
   int32_t job, qblock, split, pad;
 };
 
-// Data points from which a job is summed hierarchically: a query's near points and squares cost as
-// much as about 3000 pairs, and the moments and the wider sort are shared launches (48 jobs of
-// 1024 to 65,536 points: 5.7 -> 1.85 ms a replay).
+// Which jobs of a plan are summed hierarchically, in pairs of Eq. 1 (5.2e12 of them take 1 s): a
+// job's moments cost 6000 pairs a data point and its queries' walks 2000 pairs each, so it has to
+// save more than that, and the extra launches have to be covered by all such jobs together:
+// their part in a plan is 0.2 ms for even data and 0.5 ms for mixtures, growing with the number
+// of jobs (hence a second 6000 per data point).  Replays in us, every pair / hierarchical, sizes
+// n = m, uniform | 8-component mixtures:
+//   one job of 12,461:        364/306 | 638/738     one of 50,000:          803/440 | 1025/1015
+//   16 of 8192:              570/626 | 904/1150     48 of 512 to 32,768:    1745/1230 | 2091/2059
+//   16 of 512 to 32,768:     878/801 | 1286/1519    48 of 1024 to 65,536:   5696/1881 | 6242/3087
+//   32 of 65,536 x 1024:     989/1341 | 1269/2162   8 of 8192 x 65,536:     1256/820 | 1458/1243
 constexpr int kTreePoints = 8192;
 constexpr int kTreeQueries = 256;
+constexpr double kTreePoint = 6000.0, kTreeQuery = 2000.0, kTreeLaunches = 1.5e9;
+
+// Pairs that a job's hierarchical sums save, 0 where they are not taken.
+double tree_saves(const aidw_job& a) {
+  for (int l = 0; l < 5; ++l)
+    if (a.params.alpha[l] > 8.0) return 0.0;
+  if (a.n < kTreePoints || a.m < kTreeQueries) return 0.0;
+  return fmax(0.0, (double)a.n * (double)a.m - kTreePoint * (double)a.n - kTreeQuery * (double)a.m);
+}
 
 constexpr int kBoundsPerBlock = 4096;  // elements of one job per bounds workgroup
 
@@ -556,6 +572,10 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   for (int j = 0; j < njobs; ++j) order[j] = j;
   std::stable_sort(order.begin(), order.end(),
                    [&](int32_t a, int32_t b) { return kclass(jobs[a].params.k) < kclass(jobs[b].params.k); });
+  double saved = 0.0;
+  for (int j = 0; j < njobs; ++j)
+    if (tree_saves(jobs[j]) > 0.0) saved += tree_saves(jobs[j]) - kTreePoint * (double)jobs[j].n;
+  const bool use_tree = cfg.integer_powers && saved >= kTreeLaunches;
   for (int jj = 0; jj < njobs; ++jj) {
     const int j = jj;  // internal index
     const aidw_job& a = jobs[order[jj]];
@@ -587,8 +607,7 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
     J.cbase = (int32_t)scap;
     const int64_t cap = cell_budget(a.n, a.params);
     J.ccap = (int32_t)std::min<int64_t>(cap, AIDW_MAX_CELLS);
-    bool tree_job = cfg.integer_powers && a.n >= kTreePoints && a.m >= kTreeQueries;
-    for (int l = 0; l < 5; ++l) tree_job = tree_job && a.params.alpha[l] <= 8.0;
+    const bool tree_job = use_tree && tree_saves(a) > 0.0;
     J.tree = -1;
     if (tree_job) {
       J.tree = (int32_t)tj.size();

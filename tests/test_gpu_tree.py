@@ -238,7 +238,8 @@ def test_streams_share_nothing(T):
         assert all(T.equal(a, b) for a, b in zip(got, want))
 
 
-def test_batch_jobs(T):
+@pytest.mark.parametrize("size", ["small", "large"])
+def test_batch_jobs(T, size):
     """Jobs on both sides of the batched form's size rule in one plan, replayed as a graph after the
     fields change, against Eq. 1 in float64: uneven kinds and levels, a job whose z holds a NaN, one
     with a leaf of very many points, one without an area."""
@@ -247,6 +248,11 @@ def test_batch_jobs(T):
     specs = [(8191, 700, "uniform", {}), (8192, 256, "uniform", {}), (8192, 255, "mixture", {}), (20011, 9001, "mixture", {}),
              (30000, 12000, "mixture", dict(levels=(0.5, 1.25, 2.0, 3.5, 7.0))), (40000, 3000, "uniform", dict(levels=(1, 2, 3, 4, 9))),
              (10000, 5000, "uniform", {}), (40000, 2000, "uniform", {}), (9000, 500, "uniform", {}), (500, 30000, "uniform", {})]
+    if size == "large":  # enough pairs for the hierarchical sums, on both sides of the rules for a job
+        specs = [(8191, 60000, "uniform", {}), (8192, 60000, "uniform", {}), (65536, 255, "mixture", {}),
+                 (20011, 9001, "mixture", {}), (60000, 40000, "mixture", dict(levels=(0.5, 1.25, 2.0, 3.5, 7.0))),
+                 (40000, 40000, "uniform", dict(levels=(1, 2, 3, 4, 9))), (50000, 50000, "uniform", {}),
+                 (50000, 40000, "uniform", {}), (9000, 30000, "uniform", {}), (500, 30000, "uniform", {})]
     jobs = []
     for i, (n, m, kind, kw) in enumerate(specs):
         d = make(n, m, 870 + i, kind)
