@@ -207,17 +207,12 @@ hipError_t launch_knn_paper(const GridScalars* gs, const int32_t* cell_start, co
                             const int32_t* sidx, const float* qx, const float* qy, const uint32_t* qperm, int m, int k,
                             float* r_obs, float* d1sq, int32_t* nn_idx, hipStream_t s);
 struct AlphaParams;
-// The same with `lanes` (2, 4 or 8) lanes per query (for small or sparse query sets); identical results.
+// The same with `lanes` (4 or 8) lanes per query (for small or sparse query sets); identical results.
 // With ap and alpha_f non-null, alpha_f[q] also receives Eq. 4-6 of each query's r_obs.
 hipError_t launch_knn_lanes(const GridScalars* gs, const int32_t* cell_start, const float* sx, const float* sy,
                             const int32_t* sidx, const float* qx, const float* qy, const uint32_t* qperm,
                             const uint32_t* active, int m, int k, float* r_obs, float* d1sq, int32_t* nn_idx,
                             int lanes, hipStream_t s, const AlphaParams* ap = nullptr, float* alpha_f = nullptr);
-// Four lanes per query.
-hipError_t launch_knn4(const GridScalars* gs, const int32_t* cell_start, const float* sx, const float* sy,
-                       const int32_t* sidx, const float* qx, const float* qy, const uint32_t* qperm,
-                       const uint32_t* active, int m, int k, float* r_obs, float* d1sq, int32_t* nn_idx,
-                       hipStream_t s);
 
 struct AlphaParams {
   double r_exp;

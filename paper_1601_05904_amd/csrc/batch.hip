@@ -274,8 +274,8 @@ __global__ __launch_bounds__(256) void k_b_knn(const BatchJob* __restrict__ jobs
   const knn::View g{G.minx, G.miny, G.inv_cw, G.ncol, G.nrow, G.cwd};
   double bk[KMAX];
   int32_t bi[KMAX];
-  knn::search<KMAX>(g, cell_start + J.cbase, sx, sy, sidx, cqx[q], cqy[q], J.k, slack_cells(G.ncol, G.nrow), bk,
-                    bi);
+  knn::nearest<KMAX, 1, false>(g, cell_start + J.cbase, sx, sy, sidx, cqx[q], cqy[q], J.k, slack_cells(G.ncol, G.nrow),
+                               bk, bi);
   float ro, d1;
   knn::summarise<KMAX>(bk, J.k, ro, d1);
   r_obs[q] = ro;

@@ -1,13 +1,11 @@
 // Stage 1, kNN search and Eq. 3 (Section 3.2.4 and 4.1.4 of the paper).
 //
-// One query per lane, lanes taking the queries in cell order (the queries are
-// binned by the same counting sort as the data), so that a wavefront's lanes
-// walk neighbouring cells and share cache lines.  Each lane grows square rings
-// of cells around its query's cell (level L = cells at Chebyshev distance L)
-// and keeps its k best candidates in registers, ordered by (squared distance,
-// data index), with a fully unrolled insertion (the paper's insert-and-swap
-// k-array, initialised to +inf instead of 0 so that it accepts candidates) whose
-// comparisons are branch-free (vector compares combined with bitwise operators).
+// One query per lane (or several lanes per query), lanes taking the queries in cell order (the
+// queries are binned by the same counting sort as the data), so that a wavefront's lanes
+// walk neighbouring cells and share cache lines.  Each lane walks the block of cells around its
+// query's cell (level L = cells up to Chebyshev distance L; the paper grows it ring by ring, here
+// it starts at 5 x 5 or 3 x 3, knn_core.h) and keeps its k smallest squared distances in
+// registers; a list with indices is ordered by (squared distance, data index).
 //
 // Stop rule.  The paper expands until the block holds k points and then adds
 // one more level.  That is not always enough: the block of level L only
@@ -33,15 +31,30 @@ namespace aidw {
 
 namespace {
 
+template <int KMAX>
+__device__ __forceinline__ void store_indices(const int32_t (&bi)[KMAX], int k, int32_t* __restrict__ row) {
+#pragma unroll
+  for (int s = 0; s < KMAX; ++s)
+    if (s >= KMAX - k) row[s - (KMAX - k)] = bi[s];
+}
 
-template <int KMAX, bool PAPER = false>
-__global__ __launch_bounds__(256) void k_knn(const GridScalars* __restrict__ gs, const int32_t* __restrict__ cell_start,
+// Wavefronts per SIMD that the registers are held to: as many as leave the list unspilled.
+constexpr int knn_waves(int kmax, bool idx) { return kmax > 16 ? 1 : idx ? 5 : kmax > 10 ? 6 : 7; }
+
+// One lane per query.  What bounds it: the vector instructions per candidate, 19 of the list and
+// about 20 of the walk for k = 10, times the largest block of a wavefront's lanes (some 70
+// candidates at two points a cell).  The list holds distances alone; a ring-by-ring walk with the
+// indices in the list took 120 a candidate and 118 candidates.  2^20 queries of 2^20 points, k = 10,
+// with the binning: uniform 349 -> 213 us, 361 -> 290 with indices; mixture 632 -> 414 and 648 -> 557.
+template <int KMAX, bool IDX>
+__global__ __launch_bounds__(256, knn_waves(KMAX, IDX)) void k_knn(const GridScalars* __restrict__ gs, const int32_t* __restrict__ cell_start,
                                              const float* __restrict__ sx, const float* __restrict__ sy,
                                              const int32_t* __restrict__ sidx, const float* __restrict__ qx,
                                              const float* __restrict__ qy, const uint32_t* __restrict__ qperm,
                                              const uint32_t* __restrict__ active, int m, int k,
                                              float* __restrict__ r_obs, float* __restrict__ d1sq,
                                              int32_t* __restrict__ nn_idx) {
+  __shared__ int32_t s_list[IDX ? KMAX * 256 : 1];
   // XCD-aware order only when every workgroup has queries (with a device-side count, the live
   // workgroups are the first ones, which the remap would put on one XCD)
   const int blk = active ? (int)blockIdx.x : xcd_block(blockIdx.x, gridDim.x);
@@ -52,18 +65,39 @@ __global__ __launch_bounds__(256) void k_knn(const GridScalars* __restrict__ gs,
   const float fx = qx[q], fy = qy[q];
   const knn::View g{gs->minx, gs->miny, gs->inv_cw, gs->ncol, gs->nrow, gs->cwd};
   double bk[KMAX];
-  int32_t bi[KMAX];
-  knn::search<KMAX, 1, PAPER>(g, cell_start, sx, sy, sidx, fx, fy, k, slack, bk, bi);
+  int32_t bi[KMAX];  // not used without indices
+  knn::nearest<KMAX, 1, false>(g, cell_start, sx, sy, sidx, fx, fy, k, slack, bk, bi);
   float ro, d1;
   knn::summarise<KMAX>(bk, k, ro, d1);
   r_obs[q] = ro;
   if (d1sq) d1sq[q] = d1;
-  if (nn_idx) {
-    int32_t* row = nn_idx + (size_t)q * k;
-#pragma unroll
-    for (int s = 0; s < KMAX; ++s)
-      if (s >= KMAX - k) row[s - (KMAX - k)] = bi[s];
-  }
+  if constexpr (IDX)
+    knn::collect<KMAX, 256>(g, cell_start, sx, sy, sidx, fx, fy, k, slack, bk, s_list + threadIdx.x,
+                            nn_idx + (size_t)q * k);
+}
+
+// The paper's stop rule, one lane per query.
+template <int KMAX>
+__global__ __launch_bounds__(256) void k_knn_paper(const GridScalars* __restrict__ gs,
+                                                   const int32_t* __restrict__ cell_start,
+                                                   const float* __restrict__ sx, const float* __restrict__ sy,
+                                                   const int32_t* __restrict__ sidx, const float* __restrict__ qx,
+                                                   const float* __restrict__ qy, const uint32_t* __restrict__ qperm,
+                                                   int m, int k, float* __restrict__ r_obs, float* __restrict__ d1sq,
+                                                   int32_t* __restrict__ nn_idx) {
+  const int t = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+  if (t >= m || gs->status != AIDW_OK) return;
+  const double slack = slack_cells(gs->ncol, gs->nrow);
+  const int q = qperm ? (int)qperm[t] : t;
+  const knn::View g{gs->minx, gs->miny, gs->inv_cw, gs->ncol, gs->nrow, gs->cwd};
+  double bk[KMAX];
+  int32_t bi[KMAX];
+  knn::search<KMAX, true, false>(g, cell_start, sx, sy, sidx, qx[q], qy[q], k, slack, bk, bi);
+  float ro, d1;
+  knn::summarise<KMAX>(bk, k, ro, d1);
+  r_obs[q] = ro;
+  if (d1sq) d1sq[q] = d1;
+  if (nn_idx) store_indices<KMAX>(bi, k, nn_idx + (size_t)q * k);
 }
 
 // The kNN of 256 binned queries per workgroup with their cells' neighbourhood staged in LDS:
@@ -140,24 +174,19 @@ __global__ __launch_bounds__(256) void k_knn_window(const GridScalars* __restric
   const int q = qperm ? (int)qperm[t] : t;
   double bk[KMAX];
   int32_t bi[KMAX];
-  knn::search<KMAX, 1, false, true>(g, cell_start, sx, sy, sidx, qx[q], qy[q], k, slack, bk, bi, 0, &win);
+  knn::search<KMAX, false, true>(g, cell_start, sx, sy, sidx, qx[q], qy[q], k, slack, bk, bi, &win);
   float ro, d1;
   knn::summarise<KMAX>(bk, k, ro, d1);
   r_obs[q] = ro;
   if (d1sq) d1sq[q] = d1;
-  if (nn_idx) {
-    int32_t* row = nn_idx + (size_t)q * k;
-#pragma unroll
-    for (int s = 0; s < KMAX; ++s)
-      if (s >= KMAX - k) row[s - (KMAX - k)] = bi[s];
-  }
+  if (nn_idx) store_indices<KMAX>(bi, k, nn_idx + (size_t)q * k);
 }
 
-// LANES lanes per query (knn::search with LANES > 1), for query sets too small to fill
+// LANES lanes per query (knn::nearest with LANES > 1), for query sets too small to fill
 // the chip with one query per lane: LANES times the wavefronts to hide the gathers'
 // latency, and 1 / LANES of the candidates per lane.
-template <int KMAX, int LANES>
-__global__ __launch_bounds__(256) void k_knn_lanes(const GridScalars* __restrict__ gs, const int32_t* __restrict__ cell_start,
+template <int KMAX, int LANES, bool IDX>
+__global__ __launch_bounds__(256, knn_waves(KMAX, IDX)) void k_knn_lanes(const GridScalars* __restrict__ gs, const int32_t* __restrict__ cell_start,
                                               const float* __restrict__ sx, const float* __restrict__ sy,
                                               const int32_t* __restrict__ sidx, const float* __restrict__ qx,
                                               const float* __restrict__ qy, const uint32_t* __restrict__ qperm,
@@ -176,9 +205,9 @@ __global__ __launch_bounds__(256) void k_knn_lanes(const GridScalars* __restrict
   const knn::View g{gs->minx, gs->miny, gs->inv_cw, gs->ncol, gs->nrow, gs->cwd};
   double bk[KMAX];
   int32_t bi[KMAX];
-  knn::search<KMAX, LANES>(g, cell_start, sx, sy, sidx, qx[q], qy[q], k, slack, bk, bi, sub);
+  knn::nearest<KMAX, LANES, IDX>(g, cell_start, sx, sy, sidx, qx[q], qy[q], k, slack, bk, bi, sub);
   float ro, d1;
-  knn::merge_lanes<KMAX, LANES>(bk, bi, k, sub, ro, d1, nn_idx ? nn_idx + (size_t)q * k : nullptr);
+  knn::merge_lanes<KMAX, LANES, IDX>(bk, bi, k, sub, ro, d1, IDX ? nn_idx + (size_t)q * k : nullptr);
   if (sub == 0) {
     r_obs[q] = ro;
     if (d1sq) d1sq[q] = d1;
@@ -235,12 +264,7 @@ __global__ __launch_bounds__(256) void k_knn_brute(const float* __restrict__ x, 
   knn::summarise<KMAX>(bk, k, ro, d1);
   r_obs[q] = ro;
   if (d1sq) d1sq[q] = d1;
-  if (nn_idx) {
-    int32_t* row = nn_idx + (size_t)q * k;
-#pragma unroll
-    for (int s = 0; s < KMAX; ++s)
-      if (s >= KMAX - k) row[s - (KMAX - k)] = bi[s];
-  }
+  if (nn_idx) store_indices<KMAX>(bi, k, nn_idx + (size_t)q * k);
 }
 
 }  // namespace
@@ -269,8 +293,8 @@ hipError_t launch_knn_paper(const GridScalars* gs, const int32_t* cell_start, co
   if (m <= 0) return hipSuccess;
   const dim3 grid((m + 255) / 256), block(256);
 #define AIDW_KNNP(K)                                                                                                \
-  hipLaunchKernelGGL((k_knn<K, true>), grid, block, 0, s, gs, cell_start, sx, sy, sidx, qx, qy, qperm, nullptr, m, \
-                     k, r_obs, d1sq, nn_idx)
+  hipLaunchKernelGGL(k_knn_paper<K>, grid, block, 0, s, gs, cell_start, sx, sy, sidx, qx, qy, qperm, m, k, r_obs, \
+                     d1sq, nn_idx)
   if (k <= 8)
     AIDW_KNNP(8);
   else if (k <= 16)
@@ -290,37 +314,34 @@ hipError_t launch_knn_lanes(const GridScalars* gs, const int32_t* cell_start, co
   if (m <= 0) return hipSuccess;
   const AlphaParams apv = ap ? *ap : AlphaParams{};
   if (!ap) alpha_f = nullptr;
-  if (lanes != 2 && lanes != 4 && lanes != 8) return hipErrorInvalidValue;
   // one workgroup per 256 / lanes queries; with an active count the workgroups beyond it exit at
   // once (a grid-stride loop instead keeps more registers live across the search: measured slower)
   const dim3 grid((int)(((int64_t)m * lanes + 255) / 256)), block(256);
-#define AIDW_KNNL(K, LN)                                                                                         \
-  hipLaunchKernelGGL((k_knn_lanes<K, LN>), grid, block, 0, s, gs, cell_start, sx, sy, sidx, qx, qy, qperm, active, \
+#define AIDW_KNNL(K, LN, IDX)                                                                                       \
+  hipLaunchKernelGGL((k_knn_lanes<K, LN, IDX>), grid, block, 0, s, gs, cell_start, sx, sy, sidx, qx, qy, qperm, active, \
                      m, k, r_obs, d1sq, nn_idx, apv, alpha_f)
-#define AIDW_KNNL_2(K) AIDW_KNNL(K, 2)
-#define AIDW_KNNL_4(K) AIDW_KNNL(K, 4)
-#define AIDW_KNNL_8(K) AIDW_KNNL(K, 8)
-#define AIDW_KNNL_K(LN) AIDW_FOR_KNN_SLOTS(k, AIDW_KNNL_##LN)
-  if (lanes == 2) {
-    AIDW_KNNL_K(2);
-  } else if (lanes == 4) {
-    AIDW_KNNL_K(4);
-  } else {
-    AIDW_KNNL_K(8);
+#define AIDW_KNNL_IDX(K, LN)  \
+  if (nn_idx)                \
+    AIDW_KNNL(K, LN, true);  \
+  else                       \
+    AIDW_KNNL(K, LN, false);
+#define AIDW_KNNL_4(K) AIDW_KNNL_IDX(K, 4)
+#define AIDW_KNNL_8(K) AIDW_KNNL_IDX(K, 8)
+  switch (lanes) {
+    case 4:
+      AIDW_FOR_KNN_SLOTS(k, AIDW_KNNL_4)
+      break;
+    case 8:
+      AIDW_FOR_KNN_SLOTS(k, AIDW_KNNL_8)
+      break;
+    default:
+      return hipErrorInvalidValue;
   }
-#undef AIDW_KNNL_K
 #undef AIDW_KNNL_8
 #undef AIDW_KNNL_4
-#undef AIDW_KNNL_2
+#undef AIDW_KNNL_IDX
 #undef AIDW_KNNL
   return hipGetLastError();
-}
-
-hipError_t launch_knn4(const GridScalars* gs, const int32_t* cell_start, const float* sx, const float* sy,
-                       const int32_t* sidx, const float* qx, const float* qy, const uint32_t* qperm,
-                       const uint32_t* active, int m, int k, float* r_obs, float* d1sq, int32_t* nn_idx,
-                       hipStream_t s) {
-  return launch_knn_lanes(gs, cell_start, sx, sy, sidx, qx, qy, qperm, active, m, k, r_obs, d1sq, nn_idx, 4, s);
 }
 
 hipError_t launch_knn_window(const GridScalars* gs, const int32_t* cell_start, const float* sx, const float* sy,
@@ -342,11 +363,17 @@ hipError_t launch_knn(const GridScalars* gs, const int32_t* cell_start, const fl
                       hipStream_t s) {
   if (m <= 0) return hipSuccess;
   const dim3 grid((m + 255) / 256), block(256);
-#define AIDW_KNN1(K)                                                                                              \
-  hipLaunchKernelGGL(k_knn<K>, grid, block, 0, s, gs, cell_start, sx, sy, sidx, qx, qy, qperm, active, m, k, \
+#define AIDW_KNN1_I(K, IDX)                                                                                            \
+  hipLaunchKernelGGL((k_knn<K, IDX>), grid, block, 0, s, gs, cell_start, sx, sy, sidx, qx, qy, qperm, active, m, k, \
                      r_obs, d1sq, nn_idx)
+#define AIDW_KNN1(K)      \
+  if (nn_idx)             \
+    AIDW_KNN1_I(K, true); \
+  else                    \
+    AIDW_KNN1_I(K, false);
   AIDW_FOR_KNN_SLOTS(k, AIDW_KNN1)
 #undef AIDW_KNN1
+#undef AIDW_KNN1_I
   return hipGetLastError();
 }
 

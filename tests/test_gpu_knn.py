@@ -1,0 +1,54 @@
+"""The grid searches against the brute-force kNN over all points, bit for bit: with one and several lanes
+per query, with and without indices, where equal distances, piles of points in a cell, voids and
+queries outside the grid decide which cells are walked."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def layout(kind, rng, n):
+    if kind == "lattice":  # every distance many times
+        side = int(np.ceil(np.sqrt(n)))
+        i = rng.permutation(side * side)[:n]
+        return (i % side) / np.float32(side), (i // side) / np.float32(side)
+    if kind == "piles":  # a few places, some with one point, some with hundreds
+        at = rng.random((24, 2))
+        c = np.minimum(rng.geometric(0.2, n) - 1, 23)
+        return at[c, 0], at[c, 1]
+    if kind == "gap":  # a dense corner, a far sparse rest
+        d = rng.random((n, 2)) * 0.02
+        d[: n // 20] = 0.3 + 0.7 * rng.random((n // 20, 2))
+        return d[:, 0], d[:, 1]
+    d = rng.random((n, 2))
+    return d[:, 0], d[:, 1] * 1e-3  # strip
+
+
+@pytest.mark.parametrize("k", [1, 7, 10, 15, 33])
+@pytest.mark.parametrize("kind", ["lattice", "piles", "gap", "strip"])
+def test_matches_brute_force(kind, k):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1601_05904_amd as aidw
+    aidw.load(build_if_missing=False)
+    rng = np.random.default_rng(k)
+    n = 1531
+    x, y = (torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda() for a in layout(kind, rng, n))
+    q = rng.random((300001, 2)).astype(np.float32)
+    own = rng.integers(0, n, 100000)
+    q[:50000] = np.stack([x.cpu().numpy()[own[:50000]], y.cpu().numpy()[own[:50000]]], 1)  # at data points
+    q[50000:100000] = q[:50000] + rng.normal(0, 0.01, (50000, 2)).astype(np.float32)
+    q[100000:100200] = (q[100000:100200] - 0.5) * 1e4  # outside the grid
+    q = q[rng.permutation(len(q))]
+    qx, qy = (torch.from_numpy(np.ascontiguousarray(q[:, i])).cuda() for i in range(2))
+    want = aidw.knn_bruteforce(x, y, qx, qy, k, want_idx=True)
+    grid = aidw.build_grid(x, y, x, y, aidw.Params(k=k))
+    for m in (1, 999, 40000, 200000, 300001):
+        for idx in (False, True):
+            r, d1, ix = aidw.knn(grid, qx[:m], qy[:m], k, want_idx=idx)
+            assert torch.equal(r, want[0][:m]), (m, idx)
+            assert torch.equal(d1, want[1][:m]), (m, idx)
+            if idx:
+                assert torch.equal(ix, want[2][:m]), m
+    grid.close()
