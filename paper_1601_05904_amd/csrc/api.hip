@@ -459,7 +459,7 @@ aidw_status knn_impl(const aidw_grid* g, const float* qx, const float* qy, int64
   // Few queries leave the chip idle with one lane each, and several lanes shorten the walk of a query
   // in a dense cell.  us with 1 | 4 | 8 lanes, uniform and an 8-component mixture: 4096 queries
   // - | 51 | 52 and - | 108 | 78; 65,536: - | 67 | 73 and - | 113 | 106; 262,144: 102 | 111 | - and
-  // 271 | 173 | -, with indices 129 | 156 | - and 331 | 293 | -; 2^20: 213 | 278 | - and 414 | 395 | -.
+  // 198 | 173 | -, with indices 129 | 156 | - and 270 | 293 | -; 2^20: 213 | 278 | - and 325 | 395 | -.
   if (nn_idx ? m >= (1 << 17) : m > (1 << 18))
     HIP_TRY(launch_knn(g->dev, g->cell_start, g->sx, g->sy, g->sidx, qx, qy, order, nullptr, (int)m, k, r_obs, d1sq,
                        nn_idx, s),

@@ -45,7 +45,8 @@ constexpr int knn_waves(int kmax, bool idx) { return kmax > 16 ? 1 : idx ? 5 : k
 // about 20 of the walk for k = 10, times the largest block of a wavefront's lanes (some 70
 // candidates at two points a cell).  The list holds distances alone; a ring-by-ring walk with the
 // indices in the list took 120 a candidate and 118 candidates.  2^20 queries of 2^20 points, k = 10,
-// with the binning: uniform 349 -> 213 us, 361 -> 290 with indices; mixture 632 -> 414 and 648 -> 557.
+// with the binning: uniform 349 -> 213 us, 361 -> 290 with indices; mixture 632 -> 325 and 648 -> 471 (414
+// and 557 with the whole 3 x 3 in its dense places).
 template <int KMAX, bool IDX>
 __global__ __launch_bounds__(256, knn_waves(KMAX, IDX)) void k_knn(const GridScalars* __restrict__ gs, const int32_t* __restrict__ cell_start,
                                              const float* __restrict__ sx, const float* __restrict__ sy,

@@ -87,17 +87,20 @@ __device__ __forceinline__ void insert(double (&bk)[KMAX], int32_t (&bi)[KMAX], 
   }
 }
 
-// Distance from the query to the nearest open side (one beyond which cells remain) of the block of
-// cells within L of its cell (c0, r0), less the slack.
-__device__ __forceinline__ double reach(const View& g, double px, double py, int c0, int r0, int L, double slack) {
+// Distance from the query to the nearest open side (one beyond which cells remain) of the cells in
+// columns [ca, cz] and rows [ra, rz].
+__device__ __forceinline__ double side_distance(const View& g, double px, double py, int ca, int cz, int ra, int rz) {
   const double minxd = g.minx, minyd = g.miny, cwd = g.cwd;
-  const int cl = c0 - L, cr = c0 + L, rb = r0 - L, rt = r0 + L;
   double dout = INFINITY;
-  if (cl > 0) dout = fmin(dout, px - (minxd + (double)cl * cwd));
-  if (cr < g.ncol - 1) dout = fmin(dout, (minxd + (double)(cr + 1) * cwd) - px);
-  if (rb > 0) dout = fmin(dout, py - (minyd + (double)rb * cwd));
-  if (rt < g.nrow - 1) dout = fmin(dout, (minyd + (double)(rt + 1) * cwd) - py);
-  return dout - slack;
+  if (ca > 0) dout = fmin(dout, px - (minxd + (double)ca * cwd));
+  if (cz < g.ncol - 1) dout = fmin(dout, (minxd + (double)(cz + 1) * cwd) - px);
+  if (ra > 0) dout = fmin(dout, py - (minyd + (double)ra * cwd));
+  if (rz < g.nrow - 1) dout = fmin(dout, (minyd + (double)(rz + 1) * cwd) - py);
+  return dout;
+}
+// The same for the block of cells within L of the cell (c0, r0), less the slack.
+__device__ __forceinline__ double reach(const View& g, double px, double py, int c0, int r0, int L, double slack) {
+  return side_distance(g, px, py, c0 - L, c0 + L, r0 - L, r0 + L) - slack;
 }
 
 // The largest over the LANES lanes of a query (an aligned group of LANES consecutive lanes)
@@ -136,7 +139,8 @@ __device__ __forceinline__ bool k_below(const double (&bk)[KMAX], int k, double 
 //
 // The first block is the 5 x 5 cells around the query's (at the usual two points a cell it holds
 // the ten nearest of nearly every query), or 3 x 3 where those 25 cells hold so many points that 9
-// should do; its rows are contiguous runs of points whose bounds are read together, and a lane walks
+// should do (with one lane and a short list, before these the cells that a still denser place
+// should need); its rows are contiguous runs of points whose bounds are read together, and a lane walks
 // them as one sequence, so the lanes of a wavefront differ by their blocks' totals and not row by
 // row.  A block that fails the stop test grows to the level that the k-th distance asks for (twice
 // the level while it holds fewer than k points), by rows and the runs beside it.
@@ -238,7 +242,7 @@ __device__ __forceinline__ void nearest(const View& g, const int32_t* __restrict
   const double slack = slack_cells * g.cwd;
   clear<KMAX>(k, bk);
   if constexpr (IDX) clear<KMAX>(k, bk, bi);
-  auto two = [&](int p, int p2, bool pair) __attribute__((always_inline)) {
+  auto two = [&](int p, int p2, bool pair, bool late = false) __attribute__((always_inline)) {
     const float x = sx[p], y = sy[p], x2 = sx[p2], y2 = sy[p2];
     const double dx = (double)x - px, dy = (double)y - py;
     const double ex = (double)x2 - px, ey = (double)y2 - py;
@@ -249,8 +253,11 @@ __device__ __forceinline__ void nearest(const View& g, const int32_t* __restrict
       insert<KMAX>(bk, bi, d2, id);
       if (pair) insert<KMAX>(bk, bi, e2, id2);
     } else {
-      insert<KMAX>(bk, d2);
-      insert<KMAX>(bk, e2);
+      // far out few candidates enter: a wavefront in which none does goes on
+      if (!late || min_f64(d2, e2) < bk[KMAX - 1]) {
+        insert<KMAX>(bk, d2);
+        insert<KMAX>(bk, e2);
+      }
     }
   };
   auto around = [&](int l) __attribute__((always_inline)) {
@@ -261,6 +268,19 @@ __device__ __forceinline__ void nearest(const View& g, const int32_t* __restrict
   if (b.e4 >= kDenseBlock * k) {
     L = 1;
     b = around(1);
+    if constexpr (LANES == 1 && KMAX <= 16) {
+      // first the cells within 1.5 times the k-th distance that the density of the 3 x 3 lets expect
+      const float r = sqrtf(6.45f * (float)k / (float)b.e4);  // 1.5 sqrt(9 k / (pi points)) cells
+      const float u = (fx - g.minx) * g.inv, v = (fy - g.miny) * g.inv;
+      const int ca = min(max((int)floorf(u - r), max(c0 - 1, 0)), c0);
+      const int cz = max(min((int)floorf(u + r), min(c0 + 1, ncol - 1)), c0);
+      const int ra = min(max((int)floorf(v - r), max(r0 - 1, 0)), r0);
+      const int rz = max(min((int)floorf(v + r), min(r0 + 1, nrow - 1)), r0);
+      walk_block(block_rows(g, cell_start, ra, rz, ca, cz), 0, 1, two);
+      const double dout = side_distance(g, px, py, ca, cz, ra, rz) - slack;
+      if (dout > 0.0 && bk[KMAX - 1] < dout * dout) return;
+      clear<KMAX>(k, bk);
+    }
   }
   int count = b.e4;
   walk_block(b, sub, LANES, two);
@@ -268,20 +288,23 @@ __device__ __forceinline__ void nearest(const View& g, const int32_t* __restrict
   for (;;) {
     if (c0 - L <= 0 && c0 + L >= ncol - 1 && r0 - L <= 0 && r0 + L >= nrow - 1) break;  // the block covers the grid
     const double dout = reach(g, px, py, c0, r0, L, slack);
-    int next = 2 * L;
+    // the level that 1.15 times the k-th distance at the block's density reaches, at most twice this one
+    int next = count > 0 ? (int)fminf(0.65f * (float)(2 * L + 1) * sqrtf((float)k / (float)count), (float)span) + 1 : span;
+    next = min(next, 2 * L);
     if (count >= k) {
       if (dout > 0.0 && k_below<KMAX, LANES>(bk, k, dout * dout)) break;
-      // the level whose sides lie beyond the k-th distance so far (over several lanes, a bound of it)
+      // no farther than the level whose sides lie beyond the k-th distance so far (over several
+      // lanes, a bound of it)
       const double kth = LANES > 1 ? group_kth<KMAX, LANES>(bk, k) : bk[KMAX - 1];
-      if (kth < INFINITY) next = L + 1 + (int)fmin((double)span, fmax(0.0, (sqrt(kth) - dout) * (double)g.inv));
+      if (kth < INFINITY)
+        next = min(next, L + 1 + (int)fmin((double)span, fmax(0.0, (sqrt(kth) - dout) * (double)g.inv)));
     }
-    if (LANES > 1) next = min(next, 2 * L);
     next = min(max(next, L + 1), span);
     // LANES > 1: the lanes of a query agree on L, next and count
     int seen = 0;
     walk_growth(g, cell_start, c0, r0, L, next, sub, LANES, [&](int p, int p2, bool pair) __attribute__((always_inline)) {
       seen += pair ? 2 : 1;
-      two(p, p2, pair);
+      two(p, p2, pair, true);
     });
 #pragma unroll
     for (int o = 1; o < LANES; o <<= 1) seen += __shfl_xor(seen, o, 64);
@@ -336,6 +359,7 @@ __device__ __forceinline__ void collect(const View& g, const int32_t* __restrict
     }
   });
   if (!tie && cnt == k) {
+#pragma unroll 2
     for (int i = 0; i < k; ++i) {
       const int p = list[i * STRIDE];
       const int32_t id = sidx[p];
