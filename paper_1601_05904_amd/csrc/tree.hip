@@ -37,7 +37,7 @@ constexpr CoefTable make_coefs() {
   return t;
 }
 __device__ constexpr CoefTable kCoef = make_coefs();
-static_assert(coef_offset(0, kOrder / 2) + 2 <= kRec, "a record holds every order");
+static_assert(coef_offset(0, kOrder / 2) + 2 <= kChild, "a record holds every order and its links");
 
 // Entries (J, k), J + k <= kOrder, of the shift's first stage.
 constexpr int kTri = (kOrder + 1) * (kOrder + 2) / 2;
@@ -127,6 +127,9 @@ __global__ void k_tree_plan(Jobs jobs, uint32_t* __restrict__ zero_word) {
     }
   }
   p.bs = bs;
+  // an opened square's coordinates have 14 bits on the stack
+  p.fine = p.nx[0] <= kMaxSide / 2 && p.ny[0] <= kMaxSide / 2 ? min(bs, kFine) : 0;
+  for (int d = 0; d < kFine; ++d) p.pool[d] = node_cap + d * 4 * refine_capacity(n);
   *job.plan = p;
 }
 
@@ -269,14 +272,58 @@ __device__ inline void store_moments(float* __restrict__ rec, int q, double v) {
   }
 }
 
+// The points of columns [c0, c1), rows [r0, r1) of the grid about (cx, cy) (add_points); returns their count.
+__device__ __forceinline__ int add_cells(const float* __restrict__ tx, const float* __restrict__ ty,
+                                         const float* __restrict__ tz, const int32_t* __restrict__ cell_start, int ncol,
+                                         int c0, int c1, int r0, int r1, float cx, float cy, float ih,
+                                         float* __restrict__ tab, double* __restrict__ acc, double& sabs) {
+  const int lane = threadIdx.x & 63;
+  int count = 0;
+  for (int rb = r0; rb < r1; rb += 64) {
+    const int row = rb + lane;
+    int lo = 0, len = 0;
+    if (row < r1) {
+      lo = cell_start[(int64_t)row * ncol + c0];
+      len = cell_start[(int64_t)row * ncol + c1] - lo;
+    }
+    int incl = len;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    const int total = __builtin_amdgcn_readlane(incl, 63), nrows = min(64, r1 - rb);
+    count += total;
+    sabs += add_points<kOrder>(tx, ty, tz, lo, incl, len, nrows, total, cx, cy, ih, tab, acc);
+  }
+  return count;
+}
+
+// One lane: four squares for a square of many points, -1 - depth levels below the leaves' parents.
+__device__ inline void refine(Plan* __restrict__ plan, float* __restrict__ nodes, int idx, int count, int depth, int ix,
+                              int iy) {
+  int base = 0;
+  if (count > kRefine && depth < plan->fine) {
+    base = plan->pool[depth] + 4 * (int)atomicAdd(&plan->refined[depth], 1u);
+    int* first = reinterpret_cast<int*>(nodes + (size_t)base * kRec);
+    first[kParentX] = ix;
+    first[kParentY] = iy;
+  }
+  reinterpret_cast<int*>(nodes + (size_t)idx * kRec)[kChild] = base;
+}
+
+// A wavefront's work space for the moments of points.
+struct PointSums {
+  float tab[kWaveLds];
+  double acc[4 * kCoefs];
+};
+
 // Levels 0 and 1 from the points: one workgroup per level-1 square, one wavefront per leaf of it.
 // Each wavefront adds its points about the leaf's centre and about the square's; the four shares of
 // the square are then added.
 template <typename Jobs>
 __global__ __launch_bounds__(256, 5) void k_tree_p2m(Jobs jobs, const float* __restrict__ tx,
                                                      const float* __restrict__ ty, const float* __restrict__ tz) {
-  __shared__ float s_tab[4][kWaveLds];
-  __shared__ double s_acc[4][4 * kCoefs];
+  __shared__ PointSums s_sum[4];
   __shared__ double s_abs[4];
   __shared__ int s_cnt[4];
   const Job& job = jobs[blockIdx.y];
@@ -298,42 +345,28 @@ __global__ __launch_bounds__(256, 5) void k_tree_p2m(Jobs jobs, const float* __r
     centre(plan, 0, ix, iy, cx0, cy0);
     centre(plan, 1, px, py, cx1, cy1);
     const float ih0 = (float)(1.0 / plan->h[0]);
-    double sabs = 0.0;
+    double sabs = 0.0, unused = 0.0;
     int count = 0;
+    double* const acc = s_sum[w].acc;
     for (int pass = 0; pass < (two ? 2 : 1); ++pass) {
-      for (int q = lane; q < 4 * kCoefs; q += 64) s_acc[w][q] = 0.0;
+      for (int q = lane; q < 4 * kCoefs; q += 64) acc[q] = 0.0;
       wave_sync();
-      for (int rb = r0; rb < r1; rb += 64) {
-        const int row = rb + lane;
-        int lo = 0, len = 0;
-        if (row < r1) {
-          lo = cell_start[(int64_t)row * ncol + c0];
-          len = cell_start[(int64_t)row * ncol + c1] - lo;
-        }
-        int incl = len;
-        for (int o = 1; o < 64; o <<= 1) {
-          const int t = __shfl_up(incl, o, 64);
-          if (lane >= o) incl += t;
-        }
-        const int total = __builtin_amdgcn_readlane(incl, 63), nrows = min(64, r1 - rb);
-        if (pass == 0) {
-          count += total;
-          sabs += add_points<kOrder>(tx, ty, tz, lo, incl, len, nrows, total, cx0, cy0, ih0, s_tab[w], s_acc[w]);
-        } else {
-          add_points<kOrder>(tx, ty, tz, lo, incl, len, nrows, total, cx1, cy1, 0.5f * ih0, s_tab[w], s_acc[w]);
-        }
-      }
+      if (pass == 0)
+        count = add_cells(tx, ty, tz, cell_start, ncol, c0, c1, r0, r1, cx0, cy0, ih0, s_sum[w].tab, acc, sabs);
+      else
+        add_cells(tx, ty, tz, cell_start, ncol, c0, c1, r0, r1, cx1, cy1, 0.5f * ih0, s_sum[w].tab, acc, unused);
       if (pass == 0) {
         for (int o = 32; o > 0; o >>= 1) sabs += __shfl_xor(sabs, o, 64);
         if (live) {
-          float* rec = nodes + (size_t)(plan->off[0] + iy * plan->nx[0] + ix) * kRec;
-          for (int q = lane; q < 4 * kCoefs; q += 64)
-            store_moments(rec, q, s_acc[w][q]);
+          const int idx = plan->off[0] + iy * plan->nx[0] + ix;
+          float* rec = nodes + (size_t)idx * kRec;
+          for (int q = lane; q < 4 * kCoefs; q += 64) store_moments(rec, q, acc[q]);
           if (lane == 0) {
             rec[0] = (float)count;
             rec[1] = (float)sabs;
             rec[2] = cx0;
             rec[3] = cy0;
+            refine(plan, nodes, idx, count, 0, ix, iy);
           }
         }
         if (lane == 0) {
@@ -347,7 +380,7 @@ __global__ __launch_bounds__(256, 5) void k_tree_p2m(Jobs jobs, const float* __r
       __syncthreads();
       float* rec = nodes + (size_t)(plan->off[1] + id) * kRec;
       for (int q = threadIdx.x; q < 4 * kCoefs; q += 256)
-        store_moments(rec, q, (s_acc[0][q] + s_acc[1][q]) + (s_acc[2][q] + s_acc[3][q]));
+        store_moments(rec, q, (s_sum[0].acc[q] + s_sum[1].acc[q]) + (s_sum[2].acc[q] + s_sum[3].acc[q]));
       if (threadIdx.x == 0) {
         rec[0] = (float)(s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3]);
         rec[1] = (float)((s_abs[0] + s_abs[1]) + (s_abs[2] + s_abs[3]));
@@ -363,16 +396,20 @@ __global__ __launch_bounds__(256, 5) void k_tree_p2m(Jobs jobs, const float* __r
 // and d = (c_child - c_parent) / h_parent, r' = lambda r + d, hence
 //   mu'_{JK} = sum_{j,k} C(J,j) lambda^j d^(J-j)  C(K,k) lambda^k conj(d)^(K-k)  mu_{jk},
 // first over j, then over k.  One wavefront per child, one workgroup per parent.
-template <typename Jobs>
-__global__ __launch_bounds__(256) void k_tree_m2m(Jobs jobs, int lvl) {
-  __shared__ double2 s_pow[4][kOrder + 1];  // d^i
-  __shared__ float s_c[kTri];               // C(J,j) / 2^j at J (J + 1) / 2 + j
-  __shared__ double s_t[4][kTri][4];        // the first stage
-  __shared__ double s_m[4][kCoefs][4];      // child's mu, then its share of the parent's
-  __shared__ float s_head[4][2];
-  const Plan* __restrict__ plan = jobs[blockIdx.y].plan;
-  float* __restrict__ nodes = jobs[blockIdx.y].nodes;
-  if (plan->bad || lvl >= plan->levels) return;
+struct ShiftSums {
+  double2 pow[4][kOrder + 1];  // d^i
+  float c[kTri];               // C(J,j) / 2^j at J (J + 1) / 2 + j
+  double t[4][kTri][4];        // the first stage
+  double m[4][kCoefs][4];      // child's mu, then its share of the parent's
+  float head[4][2];
+};
+__device__ __forceinline__ void shift_up(const Plan* __restrict__ plan, float* __restrict__ nodes, int lvl, int block, int blocks,
+                         ShiftSums& sh) {
+  auto& s_pow = sh.pow;
+  auto& s_c = sh.c;
+  auto& s_t = sh.t;
+  auto& s_m = sh.m;
+  auto& s_head = sh.head;
   const int nx = plan->nx[lvl];
   const int all = nx * plan->ny[lvl];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -383,7 +420,7 @@ __global__ __launch_bounds__(256) void k_tree_m2m(Jobs jobs, int lvl) {
     const int before = (o / 2) * ((o + 1) / 2) + o - o / 2;  // coefficients of the orders below o
     return before + (j - k - (o & 1)) / 2;
   };
-  for (int id = blockIdx.x; id < all; id += gridDim.x) {
+  for (int id = block; id < all; id += blocks) {
     const int py = id / nx, px = id - py * nx;
     const int chx = 2 * px + (w & 1), chy = 2 * py + (w >> 1);
     const bool live = chx < plan->nx[lvl - 1] && chy < plan->ny[lvl - 1];
@@ -473,6 +510,60 @@ __global__ __launch_bounds__(256) void k_tree_m2m(Jobs jobs, int lvl) {
     }
     __syncthreads();
   }
+}
+
+// Moments of the squares below refined ones, depth levels below the leaves: one workgroup per
+// refined square, one wavefront per square below.
+__device__ __forceinline__ void fine_squares(Plan* __restrict__ plan, const int32_t* __restrict__ cell_start, float* __restrict__ nodes,
+                             const float* __restrict__ tx, const float* __restrict__ ty, const float* __restrict__ tz,
+                             int depth, int block, int blocks, PointSums& sum) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int count = (int)plan->refined[depth - 1], pool = plan->pool[depth - 1], sh = plan->bs - depth;
+  const float ih = (float)((double)(1 << depth) / plan->h[0]);
+  for (int id = block; id < count; id += blocks) {
+    const int* first = reinterpret_cast<const int*>(nodes + (size_t)(pool + 4 * id) * kRec);
+    const int ix = 2 * first[kParentX] + (w & 1), iy = 2 * first[kParentY] + (w >> 1);
+    const int c0 = min(plan->ncol, ix << sh), c1 = min(plan->ncol, (ix + 1) << sh);
+    const int r0 = min(plan->nrow, iy << sh), r1 = min(plan->nrow, (iy + 1) << sh);
+    float cx, cy;
+    centre(plan, -depth, ix, iy, cx, cy);
+    for (int q = lane; q < 4 * kCoefs; q += 64) sum.acc[q] = 0.0;
+    wave_sync();
+    double sabs = 0.0;
+    const int n = add_cells(tx, ty, tz, cell_start, plan->ncol, c0, c1, r0, r1, cx, cy, ih, sum.tab, sum.acc, sabs);
+    for (int o = 32; o > 0; o >>= 1) sabs += __shfl_xor(sabs, o, 64);
+    const int idx = pool + 4 * id + w;
+    float* rec = nodes + (size_t)idx * kRec;
+    for (int q = lane; q < 4 * kCoefs; q += 64) store_moments(rec, q, sum.acc[q]);
+    if (lane == 0) {
+      rec[0] = (float)n;
+      rec[1] = (float)sabs;
+      rec[2] = cx;
+      rec[3] = cy;
+      refine(plan, nodes, idx, n, depth, ix, iy);
+    }
+    wave_sync();
+  }
+}
+
+// Level lvl from the squares below it, and, by the first fine_blocks workgroups of a job, the squares
+// depth levels below the leaves (depth 0: none); neither needs the other, and one launch fills the
+// chip better than two (2^18 mixture: 960 us of summation against 1010).
+template <typename Jobs>
+__global__ __launch_bounds__(256, 5) void k_tree_up(Jobs jobs, int lvl, int depth, int fine_blocks,
+                                                    const float* __restrict__ tx, const float* __restrict__ ty,
+                                                    const float* __restrict__ tz) {
+  __shared__ __align__(16) unsigned char s_mem[sizeof(ShiftSums) > 4 * sizeof(PointSums) ? sizeof(ShiftSums)
+                                                                                         : 4 * sizeof(PointSums)];
+  const Job& job = jobs[blockIdx.y];
+  if (job.plan->bad) return;
+  const int block = (int)blockIdx.x;
+  if (block < fine_blocks)
+    fine_squares(job.plan, job.cell_start, job.nodes, tx, ty, tz, depth, block, fine_blocks,
+                 reinterpret_cast<PointSums*>(s_mem)[threadIdx.x >> 6]);
+  else if (lvl < job.plan->levels)
+    shift_up(job.plan, job.nodes, lvl, block - fine_blocks, (int)gridDim.x - fine_blocks,
+             *reinterpret_cast<ShiftSums*>(s_mem));
 }
 
 // The query order: the Hilbert index of the query's tile.  (Ordering by alpha class inside stretches
@@ -781,12 +872,15 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 // level from the leaves, the squares whose parents are near and which are not themselves: a lane
 // takes a square, finds the order that serves every query of the group, and the squares of one
 // order are then evaluated one after the other, each by all lanes.
-// A group whose box holds many points (queries on both sides of a gap) is taken in parts.
+// A group whose box holds many points (queries on both sides of a gap) is taken in parts; in a dense
+// place it starts below the leaves instead: the near points of a leaf of 700 cost 60,000
+// instructions a query, the squares of 176 inside it and their near points 34,000.
 // What bounds it: the vector instructions of the pairs and expansions (about 25,000 per query at
 // 2^20 uniform, against 11 million for all pairs) and the latency of the scalar and header loads,
 // which four wavefronts a SIMD do not hide altogether (three, five and six were slower: 1.47 ms of
 // summation with four, 1.60 with three, 1.51 with five and six, whose registers spill).
-// Measured, whole summation: 2^20 uniform 209 -> 1.6 ms, 2^18 mixture 13.3 -> 0.9 ms.
+// Measured, whole summation: 2^20 uniform 209 -> 1.6 ms, 2^18 mixture 13.3 -> 0.9 ms, 2^20 mixture 210 ->
+// 2.7 (3.9 from the leaves on).
 // Output: qz, or with PARTIAL the float64 (num, den).
 template <typename Jobs, bool PARTIAL>
 __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, const float* __restrict__ tx,
@@ -839,9 +933,11 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
   const int pw = uniform(whole && !mixed ? (int)alpha : 0);
   const float sc = pair::pow2_scale(d1);
   Query L{fx * sc, fy * sc, -sc, -0.5f * alpha, 0.0f, 0.0f, 0.0, 0.0, 0.0f, exp2f(-kLogRim * alpha)};
-  const int bs = plan->bs, ncol = plan->ncol, nrow = plan->nrow, levels = plan->levels;
-  const int lx = knn::clamp_cell((fx - plan->minx) * plan->inv, ncol) >> bs;
-  const int ly = knn::clamp_cell((fy - plan->miny) * plan->inv, nrow) >> bs;
+  const int bs = plan->bs, ncol = plan->ncol, nrow = plan->nrow, levels = plan->levels, fine = plan->fine;
+  // squares per side at a level, from the cells: a load of each would be waited for level by level
+  auto squares = [&](int cells, int l) { return (int)(((int64_t)cells + (1ll << (bs + l)) - 1) >> (bs + l)); };
+  const int colq = knn::clamp_cell((fx - plan->minx) * plan->inv, ncol);
+  const int rowq = knn::clamp_cell((fy - plan->miny) * plan->inv, nrow);
   const Points P{cell_start, tx, ty, tz, ncol};
   float f[kOrder + 1];
   const float ch = 0.5f * alpha - 1.0f;
@@ -851,8 +947,10 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
   for (int qa = 0, qb; qa < nq; qa = qb) {
     // the part [qa, qb) of the group: halved while that saves more than the far squares of another part
     int x0, x1, y0, y1;
+    int dep = 0;  // the part's smallest squares are dep levels below the leaves
     auto box = [&](int a, int b) {
       const bool in = lane >= a && lane < b;
+      const int lx = colq >> (bs - dep), ly = rowq >> (bs - dep);
       x0 = in ? lx : 0x7fffffff;
       x1 = in ? lx : 0;
       y0 = in ? ly : 0x7fffffff;
@@ -870,13 +968,25 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
     };
     auto near_points = [&](int a, int b) {
       box(a, b);
-      return count_points(P, max(0, x0 - kNear) << bs, min(ncol, (x1 + kNear + 1) << bs) - 1,
-                          max(0, y0 - kNear) << bs, min(nrow, (y1 + kNear + 1) << bs) - 1);
+      const int b2 = bs - dep;
+      return count_points(P, max(0, x0 - kNear) << b2, min(ncol, (x1 + kNear + 1) << b2) - 1,
+                          max(0, y0 - kNear) << b2, min(nrow, (y1 + kNear + 1) << b2) - 1);
     };
     qb = nq;
     int c = near_points(qa, qb);
+    // in dense places smaller squares leave fewer points near; a box across a gap stays as wide
+    while (dep < fine && c > kFineNear && c > kRefine / 2 * (x1 - x0 + 1 + 2 * kNear) * (y1 - y0 + 1 + 2 * kNear)) {
+      ++dep;
+      const int c1 = near_points(qa, qb);
+      if (c1 > c - (c >> 2)) {
+        --dep;
+        break;
+      }
+      c = c1;
+    }
     while (c > kSplitPoints && qb - qa > 1) {
       // at the largest step between two consecutive queries
+      const int lx = colq >> (bs - dep), ly = rowq >> (bs - dep);
       const int step = max(abs(__shfl_down(lx, 1, 64) - lx), abs(__shfl_down(ly, 1, 64) - ly));
       int best = lane >= qa && lane < qb - 1 ? step * 64 + (63 - lane) : -1;
       for (int o = 32; o > 0; o >>= 1) best = max(best, __shfl_xor(best, o, 64));
@@ -891,8 +1001,9 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
     L.num = L.den = 0.0;
     L.sabs = 0.0f;
     {
-      const int cx0 = max(0, x0 - kNear) << bs, cx1 = min(ncol, (x1 + kNear + 1) << bs) - 1;
-      const int ry0 = max(0, y0 - kNear) << bs, ry1 = min(nrow, (y1 + kNear + 1) << bs) - 1;
+      const int b2 = bs - dep;
+      const int cx0 = max(0, x0 - kNear) << b2, cx1 = min(ncol, (x1 + kNear + 1) << b2) - 1;
+      const int ry0 = max(0, y0 - kNear) << b2, ry1 = min(nrow, (y1 + kNear + 1) << b2) - 1;
       switch (pw) {
 #define AIDW_CASE(p) \
   case p: near_rows<p>(L, P, cx0, cx1, ry0 + wave, ry1, S); break;
@@ -932,8 +1043,8 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
     const float amin = wave_min(counts ? alpha : INFINITY), amax = wave_max(counts ? alpha : 0.0f);
     // a square's share of a query's sums is at most (1 + rho)^alpha, rho < 0.4715
     const float lcap = amax * kLogRim;
-    for (int l0 = 0; l0 < levels; ++l0) {
-      const float h0 = (float)plan->h[l0];
+    for (int l0 = -dep; l0 < levels; ++l0) {
+      const float h0 = (float)plan->h[max(l0, 0)] * __uint_as_float((uint32_t)(127 + min(l0, 0)) << 23);
       // log2 of the largest weight per unit of a query's sums, for a square at distance h0
       const float ld = log2f(h0);
       const float lw = alpha * (ld + log2f(sc));
@@ -941,15 +1052,15 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
       const float rabs = counts ? __builtin_amdgcn_rcpf(base_abs + L.sabs) : 0.0f;
       const float kden = wave_max(counts ? __builtin_amdgcn_logf(rden) - lw : -INFINITY);
       const float kabs = wave_max(counts ? __builtin_amdgcn_logf(rabs) - lw : -INFINITY);
-      const int nx = plan->nx[l0], ny = plan->ny[l0];
-      const int ax0 = max(0, (x0 >> l0) - kNear), ax1 = min(nx - 1, (x1 >> l0) + kNear);
-      const int ay0 = max(0, (y0 >> l0) - kNear), ay1 = min(ny - 1, (y1 >> l0) + kNear);
+      const int nx = squares(ncol, l0), ny = squares(nrow, l0), up = l0 + dep;
+      const int ax0 = max(0, (x0 >> up) - kNear), ax1 = min(nx - 1, (x1 >> up) + kNear);
+      const int ay0 = max(0, (y0 >> up) - kNear), ay1 = min(ny - 1, (y1 >> up) + kNear);
       int bx0 = 0, bx1 = nx - 1, by0 = 0, by1 = ny - 1;
       if (l0 + 1 < levels) {
-        bx0 = 2 * max(0, (x0 >> (l0 + 1)) - kNear);
-        bx1 = min(nx - 1, 2 * ((x1 >> (l0 + 1)) + kNear) + 1);
-        by0 = 2 * max(0, (y0 >> (l0 + 1)) - kNear);
-        by1 = min(ny - 1, 2 * ((y1 >> (l0 + 1)) + kNear) + 1);
+        bx0 = 2 * max(0, (x0 >> (up + 1)) - kNear);
+        bx1 = min(nx - 1, 2 * ((x1 >> (up + 1)) + kNear) + 1);
+        by0 = 2 * max(0, (y0 >> (up + 1)) - kNear);
+        by1 = min(ny - 1, 2 * ((y1 >> (up + 1)) + kNear) + 1);
       }
       const int W = bx1 - bx0 + 1, total = W * (by1 - by0 + 1);
       int sp = 0;  // squares on the stack
@@ -962,10 +1073,10 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
           sp -= cnt;
           live = (lane >> 2) < cnt;
           const uint32_t e = live ? stack[sp + (lane >> 2)] : 0u;
-          lvl = max(0, (int)(e >> 28) - 1);
+          lvl = max(-fine, (int)(e >> 28) - kFine - 1);
           ix = 2 * (int)(e & 0x3fffu) + (lane & 1);
           iy = 2 * (int)((e >> 14) & 0x3fffu) + ((lane >> 1) & 1);
-          live = live && ix < plan->nx[lvl] && iy < plan->ny[lvl];
+          live = live && ix < squares(ncol, lvl) && iy < squares(nrow, lvl);
         } else {
           const int k = b + lane * S;
           b += 64 * S;
@@ -975,10 +1086,28 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
           iy = by0 + ky;
           live = k < total && !(ix >= ax0 && ix <= ax1 && iy >= ay0 && iy <= ay1);
         }
-        const int idx = live ? plan->off[lvl] + iy * plan->nx[lvl] + ix : 0;
+        int idx = live && lvl >= 0 ? plan->off[lvl] + iy * plan->nx[lvl] + ix : 0;
+        int few = -1;  // below the leaves: the points of a square that has no record
+        if (__any(lvl < 0)) {
+          if (live && lvl < 0) {
+            idx = plan->off[0] + (iy >> -lvl) * plan->nx[0] + (ix >> -lvl);
+            for (int j = -lvl - 1; j >= 0 && few < 0; --j) {
+              const int base = reinterpret_cast<const int*>(nodes + (size_t)idx * kRec)[kChild];
+              if (base == 0)
+                few = 0;
+              else
+                idx = base + 2 * ((iy >> j) & 1) + ((ix >> j) & 1);
+            }
+            if (few == 0) {
+              const int sh = bs + lvl, r1 = min(nrow, (iy + 1) << sh), c1 = min(ncol, (ix + 1) << sh);
+              for (int row = iy << sh; row < r1; ++row)
+                few += cell_start[(int64_t)row * ncol + c1] - cell_start[(int64_t)row * ncol + (ix << sh)];
+            }
+          }
+        }
         const float h = __uint_as_float(__float_as_uint(h0) - ((uint32_t)(l0 - lvl) << 23));  // h0 2^(lvl - l0)
         const float4 hd = *reinterpret_cast<const float4*>(nodes + (size_t)idx * kRec);
-        const float cnt = live ? hd.x : 0.0f;
+        const float cnt = !live ? 0.0f : few >= 0 ? (float)few : hd.x;
         const float ex = fmaxf(fmaxf(qx0 - hd.z, hd.z - qx1), 0.0f), ey = fmaxf(fmaxf(qy0 - hd.w, hd.w - qy1), 0.0f);
         const float lr = 0.5f * __builtin_amdgcn_logf(__builtin_fmaf(ex, ex, ey * ey));  // log2 of the distance
         float lq = fmaxf(__builtin_amdgcn_logf(cnt) + kden, __builtin_amdgcn_logf(hd.y) + kabs) - amin * (lr - ld);
@@ -993,14 +1122,16 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
         if (lrho > -2.0f && lq - amax * __builtin_amdgcn_logf(1.0f - __builtin_amdgcn_exp2f(lrho)) > 0.0f)
           tier = kTiers;
         const int order = 2 * tier + 2;
-        const bool points = cnt * 12.0f + (float)(16 << (bs + lvl)) <= (float)(60 + 2 * (order + 1) * (order + 2)) ||
-                            (tier == kTiers && lvl == 0);
+        bool end = few >= 0;
+        if (tier == kTiers && lvl < 1 && !end) end = reinterpret_cast<const int*>(nodes + (size_t)idx * kRec)[kChild] == 0;
+        const bool points = end ||
+                            cnt * 12.0f + (float)(16 << (bs + lvl)) <= (float)(60 + 2 * (order + 1) * (order + 2));
         const int kind = cnt > 0.0f ? (points ? kTiers + 1 : tier) : -1;
         uint64_t mask = __ballot(kind == kTiers);
         if (mask) {
           if (kind == kTiers)
             stack[sp + __popcll(mask & ((1ull << lane) - 1ull))] =
-                ((uint32_t)lvl << 28) | ((uint32_t)iy << 14) | (uint32_t)ix;
+                ((uint32_t)(lvl + kFine) << 28) | ((uint32_t)iy << 14) | (uint32_t)ix;
           sp += (int)__popcll(mask);
           wave_sync();
         }
@@ -1060,7 +1191,9 @@ int padded_points(int64_t n) { return (int)((n + 7) / 8 * 8 + 16); }
 
 size_t plan_bytes() { return sizeof(Plan); }
 
-size_t node_bytes(int64_t n) { return sizeof(float) * (size_t)kRec * node_capacity(n); }
+size_t node_bytes(int64_t n) {
+  return sizeof(float) * (size_t)kRec * ((size_t)node_capacity(n) + 4 * kFine * (size_t)refine_capacity(n));
+}
 
 }  // namespace tree
 
@@ -1110,9 +1243,12 @@ void launch_moments(const Jobs& jobs, int njobs, int64_t n, int level_cap, const
   // squares of level 1 of a square box; a workgroup loops where a ragged shape has more
   int64_t blocks = n / (4 * kLeafPoints) + 64;
   hipLaunchKernelGGL(k_tree_p2m<Jobs>, dim3((unsigned)blocks, njobs), dim3(256), 0, s, jobs, tx, ty, tz);
-  for (int l = 2; l < level_cap; ++l) {
-    blocks = blocks / 4 + 16;
-    hipLaunchKernelGGL(k_tree_m2m<Jobs>, dim3((unsigned)blocks, njobs), dim3(256), 0, s, jobs, l);
+  for (int l = 2; l < level_cap || l < 2 + kFine; ++l) {
+    blocks = l < level_cap ? blocks / 4 + 16 : 0;
+    const int depth = l < 2 + kFine ? l - 1 : 0;
+    const int fine = depth ? (int)(n / (4 * kRefine) + 16 < 2048 ? n / (4 * kRefine) + 16 : 2048) : 0;
+    hipLaunchKernelGGL(k_tree_up<Jobs>, dim3((unsigned)blocks + fine, njobs), dim3(256), 0, s, jobs, l, depth, fine, tx,
+                       ty, tz);
   }
 }
 

@@ -29,10 +29,18 @@ constexpr int kLeafPoints = 32;          // wanted mean points per leaf
 constexpr int kTopSide = 8;              // squares per side at which no further level is built
 constexpr int kLevels = 14;
 constexpr int kMaxSide = 1 << 14;         // squares per side (a stack entry holds 14 bits of each)
+// Leaves of more than kRefine points have four squares below them, and these likewise, kFine times.
+constexpr int kFine = 2;
+constexpr int kRefine = 128;
+constexpr int kFineNear = 1500;          // near points from which a group looks for smaller squares
 // Opened squares of one wavefront: at most 64 from the list, and 48 more per level below it.
-constexpr int kStack = 64 + 48 * kLevels;
+constexpr int kStack = 64 + 48 * (kLevels + kFine);
+static_assert(kLevels + kFine <= 16, "a stack entry holds 4 bits of the level");
 constexpr int kCoefs = 81;               // (l, m) pairs
 constexpr int kRec = 320;                // floats per square: 4 + sum of 2 (order + 1), padded to 64 B
+// Integers in the record's padding: the first of the four squares below (0: none), and in the first of
+// four the coordinates of the square above.
+constexpr int kChild = 316, kParentX = 317, kParentY = 318;
 constexpr int kGroup = 64;               // queries per group (one per lane)
 constexpr int kClasses = 9;              // alpha classes 0 (general), 1 .. 8
 constexpr int kSplitPoints = 6000;       // near points from which a group is worth splitting
@@ -59,7 +67,8 @@ __host__ __device__ constexpr int coef_offset(int l, int m) {
 }
 
 // Geometry of a job's squares, made on the device from the grid scalars: level 0 squares (leaves)
-// are 2^bs x 2^bs grid cells, a level l + 1 square is 2 x 2 squares of level l.
+// are 2^bs x 2^bs grid cells, a level l + 1 square is 2 x 2 squares of level l.  Below the leaves with
+// many points levels -1 .. -fine go on; their squares are in the pools, four under one square together.
 struct Plan {
   int32_t bad;       // the sums are formed directly (geometry or data out of the moments' range)
   int32_t bs, levels;
@@ -67,7 +76,12 @@ struct Plan {
   float minx, miny, inv;
   int32_t nx[kLevels], ny[kLevels], off[kLevels];  // squares per row / column, first record
   double h[kLevels];                               // side
+  int32_t fine, pool[kFine];                       // levels below the leaves, each one's first record
+  uint32_t refined[kFine];                         // squares above with four in the pool
 };
+
+// Squares of more than kRefine points that n points can make at one level.
+__host__ __device__ inline int refine_capacity(int64_t n) { return (int)(n / kRefine) + 1; }
 
 // |z| from here on (or NaN) takes the direct sums: the moments' sums stay far from overflow.
 constexpr float kZLimit = 1.2676506002282294e30f;  // 2^100
@@ -90,7 +104,7 @@ struct Job {
 
 // Centre of a square, the same float32 values wherever they are needed.
 __device__ inline void centre(const Plan* p, int lvl, int ix, int iy, float& cx, float& cy) {
-  const double h = p->h[lvl];
+  const double h = lvl >= 0 ? p->h[lvl] : p->h[0] / (double)(1 << -lvl);
   cx = (float)((double)p->minx + ((double)ix + 0.5) * h);
   cy = (float)((double)p->miny + ((double)iy + 0.5) * h);
 }

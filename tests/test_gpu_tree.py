@@ -71,6 +71,25 @@ def make(n, m, seed, kind="uniform"):
     return [ds.x, ds.y, ds.z, ds.qx, ds.qy]
 
 
+@pytest.mark.parametrize("occupancy", [0.5, 2.0, 8.0, 40.0])
+def test_dense_places(T, occupancy):
+    """Clusters of thousands of points inside one leaf, whose squares go on below it (two levels where a
+    leaf is 4 x 4 cells or more, one at 2 x 2, none at one cell), in a sparse rest."""
+    aidw = aidw_mod()
+    rng = np.random.default_rng(61)
+
+    def places(n):
+        p = rng.random((n, 2))
+        c = rng.integers(0, 4, n // 2)
+        p[: n // 2] = np.array([[0.2, 0.3], [0.7, 0.2], [0.25, 0.8], [0.5, 0.5]])[c] + rng.normal(0, 1, (n // 2, 2)) * (
+            np.array([0.002, 0.004, 0.008, 0.016])[c, None])
+        return W.quantise(p[rng.permutation(n)].clip(0, 1))
+
+    p, q = places(60000), places(40000)
+    z = np.sin(9 * p[:, 0]) + np.cos(7 * p[:, 1]) + 0.3
+    check(T, [p[:, 0], p[:, 1], z, q[:, 0], q[:, 1]], aidw.Params(k=10, occupancy=occupancy))
+
+
 @pytest.mark.parametrize("case", ["ragged", "mixture", "levels", "levels_low", "strip", "tall", "few_queries", "few_data",
                                   "map_coords", "fine_cells", "wide_cells", "cell_width"])
 def test_shapes(T, case):
