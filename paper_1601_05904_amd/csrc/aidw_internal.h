@@ -248,8 +248,6 @@ int interp_padded_len(int n);
 // zero_word (may be null) is cleared by the same launch.
 hipError_t launch_pad_copy(const float* x, const float* y, const float* z, int n, float* xp, float* yp, float* zp,
                            uint32_t* zero_word, hipStream_t s);
-hipError_t launch_combine(const double2* partial, int m, int split, float* qz, hipStream_t s,
-                          const tree::Plan* fallback = nullptr);
 
 // ---- hierarchical summation (tree.hip, tree_core.h) ----
 namespace tree {
@@ -281,11 +279,20 @@ hipError_t launch_tree_batch(const tree::Job* jobs, int njobs, int64_t max_n, in
                              const float* alpha_f, const float* d1sq, const uint32_t* perm, double2* partial,
                              hipStream_t s);
 
-hipError_t launch_fixup_grid(const uint32_t* count, const uint32_t* list, const float* qx, const float* qy,
-                             const GridScalars* gs, const int32_t* cell_start, const float* sx, const float* sy,
-                             const int32_t* sidx, const float* z, float* qz, hipStream_t s);
-hipError_t launch_fixup_scan(const uint32_t* count, const uint32_t* list, const float* qx, const float* qy,
-                             const float* x, const float* y, const float* z, int n, float* qz, hipStream_t s);
+// The float64 (num, den) of split data ranges: partial[s * m + q].  With fallback, only where it is off.
+struct Partials {
+  const double2* partial;
+  int split, m;
+  const tree::Plan* fallback;
+};
+// Combines the partials (split > 1) and replaces the listed coincident queries' values.
+hipError_t launch_finish_grid(const Partials& P, const float* d1sq, const uint32_t* count, const uint32_t* list,
+                              const float* qx, const float* qy, const GridScalars* gs, const int32_t* cell_start,
+                              const float* sx, const float* sy, const int32_t* sidx, const float* z, float* qz,
+                              hipStream_t s);
+hipError_t launch_finish_scan(const Partials& P, const float* d1sq, const uint32_t* count, const uint32_t* list,
+                              const float* qx, const float* qy, const float* x, const float* y, const float* z, int n,
+                              float* qz, hipStream_t s);
 
 // ---- learned-R form ----
 

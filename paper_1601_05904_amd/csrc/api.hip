@@ -478,14 +478,19 @@ void choose_interp_config(int64_t n, int64_t m, int* q, int* split) {
   // 2048 points per split, at most 256 splits and 16 split m bytes of partials <= 1 GiB.
   // Fine splits keep the chip full when the queries are few (measured at 2^18 clustered
   // with one launch per class: 8 splits 64 % of the roofline, 128 splits 82 %; at 2^20
-  // uniform 32 -> 64 splits 86.0 -> 86.2 %).
+  // uniform 32 -> 64 splits 86.0 -> 86.2 %).  Where that leaves the chip short of 2048 workgroups it is
+  // split on, down to 64 points: a lone wavefront takes 45 ns a point (1000 points, 257 queries:
+  // 45 -> 9 us; 4096 x 4096: 88 -> 9 us).
   const int qq = g_cfg_q ? g_cfg_q : 1;
   int sp = 1;
   if (g_cfg_split) {
     sp = g_cfg_split;
   } else {
     const int64_t max_by_mem = ((int64_t)1 << 26) / (m > 0 ? m : 1);
-    while (sp < 256 && (int64_t)sp * 2 <= max_by_mem && n / ((int64_t)sp * 2) >= 2048) sp *= 2;
+    const int64_t blocks = (m + 256 * qq - 1) / (256 * qq);
+    while (sp < 256 && (int64_t)sp * 2 <= max_by_mem &&
+           n / ((int64_t)sp * 2) >= (blocks * sp < 2048 ? 64 : 2048))
+      sp *= 2;
   }
   if (g_split_cap > 0)
     while (sp > g_split_cap) sp >>= 1;
@@ -585,13 +590,15 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
     HIP_TRY(launch_interp(tx, ty, tz, (int)n, qx, qy, alpha_use, d1sq, sperm, skeys, (int)m, 0, 1, split, qz, partial,
                           status, s, plan),
             "interpolation kernel");
-    if (split > 1) HIP_TRY(launch_combine(partial, (int)m, split, qz, s, plan), "combine kernel");
     if (ev_end) HIP_TRY(hipEventRecord(ev_end, s), "event");
+    const Partials parts{partial, split, (int)m, plan};
     if (g && g->n == n)
-      HIP_TRY(launch_fixup_grid(count, list, qx, qy, g->dev, g->cell_start, g->sx, g->sy, g->sidx, z, qz, s),
+      HIP_TRY(launch_finish_grid(parts, d1sq, count, list, qx, qy, g->dev, g->cell_start, g->sx, g->sy, g->sidx, z, qz,
+                                 s),
               "coincidence fix-up kernel");
     else
-      HIP_TRY(launch_fixup_scan(count, list, qx, qy, x, y, z, (int)n, qz, s), "coincidence fix-up kernel");
+      HIP_TRY(launch_finish_scan(parts, d1sq, count, list, qx, qy, x, y, z, (int)n, qz, s),
+              "coincidence fix-up kernel");
     return AIDW_OK;
   }();
   if (own) aidw_grid_destroy(own);
@@ -674,12 +681,12 @@ aidw_status interp_impl(const float* x, const float* y, const float* z, int64_t 
             "interpolation kernel");
   }
   if (ev_end) HIP_TRY(hipEventRecord(ev_end, s), "event");
-  if (split > 1 && !naive) HIP_TRY(launch_combine(partial, (int)m, split, qz, s), "combine kernel");
+  const Partials parts{partial, naive ? 1 : split, (int)m, nullptr};
   if (g && g->n == n)
-    HIP_TRY(launch_fixup_grid(count, list, qx, qy, g->dev, g->cell_start, g->sx, g->sy, g->sidx, z, qz, s),
+    HIP_TRY(launch_finish_grid(parts, d1sq, count, list, qx, qy, g->dev, g->cell_start, g->sx, g->sy, g->sidx, z, qz, s),
             "coincidence fix-up kernel");
   else
-    HIP_TRY(launch_fixup_scan(count, list, qx, qy, x, y, z, (int)n, qz, s), "coincidence fix-up kernel");
+    HIP_TRY(launch_finish_scan(parts, d1sq, count, list, qx, qy, x, y, z, (int)n, qz, s), "coincidence fix-up kernel");
   return AIDW_OK;
 }
 

@@ -1,0 +1,55 @@
+"""Few queries: the data ranges that fill the chip with them, and the kernel that combines the ranges
+and replaces coincident queries.
+
+Bar: the library's stated 1e-5 in the normwise relative metric holds for each form, so two forms differ
+by at most twice that."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,m", [(12, 5), (127, 1), (128, 257), (129, 64), (513, 255), (1000, 256), (4097, 3000),
+                                 (16400, 20), (70001, 300)])
+def test_ranges_of_few_queries(n, m):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1601_05904_amd as aidw
+    aidw.load(build_if_missing=False)
+    rng = np.random.default_rng(n)
+    x, y = rng.random((2, n)).astype(np.float32)
+    x[n // 2:n // 2 + 3], y[n // 2:n // 2 + 3] = x[0], y[0]  # coincident data points
+    z = (rng.random(n) + 0.5).astype(np.float32)
+    qx, qy = rng.random((2, m)).astype(np.float32)
+    same = rng.random(m) < 0.2
+    own = rng.integers(0, n, m)
+    own[0] = 0
+    same[0] = True
+    qx[same], qy[same] = x[own[same]], y[own[same]]
+    x, y, z, qx, qy = (torch.from_numpy(a).cuda() for a in (x, y, z, qx, qy))
+    p = aidw.Params(k=10)
+    got, alpha, r_obs = aidw.run(x, y, z, qx, qy, p, want_alpha=True, want_robs=True)
+    grid = aidw.build_grid(x, y, qx, qy, p)
+    area = grid.describe()["area"]
+    _, d1, _ = aidw.knn(grid, qx, qy, 10)
+    grid.close()
+    d1 = d1.clone()
+    d1[-1] = 0.0  # claims a data point at its place: where there is none, the sums stand
+    pa = aidw.Params(k=10, area=area)
+    alone = aidw.interpolate(x, y, z, qx, qy, r_obs, d1, pa)
+    alone = alone[0] if isinstance(alone, tuple) else alone
+    aidw.set_interp_config(1, 1, 1)
+    try:
+        whole = aidw.run(x, y, z, qx, qy, p)
+        whole_alone = aidw.interpolate(x, y, z, qx, qy, r_obs, d1, pa)
+        whole_alone = whole_alone[0] if isinstance(whole_alone, tuple) else whole_alone
+    finally:
+        aidw.set_interp_config(0, 0, -1)
+    ref = (z[None].double() * ((qx[:, None] == x) & (qy[:, None] == y))).sum(1) / (
+        (qx[:, None] == x) & (qy[:, None] == y)).sum(1)
+    at = torch.isfinite(ref)
+    assert bool(at[0]) and torch.allclose(got[at].double(), ref[at], rtol=1e-6, atol=0)
+    for a, b in ((got, whole), (alone, whole_alone)):
+        assert bool(torch.isfinite(a).all())
+        assert float(((a - b).abs() / b.abs()).max()) <= 2e-5
