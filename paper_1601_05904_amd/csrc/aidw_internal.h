@@ -245,6 +245,13 @@ hipError_t launch_interp_naive(const float* x, const float* y, const float* z, i
                                const float* alpha_f, const float* d1sq, int m, float* qz, hipStream_t s);
 // Zero-padded copies of x, y, z for the pair kernels, which may prefetch one chunk past n.
 int interp_padded_len(int n);
+// For m <= kSmallQueries queries, in one launch: the padded copies, alpha (of r_obs, or alpha_in), the
+// class keys and order (sorted by class with sort, else the identity) and the coincident-query list.
+constexpr int kSmallQueries = 8192;
+hipError_t launch_small_prologue(const float* x, const float* y, const float* z, int n, float* xp, float* yp, float* zp,
+                                 const float* r_obs, const float* alpha_in, int m, const AlphaParams& ap, bool sort,
+                                 float* alpha_f, float* alpha_out, uint32_t* keys, uint32_t* perm, const float* d1sq,
+                                 uint32_t* count, uint32_t* list, hipStream_t s);
 // zero_word (may be null) is cleared by the same launch.
 hipError_t launch_pad_copy(const float* x, const float* y, const float* z, int n, float* xp, float* yp, float* zp,
                            uint32_t* zero_word, hipStream_t s);

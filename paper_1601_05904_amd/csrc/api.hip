@@ -643,37 +643,45 @@ aidw_status interp_impl(const float* x, const float* y, const float* z, int64_t 
   const uint32_t fast_mask = g_cfg_intpow ? integer_levels(p) : 0;
   Temps t(s);
   double2* partial = nullptr;
-  uint32_t *count, *list, *keys, *perm, *tk, *tv, *hist, *scan;
+  const bool small = !naive && m <= kSmallQueries;
+  uint32_t *count, *list, *keys, *perm, *tk = nullptr, *tv = nullptr, *hist = nullptr, *scan = nullptr;
   float *alpha_f, *xp, *yp, *zp;
   const int npad = interp_padded_len((int)n);
   hipError_t e;
   if (split > 1 && (e = t.get(&partial, (size_t)split * m)) != hipSuccess) return hip_fail(e, "allocating partials");
   if ((e = t.get(&count, 1)) != hipSuccess || (e = t.get(&list, m)) != hipSuccess ||
       (e = t.get(&alpha_f, m)) != hipSuccess || (e = t.get(&keys, m)) != hipSuccess ||
-      (e = t.get(&perm, m)) != hipSuccess || (e = t.get(&tk, m)) != hipSuccess || (e = t.get(&tv, m)) != hipSuccess ||
-      (e = t.get(&hist, radix_hist_words((int)m))) != hipSuccess ||
-      (e = t.get(&scan, radix_scan_tmp_words((int)m))) != hipSuccess || (e = t.get(&xp, npad)) != hipSuccess ||
+      (e = t.get(&perm, m)) != hipSuccess || (e = t.get(&xp, npad)) != hipSuccess ||
       (e = t.get(&yp, npad)) != hipSuccess || (e = t.get(&zp, npad)) != hipSuccess)
     return hip_fail(e, "allocating interpolation buffers");
-  // the coincident-query count is cleared by the padding copy (or on its own for the untiled
-  // kernel) and the list filled by the class-key kernel
-  if (!naive)
-    HIP_TRY(launch_pad_copy(x, y, z, (int)n, xp, yp, zp, count, s), "padding copy");
-  else
-    HIP_TRY(hipMemsetAsync(count, 0, sizeof(uint32_t), s), "clearing coincidence count");
-  const float* alpha_use = alpha_f;
-  if (alpha_in) {  // alpha given per query: only the class keys are needed
-    alpha_use = alpha_in;
-    if (alpha_out)
-      HIP_TRY(hipMemcpyAsync(alpha_out, alpha_in, sizeof(float) * m, hipMemcpyDeviceToDevice, s), "copying alpha");
-    HIP_TRY(launch_class_keys(alpha_in, (int)m, keys, perm, d1sq, count, list, s), "class key kernel");
-  } else {
-    HIP_TRY(launch_alpha_class(r_obs, (int)m, ap, alpha_f, alpha_out, keys, perm, d1sq, count, list, s),
-            "alpha kernel");
-  }
+  if (!small && ((e = t.get(&tk, m)) != hipSuccess || (e = t.get(&tv, m)) != hipSuccess ||
+                 (e = t.get(&hist, radix_hist_words((int)m))) != hipSuccess ||
+                 (e = t.get(&scan, radix_scan_tmp_words((int)m))) != hipSuccess))
+    return hip_fail(e, "allocating interpolation buffers");
+  const float* alpha_use = alpha_in ? alpha_in : alpha_f;
   uint32_t *ckeys = keys, *cperm = perm;  // the class order (in keys / perm or in the temporaries)
-  if (fast_mask && !naive)
-    HIP_TRY(radix_sort_pairs_to(keys, perm, tk, tv, (int)m, 4, hist, scan, s, &ckeys, &cperm), "class sort");
+  if (small) {
+    HIP_TRY(launch_small_prologue(x, y, z, (int)n, xp, yp, zp, r_obs, alpha_in, (int)m, ap, fast_mask != 0, alpha_f,
+                                  alpha_out, keys, perm, d1sq, count, list, s),
+            "alpha and class order");
+  } else {
+    // the coincident-query count is cleared by the padding copy (or on its own for the untiled
+    // kernel) and the list filled by the class-key kernel
+    if (!naive)
+      HIP_TRY(launch_pad_copy(x, y, z, (int)n, xp, yp, zp, count, s), "padding copy");
+    else
+      HIP_TRY(hipMemsetAsync(count, 0, sizeof(uint32_t), s), "clearing coincidence count");
+    if (alpha_in) {  // alpha given per query: only the class keys are needed
+      if (alpha_out)
+        HIP_TRY(hipMemcpyAsync(alpha_out, alpha_in, sizeof(float) * m, hipMemcpyDeviceToDevice, s), "copying alpha");
+      HIP_TRY(launch_class_keys(alpha_in, (int)m, keys, perm, d1sq, count, list, s), "class key kernel");
+    } else {
+      HIP_TRY(launch_alpha_class(r_obs, (int)m, ap, alpha_f, alpha_out, keys, perm, d1sq, count, list, s),
+              "alpha kernel");
+    }
+    if (fast_mask && !naive)
+      HIP_TRY(radix_sort_pairs_to(keys, perm, tk, tv, (int)m, 4, hist, scan, s, &ckeys, &cperm), "class sort");
+  }
   if (ev_begin) HIP_TRY(hipEventRecord(ev_begin, s), "event");
   if (naive) {
     HIP_TRY(launch_interp_naive(x, y, z, (int)n, qx, qy, alpha_use, d1sq, (int)m, qz, s),

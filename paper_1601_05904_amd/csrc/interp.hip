@@ -93,6 +93,97 @@ __global__ __launch_bounds__(256) void k_class_keys(const float* __restrict__ al
   vals[q] = (uint32_t)q;
 }
 
+// For few queries, everything before the pair kernel in one launch: workgroup 0 takes alpha, the class
+// keys, the coincident-query list and the stable order by class (as k_alpha_class or k_class_keys and
+// the sort), the others the padded copies (as k_pad_copy).  It is bound by launches: six kernels
+// of 2 to 10 us took 45 us with the gaps between them, this one 12 us (4096 queries); one
+// workgroup sorts kSmallQueries in less time than the four launches of the sort take.
+constexpr int kPrologueThreads = 1024;
+constexpr int kPrologueItems = kSmallQueries / kPrologueThreads;
+__global__ __launch_bounds__(kPrologueThreads) void k_small_prologue(
+    const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ z, int n, int npad,
+    float* __restrict__ xp, float* __restrict__ yp, float* __restrict__ zp, const float* __restrict__ r_obs,
+    const float* __restrict__ alpha_in, int m, AlphaParams ap, int sort, float* __restrict__ alpha_f,
+    float* __restrict__ alpha_out, uint32_t* __restrict__ keys, uint32_t* __restrict__ perm,
+    const float* __restrict__ d1sq, uint32_t* __restrict__ count, uint32_t* __restrict__ list) {
+  constexpr int kWaves = kPrologueThreads / 64, kCols = kPrologueItems * kWaves, kCls = kMaxIntPow + 1;
+  constexpr int kPer = (kCls * kCols + 63) / 64;
+  __shared__ int s_at[kPer * 64];  // queries of class c before wavefront w's item u: [c][u * kWaves + w]
+  __shared__ uint32_t s_count;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (blockIdx.x > 0) {
+    const int i = ((int)blockIdx.x - 1) * kPrologueThreads + tid;
+    if (i >= npad) return;
+    const bool in = i < n;
+    xp[i] = in ? x[i] : 0.0f;
+    yp[i] = in ? y[i] : 0.0f;
+    zp[i] = in ? z[i] : 0.0f;
+    return;
+  }
+  if (tid == 0) s_count = 0u;
+  for (int i = tid; i < kPer * 64; i += kPrologueThreads) s_at[i] = 0;
+  __syncthreads();
+  int key[kPrologueItems];
+#pragma unroll
+  for (int u = 0; u < kPrologueItems; ++u) {
+    const int i = u * kPrologueThreads + tid;
+    key[u] = -1;
+    if (i < m) {
+      if (d1sq[i] == 0.0f) list[atomicAdd(&s_count, 1u)] = (uint32_t)i;
+      float af;
+      if (alpha_in) {
+        af = alpha_in[i];
+        key[u] = af >= 1.0f && af <= (float)kMaxIntPow && af == floorf(af) ? (int)af : 0;
+      } else {
+        const double R = (double)r_obs[i] / alpha_r_exp(ap);                           // Eq. 4
+        const double alpha = level_alpha(fuzzy_mu(R, ap.r_min, ap.r_max), ap.levels);  // Eq. 5, 6
+        af = (float)alpha;
+        alpha_f[i] = af;
+        key[u] = (int)alpha_class(alpha);
+      }
+      if (alpha_out) alpha_out[i] = af;
+      if (!sort) {
+        keys[i] = (uint32_t)key[u];
+        perm[i] = (uint32_t)i;
+      }
+    }
+    if (sort)
+      for (int c = 0; c < kCls; ++c) {
+        const int cnt = (int)__popcll(__ballot(key[u] == c));
+        if (lane == 0) s_at[c * kCols + u * kWaves + w] = cnt;
+      }
+  }
+  __syncthreads();
+  if (tid == 0) *count = s_count;
+  if (!sort) return;
+  if (w == 0) {  // the exclusive sums, in the order of the classes
+    int sum = 0;
+    for (int k = 0; k < kPer; ++k) sum += s_at[lane * kPer + k];
+    int before = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(before, o, 64);
+      if (lane >= o) before += t;
+    }
+    before -= sum;
+    for (int k = 0; k < kPer; ++k) {
+      const int v = s_at[lane * kPer + k];
+      s_at[lane * kPer + k] = before;
+      before += v;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kPrologueItems; ++u)
+    for (int c = 0; c < kCls; ++c) {
+      const uint64_t same = __ballot(key[u] == c);
+      if (key[u] == c) {
+        const int at = s_at[c * kCols + u * kWaves + w] + (int)__popcll(same & ((1ull << lane) - 1ull));
+        keys[at] = (uint32_t)c;
+        perm[at] = (uint32_t)(u * kPrologueThreads + tid);
+      }
+    }
+}
+
 // One block: the Q * kThreads queries at positions pos0 ... of the class order (slot (j,
 // thread) -> position -> query perm[position]) against the data range of split blockIdx.y,
 // with the power-POW weight (POW = 0: general alpha).
@@ -327,6 +418,18 @@ hipError_t launch_alpha_class(const float* r_obs, int m, const AlphaParams& ap, 
   if (m <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_alpha_class, dim3((m + 255) / 256), dim3(256), 0, s, r_obs, m, ap, alpha_f, alpha_out, keys,
                      vals, d1sq, count, list);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_prologue(const float* x, const float* y, const float* z, int n, float* xp, float* yp, float* zp,
+                                 const float* r_obs, const float* alpha_in, int m, const AlphaParams& ap, bool sort,
+                                 float* alpha_f, float* alpha_out, uint32_t* keys, uint32_t* perm, const float* d1sq,
+                                 uint32_t* count, uint32_t* list, hipStream_t s) {
+  if (m > kSmallQueries) return hipErrorInvalidValue;
+  const int npad = interp_padded_len(n);
+  hipLaunchKernelGGL(k_small_prologue, dim3(1 + (npad + kPrologueThreads - 1) / kPrologueThreads), dim3(kPrologueThreads),
+                     0, s, x, y, z, n, npad, xp, yp, zp, r_obs, alpha_in, m, ap, sort ? 1 : 0, alpha_f, alpha_out, keys,
+                     perm, d1sq, count, list);
   return hipGetLastError();
 }
 
