@@ -482,8 +482,8 @@ void choose_interp_config(int64_t n, int64_t m, int* q, int* split) {
   // lone wavefront takes 45 ns a point (1000 points, 257 queries: 45 -> 9 us; 4096 x 4096: 88 -> 9 us), the
   // less finely the more workgroups there are, as the partials cost more then: us of aidw_interpolate
   // with 1 | 2 | 4 | 8 | 16 splits, 2000 x 9000: 197 | 160 | 138 | 127 | 122; 700 x 50,000: 142 | 133 | 130 |
-  // 132 | 132; 300 x 100,000: 126 | 131 | 130; 700 x 300,000: 172 | 175 | 172; 4000 x 300,000: 433 | 410 | 385 |
-  // 376 | 378.
+  // 132 | 132; 300 x 100,000: 126 | 131 | 130; 4000 x 150,000: 328 | 280 | 268 | 257 | 255; 700 x 300,000:
+  // 172 | 175 | 172; 4000 x 300,000: 433 | 410 | 385 | 376 | 378.
   const int qq = g_cfg_q ? g_cfg_q : 1;
   int sp = 1;
   if (g_cfg_split) {
@@ -491,9 +491,10 @@ void choose_interp_config(int64_t n, int64_t m, int* q, int* split) {
   } else {
     const int64_t max_by_mem = ((int64_t)1 << 26) / (m > 0 ? m : 1);
     const int64_t blocks = (m + 256 * qq - 1) / (256 * qq);
-    while (sp < 256 && (int64_t)sp * 2 <= max_by_mem &&
-           n / ((int64_t)sp * 2) >= (blocks * sp < 256 ? 64 : blocks * sp < 1024 ? 256 : blocks * sp < 8192 ? 512 : 2048))
-      sp *= 2;
+    auto least = [&](int64_t groups) {  // points of a range
+      return groups < 256 ? 64 : groups < 4096 && blocks < 1024 ? 256 : groups < 8192 ? 512 : 2048;
+    };
+    while (sp < 256 && (int64_t)sp * 2 <= max_by_mem && n / ((int64_t)sp * 2) >= least(blocks * sp)) sp *= 2;
   }
   if (g_split_cap > 0)
     while (sp > g_split_cap) sp >>= 1;
