@@ -564,15 +564,18 @@ uint32_t integer_levels(const aidw_params* p) {
 
 // Whether Eq. 1 is summed hierarchically (tree.hip): with the built-in launch shape, levels that the
 // expansion's error bounds cover, and enough pairs to pay for the moments and the query order.
-// The direct sums cost n m / 5.2e12 s; the hierarchical ones about 0.25 ms at the smallest sizes,
-// plus 1.2 us per 1000 data points (moments; uneven data cost most) and 0.6-3 us per 1000 queries
-// (4096 x 465,649 in a mixture: 0.94 ms against 0.87 with every pair evaluated).
+// The direct sums cost n m / 5.2e12 s; the hierarchical ones 0.25 ms at the least, plus the moments (1.2 us
+// per 1000 data points where these are uneven, which also makes few queries' groups wide) and 0.3-1 us per
+// 1000 queries.  Whole runs in us, every pair / hierarchical, uniform | 8-component mixture:
+//   8192 x 200,000:  542/483 | 593/625    32,768 x 32,768: 418/335 | 437/469    700,001 x 5003: 990/839 | 1051/1569
+//   8192 x 400,000:  869/563 | 958/741    32,768 x 50,000: 540/372 | 567/525    2^20 x 8192:   2226/866 | 2317/2182
+//   4096 x 500,000:  639/590 | 714/781    131,072 x 16,384: 674/373 | 704/597   262,144 x 8192: 700/482 | 737/930
 bool tree_pays(int64_t n, int64_t m, const aidw_params* p) {
   if (g_cfg_q || g_cfg_split || !g_cfg_intpow || g_arena) return false;
   for (int i = 0; i < 5; ++i)
     if (p->alpha[i] > 8.0) return false;
   return n >= 4096 && m >= 64 && n <= (1 << 28) && m <= (1 << 28) &&
-         (double)n * (double)m >= 1.5e9 + 6000.0 * (double)n + 900.0 * (double)m;
+         (double)n * (double)m >= 1.25e9 + 6500.0 * (double)n + 1650.0 * (double)m;
 }
 
 // Eq. 1 by hierarchical summation.  points: the grid of exactly these data points (a run's own);
