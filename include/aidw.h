@@ -5,7 +5,7 @@
  * The method has two stages (Section 3.1, Fig. 1):
  *   stage 1  bin the data points into an even grid (Section 4.1.1-4.1.3) and
  *            find, for every interpolated ("query") point, its k nearest data
- *            points by searching rings of cells outward (Section 3.2.4, 4.1.4);
+ *            points by searching the cells around it outward (Section 3.2.4, 4.1.4);
  *            r_obs = mean of the k distances (Eq. 3);
  *   stage 2  R = r_obs / r_exp (Eq. 2, 4), mu = fuzzy membership of R (Eq. 5),
  *            alpha = triangular membership of mu over five levels (Eq. 6), and
@@ -152,7 +152,7 @@ void aidw_grid_destroy(aidw_grid* g);
  * of (squared distance, data index) -- ties go to the smaller index, so the
  * neighbour set is unique.  Squared distances are formed in float64 from the
  * float32 inputs (exact for coordinates on a 2^-20 lattice in [0, 1)).
- * The search visits rings of cells around the query's cell and stops only when
+ * The search visits blocks of cells around the query's cell and stops only when
  * the block searched so far provably contains the k nearest points (the
  * paper's "one more level" rule, the Remark in Section 3.2.4, is not always
  * sufficient and is not used).  The queries are binned to cells first so that
@@ -331,7 +331,7 @@ aidw_status aidw_set_interp_config(int32_t q, int32_t split, int32_t integer_pow
  * of 256 binned queries, the cells within two of theirs (when they fit 2048
  * points) in LDS and reads the candidates of those cells from there.  Both give
  * the same index sets, r_obs and d1^2 bit for bit; the choice applies to query
- * sets of 2^17 or more (smaller ones take the four-lanes-per-query kernel).
+ * sets of 2^17 or more (smaller ones take several lanes per query).
  * Errors: AIDW_EINVAL for any other value.
  */
 aidw_status aidw_set_knn_config(int32_t lds_window);
