@@ -3,8 +3,8 @@
 // cell-ordered arrays and need no further sort.
 //
 // Steps: k_tree_plan (geometry), k_tree_gather (z in cell order), k_tree_p2m (moments of the
-// leaves and of the level above, from the points), k_tree_m2m (each further level from the one
-// below), the queries ordered along the Hilbert curve, k_tree_eval (the sums).
+// leaves and of the level above, from the points), k_tree_up (each further level from the one below,
+// and the squares inside dense leaves), the queries ordered along the Hilbert curve, k_tree_eval (the sums).
 #include <float.h>
 #include <math.h>
 
