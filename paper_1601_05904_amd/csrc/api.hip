@@ -173,12 +173,24 @@ hipError_t dmalloc_async(void** p, size_t bytes, hipStream_t s) {
   {
     std::lock_guard<std::mutex> lock(g_cache_mu);
     auto& cache = block_cache();
-    int best = -1;
-    for (int i = 0; i < (int)cache.size(); ++i) {
-      const CachedBlock& b = cache[i];
-      if (b.busy || b.device != dev || b.bytes < want || b.bytes > 2 * want) continue;
-      if (best < 0 || b.bytes < cache[best].bytes || (b.bytes == cache[best].bytes && b.stream == s))
-        best = i;
+    auto smallest = [&](size_t limit, bool own) {
+      int best = -1;
+      for (int i = 0; i < (int)cache.size(); ++i) {
+        const CachedBlock& b = cache[i];
+        if (b.busy || b.device != dev || b.bytes < want || b.bytes > limit || (own && b.stream != s)) continue;
+        if (best < 0 || b.bytes < cache[best].bytes || (b.bytes == cache[best].bytes && b.stream == s)) best = i;
+      }
+      return best;
+    };
+    int best = smallest(2 * want, false);
+    // While s is captured nothing can be allocated and no other stream waited for.  The smallest of the
+    // stream's own blocks that suffices, however large, then always leaves enough for the requests
+    // that an earlier call of the same sizes met.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if ((best < 0 || cache[best].stream != s) && hipStreamIsCapturing(s, &capture) == hipSuccess &&
+        capture != hipStreamCaptureStatusNone) {
+      const int own = smallest(~(size_t)0, true);
+      if (own >= 0) best = own;
     }
     if (best >= 0) {
       CachedBlock& b = cache[best];

@@ -53,3 +53,49 @@ def test_ranges_of_few_queries(n, m):
     for a, b in ((got, whole), (alone, whole_alone)):
         assert bool(torch.isfinite(a).all())
         assert float(((a - b).abs() / b.abs()).max()) <= 2e-5
+
+
+@pytest.mark.parametrize("n,m", [(1000, 300), (4096, 4096), (300, 100000), (40961, 50009), (65536, 65536),
+                                 (20000, 150000), (333333, 100000)])
+def test_captured_after_one_call(n, m):
+    """aidw_interpolate captured into a graph right after its first call on a stream, with no other
+    memory cached, and replayed after the field has changed."""
+    import ctypes
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1601_05904_amd as aidw
+    lib = aidw.load(build_if_missing=False)
+    rng = np.random.default_rng(n + m)
+    x, y, z = (torch.from_numpy(a).cuda() for a in rng.random((3, n)).astype(np.float32))
+    qx, qy = (torch.from_numpy(a).cuda() for a in rng.random((2, m)).astype(np.float32))
+    grid = aidw.build_grid(x, y, qx, qy, aidw.Params(k=10))
+    r_obs, d1, _ = aidw.knn(grid, qx, qy, 10)
+    p = aidw.Params(k=10, area=grid.describe()["area"])._c()
+    grid.close()
+    aidw.release_cached_memory()
+    qz = torch.empty(m, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+
+    def call():
+        assert lib.aidw_interpolate(x.data_ptr(), y.data_ptr(), z.data_ptr(), n, qx.data_ptr(), qy.data_ptr(), m,
+                                    r_obs.data_ptr(), d1.data_ptr(), ctypes.byref(p), None, qz.data_ptr(), None,
+                                    side.cuda_stream) == aidw.OK
+
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call()
+    for _ in range(3):
+        z.mul_(1.5).add_(0.125)
+        torch.cuda.synchronize()
+        qz.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = qz.clone()
+        call()
+        torch.cuda.synchronize()
+        assert torch.equal(got, qz)
