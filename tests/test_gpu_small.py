@@ -99,3 +99,43 @@ def test_captured_after_one_call(n, m):
         call()
         torch.cuda.synchronize()
         assert torch.equal(got, qz)
+
+
+@pytest.mark.parametrize("occupancy", [0.6, 2.0, 40.0])
+@pytest.mark.parametrize("kind", ["uniform", "lattice", "piles", "one_place"])
+@pytest.mark.parametrize("n,m", [(1, 3), (10, 1), (1000, 257), (1024, 7168), (4096, 4096), (8000, 192), (8191, 1)])
+def test_small_grid_matches_the_large_build(n, m, kind, occupancy):
+    """The one-workgroup build against the banded one: the same data with the queries repeated until they
+    are too many for it must give the same arrays, and every query the same neighbours."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1601_05904_amd as aidw
+    aidw.load(build_if_missing=False)
+    rng = np.random.default_rng(n + m)
+    p, q = rng.random((n, 2)), rng.random((m, 2))
+    if kind == "lattice":
+        p = np.floor(p * 64) / 64
+    elif kind == "piles":  # a few cells with hundreds of points
+        p[: n * 3 // 4] = 0.3 + 1e-4 * p[: n * 3 // 4]
+    elif kind == "one_place":
+        p[:] = 0.5
+    x, y, qx, qy = (torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda() for a in
+                    (p[:, 0], p[:, 1], q[:, 0], q[:, 1]))
+    z = torch.rand(n, device="cuda") + 0.5
+    k = min(n, 10)
+    prm = aidw.Params(k=k, occupancy=occupancy, area=1.0)
+    times = 8193 // m + 1
+    many = [a.repeat(times) for a in (qx, qy)]
+    got, want = [], []
+    for out, qs in ((got, (qx, qy)), (want, many)):
+        grid = aidw.build_grid(x, y, *qs, prm)
+        out.append(grid.describe())
+        out.extend(t.clone() for t in grid.arrays())
+        grid.close()
+    assert got[0] == want[0]
+    for a, b in zip(got[1:], want[1:]):
+        assert torch.equal(a, b)
+    r = aidw.run(x, y, z, qx, qy, prm, want_alpha=True, want_robs=True)
+    r_many = aidw.run(x, y, z, *many, prm, want_alpha=True, want_robs=True)
+    assert torch.equal(r[1], r_many[1][:m]) and torch.equal(r[2], r_many[2][:m])
