@@ -599,7 +599,8 @@ bool grid_without_host(int64_t n, hipStream_t s) {
 }
 
 // Eq. 1 by hierarchical summation.  points: the grid of exactly these data points (a run's own);
-// null: a grid is built here.  AIDW_ENOMEM only before anything that writes an output is queued.
+// null: a grid is built here.  AIDW_ENOMEM (no memory, or no grid of these points) only before anything
+// that writes an output is queued: every pair is evaluated then.
 aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t n, const float* qx, const float* qy,
                         int64_t m, const float* r_obs, const float* d1sq, const aidw_params* p, const aidw_grid* g,
                         float* qz, float* alpha_out, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end, int* used_q,
@@ -612,7 +613,7 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
     aidw_params gp;
     aidw_params_default(&gp);
     aidw_status st = build_grid_impl(x, y, n, nullptr, nullptr, 0, &gp, s, true, &own, &t, nullptr, false);
-    if (st != AIDW_OK) return st;
+    if (st != AIDW_OK) return AIDW_ENOMEM;  // no grid (points on a line, for one): not what the caller asked for
     points = own;
   }
   aidw_status st = [&]() -> aidw_status {
@@ -707,7 +708,7 @@ aidw_status interp_impl(const float* x, const float* y, const float* z, int64_t 
     const aidw_status st = interp_tree(x, y, z, n, qx, qy, m, r_obs, d1sq, p, g, qz, alpha_out, s, ev_begin, ev_end,
                                        used_q, used_split, alpha_in, points, ap);
     if (st != AIDW_ENOMEM) return st;
-    g_detail.clear();  // no room for the moments: every pair is evaluated
+    g_detail.clear();  // no room for the moments, or no grid: every pair is evaluated
   }
   int q, split;
   choose_interp_config(n, m, &q, &split);

@@ -309,3 +309,26 @@ def test_batch_jobs(T, size):
         assert T.equal(a.nan_to_num(7.0), b.nan_to_num(7.0))
     for p in (plan, direct):
         p.close()
+
+
+@pytest.mark.parametrize("n,m", [(60000, 60000), (4300001, 9000)])
+def test_points_on_a_line(T, n, m):
+    """aidw_interpolate alone needs no area of the data's own: points on a line, which no grid spans, on both
+    sides of the size from which the grid it builds is sized by the host."""
+    aidw = aidw_mod()
+    g = T.Generator(device="cuda").manual_seed(n)
+    x = T.rand(n, generator=g, device="cuda")
+    z = T.rand(n, generator=g, device="cuda") + 0.5
+    qx, qy = T.rand(m, generator=g, device="cuda"), T.rand(m, generator=g, device="cuda")
+    y = T.full_like(x, 0.25)
+    d1 = (qy - 0.25) ** 2 + 1e-9
+    r_obs = T.full_like(qx, 0.01)
+    p = aidw.Params(k=10, area=1.0)
+    got = aidw.interpolate(x, y, z, qx, qy, r_obs, d1, p)
+    aidw.set_interp_config(1, 0, -1)
+    try:
+        want = aidw.interpolate(x, y, z, qx, qy, r_obs, d1, p)
+    finally:
+        aidw.set_interp_config(0, 0, -1)
+    assert bool(T.isfinite(got).all())
+    assert float(((got - want).abs() / want.abs()).max()) <= 2 * MAX_TOL
