@@ -129,6 +129,17 @@ __global__ void k_tree_plan(Jobs jobs, uint32_t* __restrict__ zero_word) {
   p.bs = bs;
   // an opened square's coordinates have 14 bits on the stack
   p.fine = p.nx[0] <= kMaxSide / 2 && p.ny[0] <= kMaxSide / 2 ? min(bs, kFine) : 0;
+  // how far points lie from the centres (Plan::widen)
+  const float far = fmaxf(fmaxf(fabsf(g.minx), fabsf(g.maxx)), fmaxf(fabsf(g.miny), fabsf(g.maxy))) + 2.0f * (float)p.h[0];
+  const float spacing = __builtin_amdgcn_ldexpf(1.0f, __builtin_amdgcn_frexp_expf(far) - 24);
+  const float cells = __builtin_amdgcn_ldexpf(1.0f, bs);  // of a leaf's side
+  const float off0 = (spacing * g.inv_cw + 2.0f * (float)slack_cells(g.ncol, g.nrow)) / cells;
+  if (!(off0 <= kCoarse)) p.bad = 1;
+  auto finest = [&]() { return __builtin_amdgcn_ldexpf(off0, p.fine); };
+  while (p.fine > 0 && !(finest() <= 0.125f * kCoarse)) --p.fine;
+  p.widen = __builtin_amdgcn_logf(1.0f + off0);
+  p.widen_fine = __builtin_amdgcn_logf(1.0f + finest());
+  p.rim = __builtin_amdgcn_logf(1.0f + (1.0f + finest()) * (float)M_SQRT1_2 / (1.5f - finest()));
   for (int d = 0; d < kFine; ++d) p.pool[d] = node_cap + d * 4 * refine_capacity(n);
   *job.plan = p;
 }
@@ -932,7 +943,9 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
   const bool mixed = __any(whole) && __any(alpha != a0);
   const int pw = uniform(whole && !mixed ? (int)alpha : 0);
   const float sc = pair::pow2_scale(d1);
-  Query L{fx * sc, fy * sc, -sc, -0.5f * alpha, 0.0f, 0.0f, 0.0, 0.0, 0.0f, exp2f(-kLogRim * alpha)};
+  // (read beside the group's first loads: read where they are used, 10^5 uniform points take 12 % longer)
+  const float rim = plan->rim, widen = plan->widen, widen_fine = plan->widen_fine;
+  Query L{fx * sc, fy * sc, -sc, -0.5f * alpha, 0.0f, 0.0f, 0.0, 0.0, 0.0f, exp2f(-rim * alpha)};
   const int bs = plan->bs, ncol = plan->ncol, nrow = plan->nrow, levels = plan->levels, fine = plan->fine;
   // squares per side at a level, from the cells: a load of each would be waited for level by level
   auto squares = [&](int cells, int l) { return (int)(((int64_t)cells + (1ll << (bs + l)) - 1) >> (bs + l)); };
@@ -1041,8 +1054,8 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
     const float qx0 = wave_min(in ? fx : INFINITY), qx1 = wave_max(in ? fx : -INFINITY);
     const float qy0 = wave_min(in ? fy : INFINITY), qy1 = wave_max(in ? fy : -INFINITY);
     const float amin = wave_min(counts ? alpha : INFINITY), amax = wave_max(counts ? alpha : 0.0f);
-    // a square's share of a query's sums is at most (1 + rho)^alpha, rho < 0.4715
-    const float lcap = amax * kLogRim;
+    // a square's share of a query's sums is at most (1 + rho)^alpha
+    const float lcap = amax * rim;
     for (int l0 = -dep; l0 < levels; ++l0) {
       const float h0 = (float)plan->h[max(l0, 0)] * __uint_as_float((uint32_t)(127 + min(l0, 0)) << 23);
       // log2 of the largest weight per unit of a query's sums, for a square at distance h0
@@ -1112,7 +1125,8 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
         const float lr = 0.5f * __builtin_amdgcn_logf(__builtin_fmaf(ex, ex, ey * ey));  // log2 of the distance
         float lq = fmaxf(__builtin_amdgcn_logf(cnt) + kden, __builtin_amdgcn_logf(hd.y) + kabs) - amin * (lr - ld);
         lq = fminf(lq, lcap);
-        const float lrho = ld - 0.5f - lr - (float)(l0 - lvl);  // rho = (h / sqrt 2) / distance
+        // rho = (1 + e) (h / sqrt 2) / distance
+        const float lrho = ld - 0.5f + (lvl < 0 ? widen_fine : widen) - lr - (float)(l0 - lvl);
         int tier = kTiers;
 #pragma unroll
         for (int i = kTiers - 1; i >= 0; --i)

@@ -24,7 +24,7 @@ namespace tree {
 constexpr int kOrder = 16;               // highest order of the moments
 constexpr int kTiers = kOrder / 2;       // orders 2, 4, ..., kOrder are the evaluation's choices
 constexpr int kNear = 1;                 // squares within kNear of the query's are opened
-constexpr float kLogRim = 0.5574f;        // log2(1 + rho) at the largest rho = sqrt(1/2) / 1.5
+constexpr float kCoarse = 1.0f;           // largest e of Plan::widen in leaves, 1/8 of it below them
 constexpr int kLeafPoints = 32;          // wanted mean points per leaf
 constexpr int kTopSide = 8;              // squares per side at which no further level is built
 constexpr int kLevels = 14;
@@ -76,6 +76,12 @@ struct Plan {
   float minx, miny, inv;
   int32_t nx[kLevels], ny[kLevels], off[kLevels];  // squares per row / column, first record
   double h[kLevels];                               // side
+  // A centre is a float32 number, so it is off by up to half of float32's spacing at the coordinates,
+  // and a point may lie past its square's side by the slack of its cell: a point's offset is up to
+  // (1 + e) h / sqrt 2, e = (spacing + 2 slack) / h.  widen = log2(1 + e) of the leaves, widen_fine of the
+  // smallest squares; rim = log2(1 + rho) at the largest rho of a square that is not near, with e of the
+  // smallest squares (1 + e) sqrt(1/2) / (1.5 - e).
+  float widen, widen_fine, rim;
   int32_t fine, pool[kFine];                       // levels below the leaves, each one's first record
   uint32_t refined[kFine];                         // squares above with four in the pool
 };

@@ -1,0 +1,82 @@
+"""The edges of the hierarchical summation of Eq. 1: where its bounds need more than the ordinary case,
+where it hands a job back to the pair kernel, and what a call does there.  Eq. 1 in float64 over all pairs
+is the reference.
+
+Bar: the library's stated 1e-5 in the normwise relative metric, and 1e-6 where the summation is on: the
+truncation estimate of a square is 2^-22 = 2.4e-7 of a query's sums, and an integer weight rsq(t)^5 carries
+up to 5 roundings of rsq's 1.2e-7."""
+import numpy as np
+import pytest
+
+from paper_1601_05904_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+MAX_TOL, TREE_TOL = 1e-5, 1e-6
+
+
+@pytest.fixture(scope="module")
+def T():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1601_05904_amd as aidw
+    aidw.load(build_if_missing=False)
+    return torch
+
+
+def aidw_mod():
+    import paper_1601_05904_amd as aidw
+    return aidw
+
+
+def dev(T, *arrays):
+    return [T.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to("cuda") for a in arrays]
+
+
+def every_pair(f):
+    """f with every pair evaluated, in the pair kernel's own launch shape."""
+    aidw = aidw_mod()
+    aidw.set_interp_config(1, 0, -1)
+    try:
+        return f()
+    finally:
+        aidw.set_interp_config(0, 0, -1)
+
+
+def error(T, qz, x, y, z, qx, qy, alpha, sample=384):
+    """Largest error of sampled queries against Eq. 1 in float64 with the given alpha."""
+    rng = np.random.default_rng(5)
+    sel = T.from_numpy(np.sort(rng.choice(len(qx), size=min(sample, len(qx)), replace=False))).to("cuda")
+    worst = 0.0
+    for i in range(0, len(sel), 16):
+        s = sel[i:i + 16]
+        d2 = (qx[s].double()[:, None] - x.double()) ** 2 + (qy[s].double()[:, None] - y.double()) ** 2
+        d1 = d2.min(1, keepdim=True).values
+        w = T.exp(T.log(d2 / T.where(d1 > 0, d1, T.ones_like(d1))) * (-0.5 * alpha[s].double()[:, None]))
+        w = T.where(d1 == 0, (d2 == 0).double(), w)
+        den = w.sum(1)
+        ref, norm = (w * z.double()).sum(1) / den, (w * z.double().abs()).sum(1) / den
+        worst = max(worst, float(((qz[s].double() - ref).abs() / T.maximum(ref.abs(), norm)).max()))
+    return worst
+
+
+@pytest.mark.parametrize("level", [None, 5.0, 7.5])
+@pytest.mark.parametrize("offset,extent", [(5e6, 25.0), (5e6, 30.0), (120.0, 3.8e-4), (5e6, 50.0), (5e6, 100.0), (5e6, 200.0),
+                                           (5e6, 400.0)])
+def test_coarse_coordinates(T, offset, extent, level):
+    """Coordinates whose float32 spacing is 0.9 to 0.05 of a leaf's side: a square's centre is rounded to
+    them too, and its points lie that much farther from it."""
+    aidw = aidw_mod()
+    rng = np.random.default_rng(0)
+    spacing = float(np.spacing(np.float32(offset)))
+    side = int(extent / spacing)
+    sites = rng.permutation(side * side)
+    data, free = sites[:int(0.4 * side * side)], sites[int(0.4 * side * side):]
+    i, j = data[rng.integers(0, len(data), 60000)], free[rng.integers(0, len(free), 40000)]
+    z = np.sin(18.0 * (i % side) / side) + np.cos(10.0 * (i // side) / side) + rng.normal(0, 0.3, 60000)
+    d = dev(T, offset + spacing * (i % side), offset + spacing * (i // side), z, offset + spacing * (j % side),
+            offset + spacing * (j // side))
+    p = aidw.Params(k=10, levels=(1, 2, 3, 4, 5) if level is None else (level,) * 5)
+    qz, alpha, _ = aidw.run(*d, p, want_alpha=True)
+    assert error(T, qz, *d, alpha) <= TREE_TOL
