@@ -1049,11 +1049,11 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
         }
       __syncthreads();
     }
-    // a coincident query's sums are replaced by the fix-up: it asks for no accuracy
-    const bool counts = in && d1 > 0.0f;
+    // (a coincident query has infinite sums, which the fix-up replaces: it asks for no accuracy; one whose
+    // d1sq is 0 without a data point at its place keeps its sums)
     const float qx0 = wave_min(in ? fx : INFINITY), qx1 = wave_max(in ? fx : -INFINITY);
     const float qy0 = wave_min(in ? fy : INFINITY), qy1 = wave_max(in ? fy : -INFINITY);
-    const float amin = wave_min(counts ? alpha : INFINITY), amax = wave_max(counts ? alpha : 0.0f);
+    const float amin = wave_min(in ? alpha : INFINITY), amax = wave_max(in ? alpha : 0.0f);
     // a square's share of a query's sums is at most (1 + rho)^alpha
     const float lcap = amax * rim;
     for (int l0 = -dep; l0 < levels; ++l0) {
@@ -1061,10 +1061,10 @@ __global__ __launch_bounds__(512, 4) void k_tree_eval(Jobs jobs, int njobs, cons
       // log2 of the largest weight per unit of a query's sums, for a square at distance h0
       const float ld = log2f(h0);
       const float lw = alpha * (ld + log2f(sc));
-      const float rden = counts ? __builtin_amdgcn_rcpf((float)(base_den + L.den)) : 0.0f;
-      const float rabs = counts ? __builtin_amdgcn_rcpf(base_abs + L.sabs) : 0.0f;
-      const float kden = wave_max(counts ? __builtin_amdgcn_logf(rden) - lw : -INFINITY);
-      const float kabs = wave_max(counts ? __builtin_amdgcn_logf(rabs) - lw : -INFINITY);
+      const float rden = in ? __builtin_amdgcn_rcpf((float)(base_den + L.den)) : 0.0f;
+      const float rabs = in ? __builtin_amdgcn_rcpf(base_abs + L.sabs) : 0.0f;
+      const float kden = wave_max(in ? __builtin_amdgcn_logf(rden) - lw : -INFINITY);
+      const float kabs = wave_max(in ? __builtin_amdgcn_logf(rabs) - lw : -INFINITY);
       const int nx = squares(ncol, l0), ny = squares(nrow, l0), up = l0 + dep;
       const int ax0 = max(0, (x0 >> up) - kNear), ax1 = min(nx - 1, (x1 >> up) + kNear);
       const int ay0 = max(0, (y0 >> up) - kNear), ay1 = min(ny - 1, (y1 >> up) + kNear);

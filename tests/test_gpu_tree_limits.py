@@ -80,3 +80,21 @@ def test_coarse_coordinates(T, offset, extent, level):
     p = aidw.Params(k=10, levels=(1, 2, 3, 4, 5) if level is None else (level,) * 5)
     qz, alpha, _ = aidw.run(*d, p, want_alpha=True)
     assert error(T, qz, *d, alpha) <= TREE_TOL
+
+
+@pytest.mark.parametrize("level", [None, 2.0])
+def test_zero_d1sq_without_a_point(T, level):
+    """A query whose d1sq is 0 where no data point is at its place keeps its sums, so they are as exact as
+    any: all queries so, and every third."""
+    aidw = aidw_mod()
+    ds = W.make(50000, 45000, 10, 840, "uniform", 8)
+    x, y, z, qx, qy = dev(T, ds.x, ds.y, ds.z, ds.qx, ds.qy)
+    grid = aidw.build_grid(x, y, qx, qy, aidw.Params(k=10))
+    r, d1, _ = aidw.knn(grid, qx, qy, 10)
+    p = aidw.Params(k=10, area=grid.describe()["area"], levels=(1, 2, 3, 4, 5) if level is None else (level,) * 5)
+    grid.close()
+    for step in (1, 3):
+        d0 = d1.clone()
+        d0[::step] = 0.0
+        qz, alpha = aidw.interpolate(x, y, z, qx, qy, r, d0, p, want_alpha=True)
+        assert error(T, qz, x, y, z, qx, qy, alpha) <= MAX_TOL
