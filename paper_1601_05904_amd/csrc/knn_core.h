@@ -234,8 +234,10 @@ __device__ __forceinline__ void nearest(const View& g, const int32_t* __restrict
                                         const float* __restrict__ sx, const float* __restrict__ sy,
                                         const int32_t* __restrict__ sidx, float fx, float fy, int k, double slack_cells,
                                         double (&bk)[KMAX], int32_t (&bi)[KMAX], int sub = 0) {
-  // a coordinate that is no number is at no distance: the list keeps its +inf
-  const double px = fx == fx ? (double)fx : (double)INFINITY, py = fy == fy ? (double)fy : (double)INFINITY;
+  // a coordinate that is no number is at no distance: the list keeps its +inf, and its indices (an
+  // insertion by comparison rejects a NaN, one by minimum and maximum would take it)
+  const double px = IDX || fx == fx ? (double)fx : (double)INFINITY;
+  const double py = IDX || fy == fy ? (double)fy : (double)INFINITY;
   const int ncol = g.ncol, nrow = g.nrow;
   const int c0 = clamp_cell((fx - g.minx) * g.inv, ncol);
   const int r0 = clamp_cell((fy - g.miny) * g.inv, nrow);

@@ -52,3 +52,25 @@ def test_matches_brute_force(kind, k):
             if idx:
                 assert torch.equal(ix, want[2][:m]), m
     grid.close()
+
+
+@pytest.mark.parametrize("m", [1000, 40000, 200000])
+def test_queries_that_are_no_numbers(m):
+    """A query with a NaN coordinate has no neighbours: the brute-force kNN's infinite distance and unset
+    indices, whatever the number of lanes per query."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1601_05904_amd as aidw
+    aidw.load(build_if_missing=False)
+    rng = np.random.default_rng(m)
+    x, y = (torch.from_numpy(a).cuda() for a in rng.random((2, 5000)).astype(np.float32))
+    q = rng.random((2, m)).astype(np.float32)
+    q[0, 5] = q[1, 77] = q[0, m - 1] = q[1, m - 1] = np.nan
+    qx, qy = (torch.from_numpy(a).cuda() for a in q)
+    grid = aidw.build_grid(x, y, x, y, aidw.Params(k=10))
+    want = aidw.knn_bruteforce(x, y, qx, qy, 10, want_idx=True)
+    for got in (aidw.knn(grid, qx, qy, 10, want_idx=True), aidw.knn(grid, qx, qy, 10)):
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        assert got[2] is None or torch.equal(got[2], want[2])
+    grid.close()
