@@ -235,7 +235,7 @@ hipError_t launch_nn_statistic(const float* r_obs, int m, double r_exp, double c
 // x, y, z are the padded copies made by launch_pad_copy.
 // gs (may be null): a grid whose failed status makes the launch do nothing.
 // fallback (may be null): the plan of a hierarchical summation; the launch then only works where
-// that plan is off.
+// that plan is off, with q = 1.
 hipError_t launch_interp(const float* x, const float* y, const float* z, int n, const float* qx, const float* qy,
                          const float* alpha_f, const float* d1sq, const uint32_t* perm, const uint32_t* skeys, int m,
                          uint32_t fast_mask, int q, int split, float* qz, double2* partial, const GridScalars* gs,
@@ -270,8 +270,10 @@ void fill_job(Job* j, int64_t n, const double* levels);
 // *zero_word (may be null) is cleared on the way.
 hipError_t launch_tree_build(const tree::Job& job, const float* sx, const float* sy, const int32_t* sidx,
                              const float* z, float* tx, float* ty, float* tz, uint32_t* zero_word, hipStream_t s);
-// Sort keys: the queries' places along the Hilbert curve over 2^hbits x 2^hbits tiles.
+// Sort keys: the queries' places along the Hilbert curve over 2^hbits x 2^hbits tiles.  Where the plan is
+// off the keys stay as they are, and tx, ty, tz become the padded points in their own order, for the pair kernel.
 hipError_t launch_tree_keys(const tree::Plan* plan, const float* qx, const float* qy, int m, int hbits, uint32_t* keys,
+                            const float* x, const float* y, const float* z, int n, float* tx, float* ty, float* tz,
                             hipStream_t s);
 // qz of every query from the squares, the queries in the order perm.  Does nothing where the plan is off.
 hipError_t launch_tree_eval(const tree::Job& job, const float* tx, const float* ty, const float* tz, const float* qx,

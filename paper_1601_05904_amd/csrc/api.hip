@@ -619,14 +619,18 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
   aidw_status st = [&]() -> aidw_status {
     const int hbits = tree::hilbert_bits(n);
     const int npad = tree::padded_points(n);
-    // the direct sums where the plan turns out to be off: enough ranges to fill the chip
-    int split = 1;
-    const int64_t blocks = (m + 255) / 256;
-    while (blocks * split < 4096 && split < 256 && n / (2 * split) >= 2048) split *= 2;
+    // The direct sums where the plan turns out to be off: in the pair kernel's own ranges, whose partials
+    // take the place of the moments, as far as they fit it or kOffPartials.
+    constexpr size_t kOffPartials = (size_t)256 << 20;
+    const size_t moments = tree::node_bytes(n);
+    int q, split;
+    choose_interp_config(n, m, &q, &split);
+    const size_t room = moments > kOffPartials ? moments : kOffPartials;
+    while (split > 1 && sizeof(double2) * (size_t)split * (size_t)m > room) split >>= 1;
+    const size_t partials = split > 1 ? sizeof(double2) * (size_t)split * (size_t)m : 0;
     uint32_t *count, *list, *keys, *perm, *tk, *tv, *hist, *scan;
-    float *alpha_f, *tx, *ty, *tz, *nodes;
-    char* plan_mem;
-    double2* partial = nullptr;
+    float *alpha_f, *tx, *ty, *tz;
+    char *plan_mem, *nodes;
     hipError_t e;
     if ((e = t.get(&count, 1)) != hipSuccess || (e = t.get(&list, m)) != hipSuccess ||
         (e = t.get(&alpha_f, m)) != hipSuccess || (e = t.get(&keys, m)) != hipSuccess ||
@@ -635,17 +639,17 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
         (e = t.get(&scan, radix_scan_tmp_words((int)m))) != hipSuccess || (e = t.get(&tx, npad)) != hipSuccess ||
         (e = t.get(&ty, npad)) != hipSuccess || (e = t.get(&tz, npad)) != hipSuccess ||
         (e = t.get(&plan_mem, tree::plan_bytes())) != hipSuccess ||
-        (e = t.get(&nodes, tree::node_bytes(n) / sizeof(float))) != hipSuccess ||
-        (split > 1 && (e = t.get(&partial, (size_t)split * m)) != hipSuccess))
+        (e = t.get(&nodes, moments > partials ? moments : partials)) != hipSuccess)
       return hip_fail(e, "allocating summation buffers");
     tree::Plan* plan = reinterpret_cast<tree::Plan*>(plan_mem);
+    double2* partial = partials ? reinterpret_cast<double2*>(nodes) : nullptr;
     if (ev_begin) HIP_TRY(hipEventRecord(ev_begin, s), "event");
     tree::Job job{};
     tree::fill_job(&job, n, p->alpha);
     job.gs = points->dev;
     job.plan = plan;
     job.cell_start = points->cell_start;
-    job.nodes = nodes;
+    job.nodes = reinterpret_cast<float*>(nodes);
     job.m = (int32_t)m;
     HIP_TRY(launch_tree_build(job, points->sx, points->sy, points->sidx, z, tx, ty, tz, count, s), "moments");
     const float* alpha_use = alpha_f;
@@ -658,15 +662,14 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
       HIP_TRY(launch_alpha_class(r_obs, (int)m, ap, alpha_f, alpha_out, keys, perm, d1sq, count, list, s),
               "alpha kernel");
     }
-    HIP_TRY(launch_tree_keys(plan, qx, qy, (int)m, hbits, keys, s), "query keys");
+    HIP_TRY(launch_tree_keys(plan, qx, qy, (int)m, hbits, keys, x, y, z, (int)n, tx, ty, tz, s), "query keys");
     uint32_t *skeys = keys, *sperm = perm;
     HIP_TRY(radix_sort_pairs_to(keys, perm, tk, tv, (int)m, 2 * hbits, hist, scan, s, &skeys, &sperm),
             "query sort");
     HIP_TRY(launch_tree_eval(job, tx, ty, tz, qx, qy, alpha_use, d1sq, sperm, qz, s), "hierarchical summation");
     const GridScalars* status = own ? nullptr : points->dev;
-    // skeys are no class keys here: every block takes the general form
-    HIP_TRY(launch_interp(tx, ty, tz, (int)n, qx, qy, alpha_use, d1sq, sperm, skeys, (int)m, 0, 1, split, qz, partial,
-                          status, s, plan),
+    HIP_TRY(launch_interp(tx, ty, tz, (int)n, qx, qy, alpha_use, d1sq, sperm, skeys, (int)m, integer_levels(p), 1, split,
+                          qz, partial, status, s, plan),
             "interpolation kernel");
     if (ev_end) HIP_TRY(hipEventRecord(ev_end, s), "event");
     const Partials parts{partial, split, (int)m, plan};

@@ -185,17 +185,16 @@ __global__ __launch_bounds__(kPrologueThreads) void k_small_prologue(
 }
 
 // One block: the Q * kThreads queries at positions pos0 ... of the class order (slot (j,
-// thread) -> position -> query perm[position]) against the data range of split blockIdx.y,
+// thread) -> position -> query perm[position]) against the data range `split` of `splits`,
 // with the power-POW weight (POW = 0: general alpha).
 template <int Q, int POW>
 __device__ __forceinline__ void interp_block(const float* __restrict__ x, const float* __restrict__ y,
                                              const float* __restrict__ z, int n, int chunk,
                                              const float* __restrict__ qx, const float* __restrict__ qy,
                                              const float* __restrict__ alpha_f, const float* __restrict__ d1sq,
-                                             const uint32_t* __restrict__ perm, int m, int pos0,
-                                             float* __restrict__ qz, double2* __restrict__ partial) {
+                                             const uint32_t* __restrict__ perm, int m, int pos0, int split,
+                                             int splits, float* __restrict__ qz, double2* __restrict__ partial) {
   Lane<Q, POW> L;
-  const int split = blockIdx.y;
   uint32_t qid[Q];
 #pragma unroll
   for (int j = 0; j < Q; ++j) {
@@ -217,38 +216,30 @@ __device__ __forceinline__ void interp_block(const float* __restrict__ x, const 
     if (qid[j] == 0xffffffffu) continue;
     const double num = L.num(j);
     const double den = L.den(j);
-    if (gridDim.y == 1)
+    if (splits == 1)
       qz[qid[j]] = (float)(num / den);
     else
       partial[(size_t)split * m + qid[j]] = make_double2(num, den);
   }
 }
 
-// The pair kernel, one launch for every alpha class: a block whose queries all have the
-// integer class p (fast_mask bit p set) runs the power-p loop, any other block (general
-// alpha, or a block that spans two classes) the general loop.  Class 0 sorts first, so the
-// costlier general blocks are dispatched first.
+// A block of any alpha class: one whose queries all have the integer class p (fast_mask bit p set)
+// takes the power-p loop, any other (general alpha, or a block that spans two classes) the general one.
 template <int Q>
-__global__ __launch_bounds__(kThreads) void k_interp(const float* __restrict__ x, const float* __restrict__ y,
-                                                     const float* __restrict__ z, int n, int chunk,
-                                                     const float* __restrict__ qx, const float* __restrict__ qy,
-                                                     const float* __restrict__ alpha_f,
-                                                     const float* __restrict__ d1sq,
-                                                     const uint32_t* __restrict__ perm,
-                                                     const uint32_t* __restrict__ skeys, int m, uint32_t fast_mask,
-                                                     float* __restrict__ qz, double2* __restrict__ partial,
-                                                     const GridScalars* __restrict__ gs,
-                                                     const tree::Plan* __restrict__ fallback) {
-  if (fallback && !tree::off(fallback)) return;  // summed hierarchically
-  if (gs && gs->status != AIDW_OK) return;  // a failed grid build: no result to compute
-  const int pos0 = blockIdx.x * kThreads * Q;
+__device__ __forceinline__ void interp_class(const float* __restrict__ x, const float* __restrict__ y,
+                                             const float* __restrict__ z, int n, int chunk,
+                                             const float* __restrict__ qx, const float* __restrict__ qy,
+                                             const float* __restrict__ alpha_f, const float* __restrict__ d1sq,
+                                             const uint32_t* __restrict__ perm, const uint32_t* __restrict__ skeys,
+                                             int m, uint32_t fast_mask, int pos0, int split, int splits,
+                                             float* __restrict__ qz, double2* __restrict__ partial) {
   const int posl = min(m, pos0 + kThreads * Q) - 1;
   const uint32_t k0 = skeys[pos0], kl = skeys[posl];
   const uint32_t cls = (k0 == kl && ((fast_mask >> k0) & 1u)) ? k0 : 0u;
   switch (cls) {
-#define AIDW_CASE(P)                                                                                        \
-  case P:                                                                                                   \
-    interp_block<Q, P>(x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, m, pos0, qz, partial);               \
+#define AIDW_CASE(P)                                                                                              \
+  case P:                                                                                                         \
+    interp_block<Q, P>(x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, m, pos0, split, splits, qz, partial);     \
     break;
     AIDW_CASE(1)
     AIDW_CASE(2)
@@ -260,7 +251,48 @@ __global__ __launch_bounds__(kThreads) void k_interp(const float* __restrict__ x
     AIDW_CASE(8)
 #undef AIDW_CASE
     default:
-      interp_block<Q, 0>(x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, m, pos0, qz, partial);
+      interp_block<Q, 0>(x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, m, pos0, split, splits, qz, partial);
+  }
+}
+
+// The pair kernel, one launch for every alpha class.  Class 0 sorts first, so the costlier general
+// blocks are dispatched first.
+template <int Q>
+__global__ __launch_bounds__(kThreads) void k_interp(const float* __restrict__ x, const float* __restrict__ y,
+                                                     const float* __restrict__ z, int n, int chunk,
+                                                     const float* __restrict__ qx, const float* __restrict__ qy,
+                                                     const float* __restrict__ alpha_f,
+                                                     const float* __restrict__ d1sq,
+                                                     const uint32_t* __restrict__ perm,
+                                                     const uint32_t* __restrict__ skeys, int m, uint32_t fast_mask,
+                                                     float* __restrict__ qz, double2* __restrict__ partial,
+                                                     const GridScalars* __restrict__ gs) {
+  if (gs && gs->status != AIDW_OK) return;  // a failed grid build: no result to compute
+  interp_class<Q>(x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, blockIdx.x * kThreads * Q,
+                  blockIdx.y, gridDim.y, qz, partial);
+}
+
+// The same where a hierarchical summation may turn out off: a launch of fixed size whose workgroups go
+// through the blocks and ranges, and end at once where it is on.
+constexpr int kOffGroups = 2048;
+__global__ __launch_bounds__(kThreads) void k_interp_off(const float* __restrict__ x, const float* __restrict__ y,
+                                                         const float* __restrict__ z, int n, int chunk,
+                                                         const float* __restrict__ qx, const float* __restrict__ qy,
+                                                         const float* __restrict__ alpha_f,
+                                                         const float* __restrict__ d1sq,
+                                                         const uint32_t* __restrict__ perm,
+                                                         const uint32_t* __restrict__ skeys, int m, uint32_t fast_mask,
+                                                         int splits, float* __restrict__ qz,
+                                                         double2* __restrict__ partial,
+                                                         const GridScalars* __restrict__ gs,
+                                                         const tree::Plan* __restrict__ plan) {
+  if (!tree::off(plan)) return;  // summed hierarchically
+  if (gs && gs->status != AIDW_OK) return;
+  const int blocks = (m + kThreads - 1) / kThreads;
+  for (int64_t i = blockIdx.x; i < (int64_t)blocks * splits; i += gridDim.x) {
+    const int split = (int)(i / blocks);
+    interp_class<1>(x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask,
+                    (int)(i - (int64_t)split * blocks) * kThreads, split, splits, qz, partial);
   }
 }
 
@@ -452,9 +484,9 @@ template <int Q>
 hipError_t launch_q(dim3 grid, hipStream_t s, const float* x, const float* y, const float* z, int n, int chunk,
                     const float* qx, const float* qy, const float* alpha_f, const float* d1sq, const uint32_t* perm,
                     const uint32_t* skeys, int m, uint32_t mask, float* qz, double2* partial,
-                    const GridScalars* gs, const tree::Plan* fallback) {
+                    const GridScalars* gs) {
   hipLaunchKernelGGL((k_interp<Q>), grid, dim3(kThreads), 0, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys,
-                     m, mask, qz, partial, gs, fallback);
+                     m, mask, qz, partial, gs);
   return hipGetLastError();
 }
 
@@ -467,13 +499,19 @@ hipError_t launch_interp(const float* x, const float* y, const float* z, int n, 
   if (m <= 0) return hipSuccess;
   int chunk = (n + split - 1) / split;
   chunk = (chunk + kChunk - 1) / kChunk * kChunk;
-  const dim3 grid((m + kThreads * q - 1) / (kThreads * q), split);
   fast_mask &= ((1u << (kMaxIntPow + 1)) - 2u);
+  if (fallback) {
+    if (q != 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_interp_off, dim3(kOffGroups), dim3(kThreads), 0, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq,
+                       perm, skeys, m, fast_mask, split, qz, partial, gs, fallback);
+    return hipGetLastError();
+  }
+  const dim3 grid((m + kThreads * q - 1) / (kThreads * q), split);
   switch (q) {
-    case 1: return launch_q<1>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs, fallback);
-    case 2: return launch_q<2>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs, fallback);
-    case 4: return launch_q<4>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs, fallback);
-    case 8: return launch_q<8>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs, fallback);
+    case 1: return launch_q<1>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs);
+    case 2: return launch_q<2>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs);
+    case 4: return launch_q<4>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs);
+    case 8: return launch_q<8>(grid, s, x, y, z, n, chunk, qx, qy, alpha_f, d1sq, perm, skeys, m, fast_mask, qz, partial, gs);
     default: return hipErrorInvalidValue;
   }
 }

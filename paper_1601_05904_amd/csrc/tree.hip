@@ -580,12 +580,26 @@ __global__ __launch_bounds__(256, 5) void k_tree_up(Jobs jobs, int lvl, int dept
 // The query order: the Hilbert index of the query's tile.  (Ordering by alpha class inside stretches
 // of the curve gives more groups of one class, whose weights are cheaper, but wider ones: 2^20 uniform
 // 2.10 ms in plain order, 2.33 ms with stretches of 1024 queries.)
+// Where the plan is off the pair kernel takes over, with the keys as they are (the alpha classes) and the
+// points in their own order.
 __global__ __launch_bounds__(256) void k_tree_keys(const Plan* __restrict__ plan, const float* __restrict__ qx,
                                                    const float* __restrict__ qy, int m, int hbits,
-                                                   uint32_t* __restrict__ keys) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= m) return;
-  keys[q] = tile(plan, hbits, qx[q], qy[q]);
+                                                   uint32_t* __restrict__ keys, const float* __restrict__ x,
+                                                   const float* __restrict__ y, const float* __restrict__ z, int n,
+                                                   int npad, float* __restrict__ tx, float* __restrict__ ty,
+                                                   float* __restrict__ tz) {
+  const int stride = gridDim.x * blockDim.x;
+  int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (!off(plan)) {
+    if (i < m) keys[i] = tile(plan, hbits, qx[i], qy[i]);
+    return;
+  }
+  for (; i < npad; i += stride) {
+    const bool in = i < n;
+    tx[i] = in ? x[i] : 0.0f;
+    ty[i] = in ? y[i] : 0.0f;
+    tz[i] = in ? z[i] : 0.0f;
+  }
 }
 
 // ---------------------------------------------------------------- evaluation
@@ -1313,8 +1327,10 @@ hipError_t launch_tree_batch(const tree::Job* jobs, int njobs, int64_t max_n, in
 }
 
 hipError_t launch_tree_keys(const tree::Plan* plan, const float* qx, const float* qy, int m, int hbits, uint32_t* keys,
+                            const float* x, const float* y, const float* z, int n, float* tx, float* ty, float* tz,
                             hipStream_t s) {
-  hipLaunchKernelGGL(k_tree_keys, dim3(div_up(m, 256)), dim3(256), 0, s, plan, qx, qy, m, hbits, keys);
+  hipLaunchKernelGGL(k_tree_keys, dim3(div_up(m, 256)), dim3(256), 0, s, plan, qx, qy, m, hbits, keys, x, y, z, n,
+                     tree::padded_points(n), tx, ty, tz);
   return hipGetLastError();
 }
 

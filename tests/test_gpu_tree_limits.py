@@ -98,3 +98,32 @@ def test_zero_d1sq_without_a_point(T, level):
         d0[::step] = 0.0
         qz, alpha = aidw.interpolate(x, y, z, qx, qy, r, d0, p, want_alpha=True)
         assert error(T, qz, x, y, z, qx, qy, alpha) <= MAX_TOL
+
+
+@pytest.mark.parametrize("levels", [(1, 2, 3, 4, 5), (0.5, 1.25, 2.5, 3.5, 7.5)])
+@pytest.mark.parametrize("case", ["on", "nan", "huge", "dense", "line"])
+def test_off_is_the_pair_kernel(T, case, levels):
+    """Where the summation turns out off (z beyond its range, a leaf of very many points, points that no grid
+    spans) the sums are the pair kernel's, bit for bit; elsewhere they are its own."""
+    aidw = aidw_mod()
+    rng = np.random.default_rng(7)
+    ds = W.make(50000, 40000, 10, 850, "uniform", 8)
+    x, y, z, q = ds.x.copy(), ds.y.copy(), ds.z.copy(), (ds.qx, ds.qy)
+    if case == "nan":
+        z[17] = np.nan
+    elif case == "huge":
+        z *= np.float32(1e33)
+    elif case == "dense":
+        x[:30000], y[:30000] = W.quantise(0.5 + 1e-4 * rng.random((2, 30000)))
+    elif case == "line":
+        x[:] = 0.25
+    x, y, z, qx, qy = dev(T, x, y, z, *q)
+    p = aidw.Params(k=10, area=1.0, levels=levels)
+    grid = aidw.build_grid(x, y, qx, qy, p)
+    r, d1, _ = aidw.knn(grid, qx, qy, 10)
+    grid.close()
+    calls = [lambda: aidw.interpolate(x, y, z, qx, qy, r, d1, p)]
+    if case != "line":
+        calls.append(lambda: aidw.run(x, y, z, qx, qy, p))
+    for f in calls:
+        assert T.equal(f().nan_to_num(7.0), every_pair(f).nan_to_num(7.0)) == (case != "on")
