@@ -337,11 +337,15 @@ __global__ __launch_bounds__(256, 5) void k_tree_p2m(Jobs jobs, const float* __r
   __shared__ PointSums s_sum[4];
   __shared__ double s_abs[4];
   __shared__ int s_cnt[4];
+  __shared__ int s_off;
   const Job& job = jobs[blockIdx.y];
   Plan* const plan = job.plan;
   const int32_t* __restrict__ cell_start = job.cell_start;
   float* __restrict__ nodes = job.nodes;
-  if (plan->bad) return;
+  // other workgroups of this launch may turn the plan off: one thread asks for all
+  if (threadIdx.x == 0) s_off = *(volatile const int32_t*)&plan->bad;
+  __syncthreads();
+  if (s_off) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const bool two = plan->levels > 1;
   const int nx1 = two ? plan->nx[1] : (plan->nx[0] + 1) >> 1, ny1 = two ? plan->ny[1] : (plan->ny[0] + 1) >> 1;
