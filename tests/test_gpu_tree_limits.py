@@ -127,3 +127,32 @@ def test_off_is_the_pair_kernel(T, case, levels):
         calls.append(lambda: aidw.run(x, y, z, qx, qy, p))
     for f in calls:
         assert T.equal(f().nan_to_num(7.0), every_pair(f).nan_to_num(7.0)) == (case != "on")
+
+
+def test_far_outlier_costs_little(T):
+    """One far outlier puts all other points into one cell, whose leaf is refused before it is summed (32
+    times every pair's time otherwise; the grid of one cell is most of the rest)."""
+    aidw = aidw_mod()
+    ds = W.make(1 << 18, 16384, 10, 851, "uniform", 8)
+    x, y, z, qx, qy = dev(T, ds.x, ds.y, ds.z, ds.qx, ds.qy)
+    grid = aidw.build_grid(x, y, qx, qy, aidw.Params(k=10))
+    r, d1, _ = aidw.knn(grid, qx, qy, 10)
+    p = aidw.Params(k=10, area=grid.describe()["area"])
+    grid.close()
+    x[0] = y[0] = 1000.0
+
+    def fastest(f):
+        f()
+        times = []
+        for _ in range(5):
+            a, b = T.cuda.Event(enable_timing=True), T.cuda.Event(enable_timing=True)
+            a.record()
+            f()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    call = lambda: aidw.interpolate(x, y, z, qx, qy, r, d1, p)  # noqa: E731
+    assert T.equal(call(), every_pair(call))
+    assert fastest(call) <= 6.0 * every_pair(lambda: fastest(call))
