@@ -239,7 +239,7 @@ hipError_t launch_nn_statistic(const float* r_obs, int m, double r_exp, double c
 hipError_t launch_interp(const float* x, const float* y, const float* z, int n, const float* qx, const float* qy,
                          const float* alpha_f, const float* d1sq, const uint32_t* perm, const uint32_t* skeys, int m,
                          uint32_t fast_mask, int q, int split, float* qz, double2* partial, const GridScalars* gs,
-                         hipStream_t s, const tree::Plan* fallback = nullptr);
+                         hipStream_t s, tree::Plan* fallback = nullptr);
 // The untiled pair kernel (per-lane global loads, general alpha form, one data range).
 hipError_t launch_interp_naive(const float* x, const float* y, const float* z, int n, const float* qx, const float* qy,
                                const float* alpha_f, const float* d1sq, int m, float* qz, hipStream_t s);

@@ -84,6 +84,7 @@ struct Plan {
   float widen, widen_fine, rim;
   int32_t fine, pool[kFine];                       // levels below the leaves, each one's first record
   uint32_t refined[kFine];                         // squares above with four in the pool
+  uint32_t next;                                   // where it is off: the pair kernel's next item
 };
 
 // Squares of more than kRefine points that n points can make at one level.
