@@ -156,3 +156,20 @@ def test_far_outlier_costs_little(T):
     call = lambda: aidw.interpolate(x, y, z, qx, qy, r, d1, p)  # noqa: E731
     assert T.equal(call(), every_pair(call))
     assert fastest(call) <= 6.0 * every_pair(lambda: fastest(call))
+
+
+@pytest.mark.parametrize("n", [8200, 16385, 70001])
+def test_grid_of_one_full_cell(T, n):
+    """The cell that holds all points but one outlier lists them by index."""
+    aidw = aidw_mod()
+    rng = np.random.default_rng(n)
+    p = rng.random((2, n)).astype(np.float32)
+    p[:, n // 3] = 1000.0
+    x, y = dev(T, *p)
+    grid = aidw.build_grid(x, y, params=aidw.Params(k=10))
+    cell_start, sx, sy, sidx = grid.arrays()
+    grid.close()
+    assert int(cell_start[1]) == n - 1
+    want = T.cat([T.arange(n // 3), T.arange(n // 3 + 1, n), T.tensor([n // 3])]).to("cuda")
+    assert T.equal(sidx.long(), want)
+    assert T.equal(sx, x[want]) and T.equal(sy, y[want])
