@@ -590,14 +590,6 @@ bool tree_pays(int64_t n, int64_t m, const aidw_params* p) {
          (double)n * (double)m >= 1.25e9 + 6500.0 * (double)n + 1650.0 * (double)m;
 }
 
-// Whether interp_tree can build its grid here: beyond the banded build the host waits for the grid's
-// scalars, which a stream that is being captured does not allow.
-bool grid_without_host(int64_t n, hipStream_t s) {
-  if (occupancy_budget(n, 2.0) <= kBandMaxCells) return true;
-  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(s, &status) == hipSuccess && status == hipStreamCaptureStatusNone;
-}
-
 // Eq. 1 by hierarchical summation.  points: the grid of exactly these data points (a run's own);
 // null: a grid is built here.  AIDW_ENOMEM (no memory, or no grid of these points) only before anything
 // that writes an output is queued: every pair is evaluated then.
@@ -612,6 +604,9 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
   if (!points) {
     aidw_params gp;
     aidw_params_default(&gp);
+    // Within the banded build's cells: beyond them the host would wait for the grid's scalars.  2, 8 and 32
+    // points a cell make leaves of 32 (9,000,000 x 9000 points: 5.1 ms with the host waiting, 4.3 so, 5.9 with 4.5 a cell).
+    while (occupancy_budget(n, gp.occupancy) > kBandMaxCells) gp.occupancy *= gp.occupancy < 32.0 ? 4.0 : 1.0625;
     aidw_status st = build_grid_impl(x, y, n, nullptr, nullptr, 0, &gp, s, true, &own, &t, nullptr, false);
     if (st != AIDW_OK) return AIDW_ENOMEM;  // no grid (points on a line, for one): not what the caller asked for
     points = own;
@@ -707,7 +702,7 @@ aidw_status interp_impl(const float* x, const float* y, const float* z, int64_t 
   ap.r_min = p->r_min;
   ap.r_max = p->r_max;
   for (int i = 0; i < 5; ++i) ap.levels[i] = p->alpha[i];
-  if (!naive && tree_pays(n, m, p) && (points || grid_without_host(n, s))) {
+  if (!naive && tree_pays(n, m, p)) {
     const aidw_status st = interp_tree(x, y, z, n, qx, qy, m, r_obs, d1sq, p, g, qz, alpha_out, s, ev_begin, ev_end,
                                        used_q, used_split, alpha_in, points, ap);
     if (st != AIDW_ENOMEM) return st;

@@ -173,3 +173,29 @@ def test_grid_of_one_full_cell(T, n):
     want = T.cat([T.arange(n // 3), T.arange(n // 3 + 1, n), T.tensor([n // 3])]).to("cuda")
     assert T.equal(sidx.long(), want)
     assert T.equal(sx, x[want]) and T.equal(sy, y[want])
+
+
+@pytest.mark.parametrize("n", [4170001, 4300001, 9000001])
+def test_interpolate_does_not_wait(T, n):
+    """aidw_interpolate returns while earlier work of its stream is pending, whatever the size of the grid it
+    builds for itself, and sums as exactly with it."""
+    aidw = aidw_mod()
+    m = 9000
+    g = T.Generator(device="cuda").manual_seed(n)
+    x, y, z = (T.rand(n, generator=g, device="cuda") for _ in range(3))
+    qx, qy = (T.rand(m, generator=g, device="cuda") for _ in range(2))
+    r = T.full_like(qx, 0.5 / n ** 0.5)
+    d1 = T.full_like(qx, 0.1 / n)
+    p = aidw.Params(k=10, area=1.0)
+    qz, alpha = aidw.interpolate(x, y, z, qx, qy, r, d1, p, want_alpha=True)  # (its memory is cached from here on)
+    assert error(T, qz, x, y, z, qx, qy, alpha, 64) <= MAX_TOL
+    a = T.randn(8192, 8192, device="cuda")
+    T.cuda.synchronize()
+    done = T.cuda.Event()
+    for _ in range(40):  # about 0.4 s
+        a @ a
+    done.record()
+    again = aidw.interpolate(x, y, z, qx, qy, r, d1, p)
+    assert not done.query()
+    T.cuda.synchronize()
+    assert T.equal(again, qz)
