@@ -76,17 +76,28 @@ aidw_status hip_fail(hipError_t e, const char* what) {
   return fail(AIDW_EDEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
-// Test hook: AIDW_FAULT=alloc makes every device allocation fail (host-forced ENOMEM).
+// Test hook: AIDW_FAULT=alloc makes every device allocation fail (host-forced ENOMEM), AIDW_FAULT=alloc:BYTES
+// those of more than BYTES, by a request that the runtime refuses.
 bool fault_alloc() {
   const char* f = getenv("AIDW_FAULT");
   return f && strcmp(f, "alloc") == 0;
+}
+
+// hipMalloc; its failure does not stay behind as the runtime's last error, which the next launch's check
+// would take for its own when the caller goes on without the memory.
+hipError_t device_malloc(void** p, size_t bytes) {
+  const char* f = getenv("AIDW_FAULT");
+  if (f && strncmp(f, "alloc:", 6) == 0 && bytes > strtoull(f + 6, nullptr, 10)) bytes = (size_t)1 << 50;
+  const hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
 }
 
 hipError_t dmalloc(void** p, size_t bytes) {
   *p = nullptr;
   if (g_arena) return arena_take(p, bytes);
   if (fault_alloc()) return hipErrorOutOfMemory;
-  return hipMalloc(p, bytes ? bytes : 1);
+  return device_malloc(p, bytes ? bytes : 1);
 }
 
 // Temporaries of a call come from a cache of device blocks that outlives the call:
@@ -207,7 +218,7 @@ hipError_t dmalloc_async(void** p, size_t bytes, hipStream_t s) {
   nb.device = dev;
   nb.stream = s;
   nb.busy = true;
-  if ((e = hipMalloc(&nb.p, want)) != hipSuccess) return e;
+  if ((e = device_malloc(&nb.p, want)) != hipSuccess) return e;
   std::lock_guard<std::mutex> lock(g_cache_mu);
   block_cache().push_back(nb);
   *p = nb.p;

@@ -44,6 +44,15 @@ def every_pair(f):
         aidw.set_interp_config(0, 0, -1)
 
 
+@pytest.fixture
+def small_allocations(T, monkeypatch):
+    """Allocations of more than 64 MiB fail; nothing is cached."""
+    aidw_mod().release_cached_memory()
+    monkeypatch.setenv("AIDW_FAULT", "alloc:%d" % (64 << 20))
+    yield
+    monkeypatch.delenv("AIDW_FAULT")
+
+
 def error(T, qz, x, y, z, qx, qy, alpha, sample=384):
     """Largest error of sampled queries against Eq. 1 in float64 with the given alpha."""
     rng = np.random.default_rng(5)
@@ -199,3 +208,13 @@ def test_interpolate_does_not_wait(T, n):
     assert not done.query()
     T.cuda.synchronize()
     assert T.equal(again, qz)
+
+
+def test_no_room_for_the_moments(T, small_allocations):
+    """Without memory for the moments every pair is evaluated, in the same call and in the next."""
+    aidw = aidw_mod()
+    ds = W.make(1 << 20, 8192, 10, 852, "uniform", 8)
+    d = dev(T, ds.x, ds.y, ds.z, ds.qx, ds.qy)
+    p = aidw.Params(k=10)
+    for _ in range(2):
+        assert T.equal(aidw.run(*d, p), every_pair(lambda: aidw.run(*d, p)))
