@@ -554,8 +554,9 @@ aidw_status aidw_batch_describe(const aidw_batch* b, aidw_batch_desc* out);
  * enabled (a timed run is launched directly, not through the graph). */
 typedef struct {
   float grid_ms;    /* gather, bounds, grid scalars, counting sort, CSR     */
-  float knn_ms;     /* query binning, kNN + Eq. 3, Eq. 4-6, class ordering  */
-  float interp_ms;  /* the persistent pair kernel of Eq. 1                  */
+  float knn_ms;     /* query binning, kNN + Eq. 3, Eq. 4-6, class ordering
+                       (the last two in interp_ms where jobs are summed hierarchically) */
+  float interp_ms;  /* the hierarchical sums and the persistent pair kernel of Eq. 1 */
   float finish_ms;  /* combine, coincident-query fix-up, outputs            */
 } aidw_batch_timing;
 

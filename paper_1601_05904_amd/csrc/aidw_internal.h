@@ -280,13 +280,14 @@ hipError_t launch_tree_eval(const tree::Job& job, const float* tx, const float* 
                             const float* qy, const float* alpha_f, const float* d1sq, const uint32_t* perm, float* qz,
                             hipStream_t s);
 // The same for njobs jobs at once (jobs: device array, group0 ascending): the plans, then, with tz in
-// place, the moments and the float64 (num, den) of every query whose plan is not off.  max_n, max_levels:
+// place, the moments, then the float64 (num, den) of every query whose plan is not off.  max_n, max_levels:
 // the largest of the jobs; groups: of all jobs.
 hipError_t launch_tree_plans(const tree::Job* jobs, int njobs, hipStream_t s);
-hipError_t launch_tree_batch(const tree::Job* jobs, int njobs, int64_t max_n, int max_levels, int groups,
-                             const float* tx, const float* ty, const float* tz, const float* qx, const float* qy,
-                             const float* alpha_f, const float* d1sq, const uint32_t* perm, double2* partial,
-                             hipStream_t s);
+hipError_t launch_tree_moments(const tree::Job* jobs, int njobs, int64_t max_n, int max_levels, const float* tx,
+                               const float* ty, const float* tz, hipStream_t s);
+hipError_t launch_tree_evals(const tree::Job* jobs, int njobs, int groups, const float* tx, const float* ty,
+                             const float* tz, const float* qx, const float* qy, const float* alpha_f, const float* d1sq,
+                             const uint32_t* perm, double2* partial, hipStream_t s);
 
 // The float64 (num, den) of split data ranges: partial[s * m + q].  With fallback, only where it is off.
 struct Partials {

@@ -320,8 +320,17 @@ __global__ __launch_bounds__(256) void k_b_alpha(const BatchJob* __restrict__ jo
   }
 }
 
-__global__ void k_b_reset(uint32_t* __restrict__ counter) {
-  if (threadIdx.x == 0) *counter = 0u;
+// counter[0]: the next work item; counter[1]: the items to be taken.  The hierarchically summed jobs' items are the
+// last ones, taken only where one of those jobs turned out off.
+__global__ __launch_bounds__(64) void k_b_reset(uint32_t* __restrict__ counter, const tree::Job* __restrict__ tjobs,
+                                                int ntree, int nplain, int nitems) {
+  bool any = false;
+  for (int t = threadIdx.x; t < ntree; t += 64) any |= tree::off(tjobs[t].plan);
+  any = __any(any);
+  if (threadIdx.x == 0) {
+    counter[0] = 0u;
+    counter[1] = (uint32_t)(any ? nitems : nplain);
+  }
 }
 
 // One work item for a block of queries: positions [pos0, posend) of the pair order.
@@ -357,13 +366,13 @@ __device__ __forceinline__ void b_item(int pos0, int posend, const uint32_t* __r
 // exit test on every round.
 template <int Q>
 __global__ __launch_bounds__(pair::kThreads) void k_b_interp(
-    const BatchJob* __restrict__ jobs, const WorkItem* __restrict__ items, int nitems,
-    uint32_t* __restrict__ counter, const GridScalars* __restrict__ gs, const float* __restrict__ xp,
+    const BatchJob* __restrict__ jobs, const WorkItem* __restrict__ items, uint32_t* __restrict__ counter, const GridScalars* __restrict__ gs, const float* __restrict__ xp,
     const float* __restrict__ yp, const float* __restrict__ zp, const float* __restrict__ cqx,
     const float* __restrict__ cqy, const float* __restrict__ alpha_f, const float* __restrict__ d1sq,
     const uint32_t* __restrict__ perm, const uint32_t* __restrict__ skeys, uint32_t fast_mask,
     const tree::Job* __restrict__ tjobs, double2* __restrict__ partial) {
   __shared__ int s_item;
+  const int nitems = (int)counter[1];
   for (;;) {
     if (threadIdx.x == 0) s_item = (int)atomicAdd(counter, 1u);
     __syncthreads();
@@ -380,7 +389,7 @@ __global__ __launch_bounds__(pair::kThreads) void k_b_interp(
     const int lo = w.split * J.chunk;
     const int hi = min(J.n, lo + J.chunk);
     uint32_t cls = 0;
-    if (fast_mask && J.tree < 0) {  // (a hierarchical job's keys hold tiles)
+    if (fast_mask) {
       const uint32_t k0 = skeys[pos0] & 15u, kl = skeys[posend - 1] & 15u;
       if (k0 == kl && ((J.intmask >> k0) & 1u)) cls = k0;
     }
@@ -417,7 +426,8 @@ __global__ __launch_bounds__(256) void k_b_finish(const BatchJob* __restrict__ j
                                                   const int32_t* __restrict__ sidx, const float* __restrict__ zp,
                                                   const float* __restrict__ cqx, const float* __restrict__ cqy,
                                                   const float* __restrict__ r_obs, const float* __restrict__ alpha_f,
-                                                  const float* __restrict__ d1sq) {
+                                                  const float* __restrict__ d1sq,
+                                                  const tree::Job* __restrict__ tjobs) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= sum_m) return;
   const int j = find_seg(qoff, njobs, q);
@@ -427,7 +437,9 @@ __global__ __launch_bounds__(256) void k_b_finish(const BatchJob* __restrict__ j
   float v = NAN, a = NAN, ro = NAN;
   if (G.status == AIDW_OK) {
     double num = 0.0, den = 0.0;
-    for (int s = 0; s < J.splits; ++s) {
+    // (a hierarchical job's sums are in the place of its first range)
+    const int splits = J.tree >= 0 && !tree::off(tjobs[J.tree].plan) ? 1 : J.splits;
+    for (int s = 0; s < splits; ++s) {
       const double2 p = partial[J.poff + (int64_t)s * J.m + i];
       num += p.x;
       den += p.y;
@@ -463,7 +475,7 @@ struct aidw_batch {
   aidw_batch_config cfg{};
   int kmax = 16;
   uint32_t fast_mask = 0;
-  int sum_n = 0, sum_npad = 0, sum_m = 0, sum_cap = 0, nbblocks = 0, nitems = 0, workers = 0;
+  int sum_n = 0, sum_npad = 0, sum_m = 0, sum_cap = 0, nbblocks = 0, nitems = 0, nplain = 0, workers = 0;
   int64_t sum_partial = 0;
   double sum_pairs = 0.0;
   int cell_bits = 0, class_bits = 0;
@@ -629,8 +641,7 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
       tj.push_back(t);
       tree_owner.push_back(j);
     }
-    // (a hierarchically summed job has one item per block of queries, for a plan that turns out off)
-    int64_t chunk = cfg.split_points > 0 && !tree_job ? std::min<int64_t>(cfg.split_points, a.n) : a.n;
+    int64_t chunk = cfg.split_points > 0 ? std::min<int64_t>(cfg.split_points, a.n) : a.n;
     chunk = (chunk + pair::kChunk - 1) / pair::kChunk * pair::kChunk;
     J.chunk = (int32_t)chunk;
     J.splits = (int32_t)((a.n + chunk - 1) / chunk);
@@ -660,7 +671,7 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   qoff[njobs] = (int32_t)sm;
   bstart[njobs] = (int32_t)sb;
 
-  // ---- work items, longest first ----
+  // ---- work items, longest first; those of hierarchically summed jobs, for a plan that turns out off, last ----
   std::vector<WorkItem> items;
   std::vector<int64_t> cost;
   for (int j = 0; j < njobs; ++j) {
@@ -678,7 +689,10 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   if (items.size() >= (size_t)INT32_MAX) return fail(AIDW_ECAPACITY, "too many work items");
   std::vector<int32_t> by_cost(items.size());
   for (size_t i = 0; i < by_cost.size(); ++i) by_cost[i] = (int32_t)i;
-  std::stable_sort(by_cost.begin(), by_cost.end(), [&](int32_t a, int32_t b) { return cost[a] > cost[b]; });
+  auto direct = [&](int32_t i) { return hj[items[i].job].tree < 0; };
+  std::stable_sort(by_cost.begin(), by_cost.end(), [&](int32_t a, int32_t b) {
+    return direct(a) != direct(b) ? direct(a) : cost[a] > cost[b];
+  });
   std::vector<WorkItem> sorted(items.size());
   for (size_t i = 0; i < by_cost.size(); ++i) sorted[i] = items[by_cost[i]];
 
@@ -700,6 +714,7 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   b->sum_cap = (int)scap;
   b->nbblocks = (int)sb;
   b->nitems = (int)sorted.size();
+  b->nplain = (int)std::count_if(by_cost.begin(), by_cost.end(), direct);
   b->sum_partial = spart;
   b->sum_pairs = pairs;
   b->cell_bits = bits_for(scap);
@@ -757,7 +772,7 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
     b->d1sq = carve<float>(base, off, std::max<int64_t>(sm, 1));
     b->alpha_f = carve<float>(base, off, std::max<int64_t>(sm, 1));
     b->partial = carve<double2>(base, off, std::max<int64_t>(spart, 1));
-    b->counter = carve<uint32_t>(base, off, 1);
+    b->counter = carve<uint32_t>(base, off, 2);
     if (!tj.empty()) {
       b->tjobs = carve<tree::Job>(base, off, tj.size());
       b->tplans = carve<char>(base, off, tree::plan_bytes() * tj.size());
@@ -832,7 +847,7 @@ void launch_b_knn(const aidw_batch* b, int t_begin, int t_end, hipStream_t s) {
 template <int Q>
 void launch_b_interp(const aidw_batch* b, hipStream_t s) {
   const uint32_t* perm = b->fast_mask || b->ntree ? b->cperm : nullptr;
-  hipLaunchKernelGGL(k_b_interp<Q>, dim3(b->workers), dim3(pair::kThreads), 0, s, b->jobs, b->items, b->nitems,
+  hipLaunchKernelGGL(k_b_interp<Q>, dim3(b->workers), dim3(pair::kThreads), 0, s, b->jobs, b->items,
                      b->counter, b->gs, b->xp, b->yp, b->zp, b->cqx, b->cqy, b->alpha_f, b->d1sq, perm, b->ckeys,
                      b->fast_mask, b->tjobs, b->partial);
 }
@@ -871,26 +886,30 @@ aidw_status enqueue(aidw_batch* b, hipStream_t s, bool timed) {
     }
     STEP(hipSuccess, "kNN search");
     if (b->ntree) {
+      // the moments come before the queries are ordered: they may turn a job's plan off
+      if (timed) STEP(hipEventRecord(b->ev[2], s), "recording an event");
       STEP(launch_tree_plans(b->tjobs, b->ntree, s), "plans");
       const int npad = b->sum_n + 16;
       hipLaunchKernelGGL(k_b_tree_z, dim3(div_up(npad, 256)), dim3(256), 0, s, b->jobs, b->noff, nj, b->sum_n, npad,
                          b->sidx, b->zp, b->sx, b->sy, b->tz, b->tjobs);
+      STEP(launch_tree_moments(b->tjobs, b->ntree, b->tree_n, b->tree_levels, b->sx, b->sy, b->tz, s), "moments");
     }
     const bool classes = b->fast_mask != 0 || b->ntree;
     hipLaunchKernelGGL(k_b_alpha, dim3(gm), dim3(256), 0, s, b->jobs, b->qoff, nj, b->sum_m, b->gs, b->r_obs,
-                       (int)(b->fast_mask != 0), b->low_bits, b->tjobs, b->hbits, b->cqx, b->cqy, b->alpha_f, classes ? b->ckeys : nullptr, classes ? b->cperm : nullptr);
+                       (int)(b->fast_mask != 0), b->low_bits, b->tjobs, b->hbits, b->cqx, b->cqy, b->alpha_f,
+                       classes ? b->ckeys : nullptr, classes ? b->cperm : nullptr);
     STEP(hipSuccess, "adaptive power");
     if (classes)
       STEP(radix_sort_pairs(b->ckeys, b->cperm, b->tkeys, b->tvals, b->sum_m, b->class_bits, b->hist, b->scan_tmp,
                             s),
            "ordering the queries by class");
-    if (timed) STEP(hipEventRecord(b->ev[2], s), "recording an event");
+    if (timed && !b->ntree) STEP(hipEventRecord(b->ev[2], s), "recording an event");
     // stage 2: the large jobs' hierarchical summation, then the persistent pair kernel
     if (b->ntree)
-      STEP(launch_tree_batch(b->tjobs, b->ntree, b->tree_n, b->tree_levels, b->tree_groups, b->sx, b->sy, b->tz, b->cqx,
-                             b->cqy, b->alpha_f, b->d1sq, b->cperm, b->partial, s),
+      STEP(launch_tree_evals(b->tjobs, b->ntree, b->tree_groups, b->sx, b->sy, b->tz, b->cqx, b->cqy, b->alpha_f,
+                             b->d1sq, b->cperm, b->partial, s),
            "hierarchical summation");
-    hipLaunchKernelGGL(k_b_reset, dim3(1), dim3(64), 0, s, b->counter);
+    hipLaunchKernelGGL(k_b_reset, dim3(1), dim3(64), 0, s, b->counter, b->tjobs, b->ntree, b->nplain, b->nitems);
     if (b->cfg.q == 1)
       launch_b_interp<1>(b, s);
     else
@@ -898,7 +917,8 @@ aidw_status enqueue(aidw_batch* b, hipStream_t s, bool timed) {
     STEP(hipSuccess, "pair kernel");
     if (timed) STEP(hipEventRecord(b->ev[3], s), "recording an event");
     hipLaunchKernelGGL(k_b_finish, dim3(gm), dim3(256), 0, s, b->jobs, b->qoff, nj, b->sum_m, b->gs, b->partial,
-                       b->cell_start, b->sx, b->sy, b->sidx, b->zp, b->cqx, b->cqy, b->r_obs, b->alpha_f, b->d1sq);
+                       b->cell_start, b->sx, b->sy, b->sidx, b->zp, b->cqx, b->cqy, b->r_obs, b->alpha_f, b->d1sq,
+                       b->tjobs);
     STEP(hipSuccess, "combine");
   } else if (timed) {
     STEP(hipEventRecord(b->ev[2], s), "recording an event");

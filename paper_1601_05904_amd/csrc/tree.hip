@@ -1323,11 +1323,15 @@ hipError_t launch_tree_plans(const tree::Job* jobs, int njobs, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_tree_batch(const tree::Job* jobs, int njobs, int64_t max_n, int max_levels, int groups,
-                             const float* tx, const float* ty, const float* tz, const float* qx, const float* qy,
-                             const float* alpha_f, const float* d1sq, const uint32_t* perm, double2* partial,
-                             hipStream_t s) {
+hipError_t launch_tree_moments(const tree::Job* jobs, int njobs, int64_t max_n, int max_levels, const float* tx,
+                               const float* ty, const float* tz, hipStream_t s) {
   launch_moments(ManyJobs{jobs}, njobs, max_n, max_levels, tx, ty, tz, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_tree_evals(const tree::Job* jobs, int njobs, int groups, const float* tx, const float* ty,
+                             const float* tz, const float* qx, const float* qy, const float* alpha_f, const float* d1sq,
+                             const uint32_t* perm, double2* partial, hipStream_t s) {
   launch_eval<ManyJobs, true>(ManyJobs{jobs}, njobs, groups, tx, ty, tz, qx, qy, alpha_f, d1sq, perm, nullptr, partial,
                               s);
   return hipGetLastError();
