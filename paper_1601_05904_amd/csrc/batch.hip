@@ -547,7 +547,10 @@ void destroy_plan(aidw_batch* b) {
   delete b;
 }
 
-aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_config* cfg_in, aidw_batch** out) {
+// moments: jobs may be summed hierarchically.  Where the workspace does not fit with their moments, the plan
+// is made without.
+aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_config* cfg_in, aidw_batch** out,
+                        bool moments = true) {
   if (!out) return fail(AIDW_EINVAL, "out is NULL");
   *out = nullptr;
   if (!jobs || njobs < 1) return fail(AIDW_EINVAL, "need at least one job");
@@ -593,7 +596,7 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   double saved = 0.0;
   for (int j = 0; j < njobs; ++j)
     if (tree_saves(jobs[j]) > 0.0) saved += tree_saves(jobs[j]) - kTreePoint * (double)jobs[j].n;
-  const bool use_tree = cfg.integer_powers && saved >= kTreeLaunches;
+  const bool use_tree = moments && cfg.integer_powers && saved >= kTreeLaunches;
   for (int jj = 0; jj < njobs; ++jj) {
     const int j = jj;  // internal index
     const aidw_job& a = jobs[order[jj]];
@@ -786,6 +789,7 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   b->mem_bytes = layout(nullptr);
   if ((e = dmalloc(&b->mem, b->mem_bytes)) != hipSuccess) {
     destroy_plan(b);
+    if (!tj.empty()) return create_plan(jobs, njobs, cfg_in, out, false);
     return hip_fail(e, "allocating the batch workspace");
   }
   layout(static_cast<char*>(b->mem));

@@ -63,3 +63,28 @@ def test_off_is_the_pair_kernel(T, kinds, split_points, q):
             jb.z.mul_(1.5)
         T.cuda.synchronize()
     plan.close()
+
+
+def test_no_room_for_the_moments(T, monkeypatch):
+    """A plan whose workspace fits only without the moments evaluates every pair."""
+    import paper_1601_05904_amd as aidw
+    import paper_1601_05904_amd.batch as B
+    n, m = 61440, 40000
+    jobs = [job(T, n, m, 50 + i) for i in range(2)]
+    config = B.Config(split_points=4096)
+    full = B.Plan(jobs, config)
+    full_bytes = full.describe()["workspace_bytes"]
+    full.close()
+    # an 80-byte record of a point (its moments and its share of a pool) is left out of the limit
+    monkeypatch.setenv("AIDW_FAULT", "alloc:%d" % (full_bytes - 80 * 2 * n))
+    plan = B.Plan(jobs, config)
+    assert plan.describe()["workspace_bytes"] < full_bytes - 80 * 2 * n
+    plan.run()
+    T.cuda.synchronize()
+    monkeypatch.setenv("AIDW_FAULT", "alloc:1024")
+    with pytest.raises(aidw.AidwError):
+        B.Plan(jobs, config)
+    monkeypatch.delenv("AIDW_FAULT")
+    for i, jb in enumerate(jobs):
+        assert T.equal(plan.qz[i], alone(T, jb, 15))
+    plan.close()
