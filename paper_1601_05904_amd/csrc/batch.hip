@@ -594,9 +594,14 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   std::stable_sort(order.begin(), order.end(),
                    [&](int32_t a, int32_t b) { return kclass(jobs[a].params.k) < kclass(jobs[b].params.k); });
   double saved = 0.0;
+  int tree_jobs = 0;
   for (int j = 0; j < njobs; ++j)
-    if (tree_saves(jobs[j]) > 0.0) saved += tree_saves(jobs[j]) - kTreePoint * (double)jobs[j].n;
-  const bool use_tree = moments && cfg.integer_powers && saved >= kTreeLaunches;
+    if (tree_saves(jobs[j]) > 0.0) {
+      saved += tree_saves(jobs[j]) - kTreePoint * (double)jobs[j].n;
+      ++tree_jobs;
+    }
+  // (the moments' launches have a row of workgroups per job, 65,535 at most)
+  const bool use_tree = moments && cfg.integer_powers && saved >= kTreeLaunches && tree_jobs < 65536;
   for (int jj = 0; jj < njobs; ++jj) {
     const int j = jj;  // internal index
     const aidw_job& a = jobs[order[jj]];
