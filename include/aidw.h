@@ -584,7 +584,13 @@ aidw_status aidw_batch_tune(const aidw_job* jobs, int32_t njobs, const aidw_batc
 /* Temporaries of the calls above come from a cache of device blocks that the
  * library keeps between calls (reused in stream order, or after an event wait
  * on another stream).  This waits for the current device and frees the cached
- * blocks not in use on it.  Errors: AIDW_EDEVICE. */
+ * blocks not in use on it.  Errors: AIDW_EDEVICE.
+ * A call captured into a HIP graph takes the blocks that an earlier call of the
+ * same sizes on that stream left (nothing can be allocated during a capture).
+ * They stay reserved until the process ends: no other call takes them and they
+ * are not freed, so the graph can be replayed at any time and on any stream.
+ * Later captures on the same stream take them again: replays of graphs captured
+ * on one stream must not overlap each other. */
 aidw_status aidw_release_cached_memory(void);
 
 /* Static text for a status code. */

@@ -109,6 +109,8 @@ hipError_t dmalloc(void** p, size_t bytes) {
 // Blocks released together share one event: recording one costs the host about 2 us, and a run
 // released 30 (4096 x 4096 points: 220 -> 125 us).  An event is recorded again only when no free
 // block refers to it any more.  Blocks are only freed by aidw_release_cached_memory.
+// The blocks of a captured call belong to the graph, which may be replayed at any time and on any
+// stream: they are reserved from then on, for later captures on that stream alone, and never freed.
 struct Release {
   hipEvent_t event = nullptr;
   int device = 0;
@@ -121,6 +123,7 @@ struct CachedBlock {
   hipStream_t stream = nullptr;  // stream of the last use
   Release* done = nullptr;       // recorded on that stream when the block was released
   bool busy = false;
+  bool reserved = false;         // a graph captured on that stream uses it
 };
 std::mutex g_cache_mu;  // guards the blocks and the releases
 std::vector<CachedBlock>& block_cache() {
@@ -173,6 +176,11 @@ size_t block_size_class(size_t bytes) {
   return (bytes + g - 1) / g * g;
 }
 
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
 hipError_t dmalloc_async(void** p, size_t bytes, hipStream_t s) {
   *p = nullptr;
   if (g_arena) return arena_take(p, bytes);
@@ -184,23 +192,25 @@ hipError_t dmalloc_async(void** p, size_t bytes, hipStream_t s) {
   {
     std::lock_guard<std::mutex> lock(g_cache_mu);
     auto& cache = block_cache();
-    auto smallest = [&](size_t limit, bool own) {
+    auto smallest = [&](size_t limit, bool own, bool reserved) {
       int best = -1;
       for (int i = 0; i < (int)cache.size(); ++i) {
         const CachedBlock& b = cache[i];
-        if (b.busy || b.device != dev || b.bytes < want || b.bytes > limit || (own && b.stream != s)) continue;
+        if (b.busy || b.device != dev || b.bytes < want || b.bytes > limit || (own && b.stream != s) ||
+            b.reserved != reserved)
+          continue;
         if (best < 0 || b.bytes < cache[best].bytes || (b.bytes == cache[best].bytes && b.stream == s)) best = i;
       }
       return best;
     };
-    int best = smallest(2 * want, false);
+    int best = smallest(2 * want, false, false);
     // While s is captured nothing can be allocated and no other stream waited for.  The smallest of the
     // stream's own blocks that suffices, however large, then always leaves enough for the requests
-    // that an earlier call of the same sizes met.
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if ((best < 0 || cache[best].stream != s) && hipStreamIsCapturing(s, &capture) == hipSuccess &&
-        capture != hipStreamCaptureStatusNone) {
-      const int own = smallest(~(size_t)0, true);
+    // that an earlier call of the same sizes met; those of earlier captures come first, so that
+    // captures one after the other do not reserve ever more.
+    const int again = smallest(~(size_t)0, true, true);
+    if ((best < 0 || cache[best].stream != s || again >= 0) && capturing(s)) {
+      const int own = again >= 0 ? again : smallest(~(size_t)0, true, false);
       if (own >= 0) best = own;
     }
     if (best >= 0) {
@@ -225,11 +235,13 @@ hipError_t dmalloc_async(void** p, size_t bytes, hipStream_t s) {
   return hipSuccess;
 }
 
-// Releases the blocks (null entries and those of an arena are passed over) after the work queued on s.
+// Releases the blocks (null entries and those of an arena are passed over) after the work queued on s; reserves
+// them while s is captured.
 void dfree_async(void* const* ptrs, int count, hipStream_t s) {
   std::lock_guard<std::mutex> lock(g_cache_mu);
   Release* r = nullptr;
-  bool recorded = false;
+  const bool captured = capturing(s);
+  bool recorded = captured;
   for (int i = 0; i < count; ++i) {
     if (!ptrs[i] || in_arena(ptrs[i])) continue;
     for (CachedBlock& b : block_cache()) {
@@ -243,6 +255,7 @@ void dfree_async(void* const* ptrs, int count, hipStream_t s) {
       if (r) ++r->blocks;
       b.stream = s;
       b.busy = false;
+      b.reserved |= captured;
       break;
     }
   }
@@ -1590,7 +1603,7 @@ aidw_status aidw_release_cached_memory(void) {
   auto& cache = block_cache();
   std::vector<CachedBlock> keep;
   for (CachedBlock& b : cache) {
-    if (b.busy || b.device != dev) {
+    if (b.busy || b.reserved || b.device != dev) {
       keep.push_back(b);
       continue;
     }

@@ -139,3 +139,70 @@ def test_small_grid_matches_the_large_build(n, m, kind, occupancy):
     r = aidw.run(x, y, z, qx, qy, prm, want_alpha=True, want_robs=True)
     r_many = aidw.run(x, y, z, *many, prm, want_alpha=True, want_robs=True)
     assert torch.equal(r[1], r_many[1][:m]) and torch.equal(r[2], r_many[2][:m])
+
+
+def test_captured_memory_is_not_shared():
+    """The memory of a captured call belongs to its graph: no later call takes it, on another stream or its own, it
+    survives aidw_release_cached_memory, and a second capture without a call between takes it again."""
+    import ctypes
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1601_05904_amd as aidw
+    lib = aidw.load(build_if_missing=False)
+    n = m = 200000
+    rng = np.random.default_rng(3)
+    x, y, z = (torch.from_numpy(a).cuda() for a in rng.random((3, n)).astype(np.float32))
+    qx, qy = (torch.from_numpy(a).cuda() for a in rng.random((2, m)).astype(np.float32))
+    grid = aidw.build_grid(x, y, qx, qy, aidw.Params(k=10))
+    r_obs, d1, _ = aidw.knn(grid, qx, qy, 10)
+    p = aidw.Params(k=10, area=grid.describe()["area"])._c()
+    grid.close()
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def call(out, stream):
+        assert lib.aidw_interpolate(x.data_ptr(), y.data_ptr(), z.data_ptr(), n, qx.data_ptr(), qy.data_ptr(), m,
+                                    r_obs.data_ptr(), d1.data_ptr(), ctypes.byref(p), None, out.data_ptr(), None,
+                                    stream.cuda_stream) == aidw.OK
+        torch.cuda.synchronize()
+
+    def taken(f):
+        """Device memory that f takes beyond what is cached (the moments alone are some 30 MB)."""
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        f()
+        torch.cuda.synchronize()
+        return before - torch.cuda.mem_get_info()[0]
+
+    outs = [torch.empty(m, device="cuda") for _ in range(4)]
+    torch.cuda.synchronize()
+    aidw.release_cached_memory()
+    used = taken(lambda: call(outs[0], side))
+    assert used > 30 << 20
+    graphs = [torch.cuda.CUDAGraph() for _ in range(2)]
+
+    def capture(graph, out):
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            assert lib.aidw_interpolate(x.data_ptr(), y.data_ptr(), z.data_ptr(), n, qx.data_ptr(), qy.data_ptr(), m,
+                                        r_obs.data_ptr(), d1.data_ptr(), ctypes.byref(p), None, out.data_ptr(), None,
+                                        side.cuda_stream) == aidw.OK
+
+    for graph, out in zip(graphs, outs):
+        capture(graph, out)
+    assert taken(lambda: call(outs[2], other)) > used // 2
+    assert taken(lambda: call(outs[3], other)) == 0
+    assert taken(lambda: aidw.release_cached_memory()) <= -(used // 2)
+    assert taken(lambda: call(outs[3], side)) > used // 2
+    aidw.release_cached_memory()
+    for _ in range(3):
+        z.mul_(1.5).add_(0.125)
+        for o in outs:
+            o.zero_()
+        torch.cuda.synchronize()
+        for graph in graphs:
+            graph.replay()
+            torch.cuda.synchronize()
+        call(outs[2], other)
+        call(outs[3], side)
+        assert all(torch.equal(outs[0], o) for o in outs[1:])
