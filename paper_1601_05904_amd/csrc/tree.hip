@@ -432,12 +432,6 @@ __device__ __forceinline__ void shift_up(const Plan* __restrict__ plan, float* _
   const int all = nx * plan->ny[lvl];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (int t = threadIdx.x; t < kTri; t += 256) s_c[t] = kTriT.c[t];
-  // place of mu_{jk}, j >= k, in the coefficient order
-  auto place = [](int j, int k) {
-    const int o = j + k;
-    const int before = (o / 2) * ((o + 1) / 2) + o - o / 2;  // coefficients of the orders below o
-    return before + (j - k - (o & 1)) / 2;
-  };
   for (int id = block; id < all; id += blocks) {
     const int py = id / nx, px = id - py * nx;
     const int chx = 2 * px + (w & 1), chy = 2 * py + (w >> 1);
@@ -489,7 +483,7 @@ __device__ __forceinline__ void shift_up(const Plan* __restrict__ plan, float* _
         const double2 d = s_pow[w][J - j];
         const double ex = c * d.x, ey = c * d.y;
         const bool up = j >= k;
-        const double* mu = s_m[w][up ? place(j, k) : place(k, j)];
+        const double* mu = s_m[w][up ? coef_place(j, k) : coef_place(k, j)];
         const double i0 = up ? mu[1] : -mu[1], i1 = up ? mu[3] : -mu[3];
         a[0] += ex * mu[0] - ey * i0;
         a[1] += ex * i0 + ey * mu[0];
@@ -1231,14 +1225,6 @@ size_t node_bytes(int64_t n) {
 }
 
 }  // namespace tree
-
-// Bound of the truncation: the terms of order o of one square sum to at most w0 C_o(alpha) rho^o
-// times its count (or sum |z|), C_o = Gamma(o + alpha) / (Gamma(alpha) o!) the Gegenbauer bound and
-// rho = (half diagonal) / distance; they may reach 2^-22 of the query's sums.
-static float order_bound(double alpha, int tier) {
-  const int o = 2 * tier + 3;
-  return (float)(-22.0 - (lgamma(o + alpha) - lgamma(alpha) - lgamma(o + 1.0)) / M_LN2);
-}
 
 static Thresholds class_bounds() {
   Thresholds t{};

@@ -13,6 +13,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include "aidw_internal.h"
@@ -64,6 +65,24 @@ __host__ __device__ constexpr int coef_offset(int l, int m) {
     return at + 2 * (m - 2);
   }
   return at + 4 * (m - coef_first(l));
+}
+
+// Place of mu_{jk} = sum r^j conj(r)^k, j >= k, in the coefficient order: orders ascending, l = j - k
+// ascending within an order.
+__host__ __device__ constexpr int coef_place(int j, int k) {
+  const int o = j + k;
+  const int before = (o / 2) * ((o + 1) / 2) + o - o / 2;  // coefficients of the orders below o
+  return before + (j - k - (o & 1)) / 2;
+}
+
+// log2 of the largest Q rho^o for which the order P = 2 tier + 2 is taken, o = P + 1: the terms of order o of one
+// square sum to at most w0 C_o(alpha) rho^o times its count (or sum |z|), C_o = Gamma(o + alpha) /
+// (Gamma(alpha) o!) the Gegenbauer bound and rho = (half diagonal) / distance, and these may reach
+// 2^-22 of the query's sums.  The terms of the further orders are not counted: at most some three times these
+// together at alpha = 8, less below.
+inline float order_bound(double alpha, int tier) {
+  const int o = 2 * tier + 3;
+  return (float)(-22.0 - (lgamma(o + alpha) - lgamma(alpha) - lgamma(o + 1.0)) / M_LN2);
 }
 
 // Geometry of a job's squares, made on the device from the grid scalars: level 0 squares (leaves)

@@ -218,3 +218,32 @@ def test_no_room_for_the_moments(T, small_allocations):
     p = aidw.Params(k=10)
     for _ in range(2):
         assert T.equal(aidw.run(*d, p), every_pair(lambda: aidw.run(*d, p)))
+
+
+@pytest.mark.parametrize("n", [4096, 4099, 8192, 40961, 65537, 1 << 20])
+def test_sizes_of_the_summation(T, n):
+    """n m >= 1.25e9 + 6500 n + 1650 m with n >= 4096, m >= 64 is summed hierarchically (its bits are not the pair
+    kernel's), one query less is not; nor is a size below, a level above 8 or a launch shape of the caller's."""
+    aidw = aidw_mod()
+    m = int(np.ceil((1.25e9 + 6500.0 * n) / (n - 1650.0)))
+    ds = W.make(n, m, 10, n, "uniform", 8)
+    x, y, z, qx, qy = dev(T, ds.x, ds.y, ds.z, ds.qx, ds.qy)
+    call = lambda k, p: aidw.run(x, y, z, qx[:k].contiguous(), qy[:k].contiguous(), p)  # noqa: E731
+    p = aidw.Params(k=10)
+    assert not T.equal(call(m, p), every_pair(lambda: call(m, p)))
+    assert T.equal(call(m - 1, p), every_pair(lambda: call(m - 1, p)))
+    p = aidw.Params(k=10, levels=(1, 2, 3, 4, 8.5))
+    assert T.equal(call(m, p), every_pair(lambda: call(m, p)))
+
+
+@pytest.mark.parametrize("n,m,kind", [(40961, 50009, "uniform"), (65537, 40001, "mixture"), ((1 << 20) + 13, 9001, "mixture"),
+                                      (4099, (1 << 19) + 77, "uniform"), (50003, 45001, "uniform")])
+def test_usual_data_are_summed_hierarchically(T, n, m, kind):
+    """Sizes and kinds that other tests of the summation rest on: the plan is on."""
+    aidw = aidw_mod()
+    ds = W.make(n, m, 10, n, kind, 8)
+    d = dev(T, ds.x, ds.y, ds.z, ds.qx, ds.qy)
+    p = aidw.Params(k=10)
+    qz, alpha, _ = aidw.run(*d, p, want_alpha=True)
+    assert not T.equal(qz, every_pair(lambda: aidw.run(*d, p)))
+    assert error(T, qz, *d, alpha, 128) <= TREE_TOL
