@@ -263,8 +263,8 @@ int hilbert_bits(int64_t n);    // bits per axis of the query order's tiles
 int padded_points(int64_t n);   // length of the cell-ordered arrays tx, ty, tz
 size_t plan_bytes();
 size_t node_bytes(int64_t n);   // the squares' records
-// The parts of a job that follow from its size and alpha levels (all <= 8).
-void fill_job(Job* j, int64_t n, const double* levels);
+// The parts of a job that follow from its sizes and alpha levels (all <= 8); pairs: of all jobs of its launches.
+void fill_job(Job* j, int64_t n, int64_t m, double pairs, const double* levels);
 }  // namespace tree
 // The squares of a job's points: plan, the padded points in cell order and the moments.
 // *zero_word (may be null) is cleared on the way.

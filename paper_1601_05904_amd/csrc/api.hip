@@ -664,12 +664,11 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
     double2* partial = partials ? reinterpret_cast<double2*>(nodes) : nullptr;
     if (ev_begin) HIP_TRY(hipEventRecord(ev_begin, s), "event");
     tree::Job job{};
-    tree::fill_job(&job, n, p->alpha);
+    tree::fill_job(&job, n, m, (double)n * (double)m, p->alpha);
     job.gs = points->dev;
     job.plan = plan;
     job.cell_start = points->cell_start;
     job.nodes = reinterpret_cast<float*>(nodes);
-    job.m = (int32_t)m;
     HIP_TRY(launch_tree_build(job, points->sx, points->sy, points->sidx, z, tx, ty, tz, count, s), "moments");
     const float* alpha_use = alpha_f;
     if (alpha_in) {

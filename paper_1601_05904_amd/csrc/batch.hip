@@ -229,7 +229,7 @@ __global__ __launch_bounds__(256) void k_b_query_keys(const BatchJob* __restrict
 }
 
 // z in the cell order of all jobs' points, for the jobs' moments; the points past the last are zero.
-// A value beyond the moments' range turns its job's plan off.
+// A value beyond the moments' range turns its job's plan off, and a leaf of too many points.
 __global__ __launch_bounds__(256) void k_b_tree_z(const BatchJob* __restrict__ jobs, const int32_t* __restrict__ noff,
                                                   int njobs, int sum_n, int npad, const int32_t* __restrict__ sidx,
                                                   const float* __restrict__ zp, float* __restrict__ sx,
@@ -243,10 +243,11 @@ __global__ __launch_bounds__(256) void k_b_tree_z(const BatchJob* __restrict__ j
   }
   const float v = zp[sidx[e]];
   tz[e] = v;
-  if ((__float_as_uint(v) & 0x7fffffffu) >= __float_as_uint(tree::kZLimit)) {
-    const int t = jobs[find_seg(noff, njobs, e)].tree;
-    if (t >= 0) tjobs[t].plan->bad = 1;
-  }
+  const BatchJob& J = jobs[find_seg(noff, njobs, e)];
+  if (J.tree < 0) return;
+  const tree::Job& T = tjobs[J.tree];
+  if ((__float_as_uint(v) & 0x7fffffffu) >= __float_as_uint(tree::kZLimit) || tree::dense_leaf_at(T, e - J.noff))
+    T.plan->bad = 1;
 }
 
 // kNN + Eq. 3 for the queries at binned positions [t_begin, t_end), LANES lanes each; a lane searches
@@ -593,11 +594,12 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   for (int j = 0; j < njobs; ++j) order[j] = j;
   std::stable_sort(order.begin(), order.end(),
                    [&](int32_t a, int32_t b) { return kclass(jobs[a].params.k) < kclass(jobs[b].params.k); });
-  double saved = 0.0;
+  double saved = 0.0, tree_pairs = 0.0;
   int tree_jobs = 0;
   for (int j = 0; j < njobs; ++j)
     if (tree_saves(jobs[j]) > 0.0) {
       saved += tree_saves(jobs[j]) - kTreePoint * (double)jobs[j].n;
+      tree_pairs += (double)jobs[j].n * (double)jobs[j].m;
       ++tree_jobs;
     }
   // (the moments' launches have a row of workgroups per job, 65,535 at most)
@@ -638,9 +640,8 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
     if (tree_job) {
       J.tree = (int32_t)tj.size();
       tree::Job t{};
-      tree::fill_job(&t, a.n, a.params.alpha);
+      tree::fill_job(&t, a.n, a.m, tree_pairs, a.params.alpha);
       t.q0 = (int32_t)sm;
-      t.m = (int32_t)a.m;
       t.group0 = (int32_t)groups;
       t.out0 = spart - sm;
       groups += (a.m + tree::kGroup - 1) / tree::kGroup;

@@ -145,23 +145,26 @@ __global__ void k_tree_plan(Jobs jobs, uint32_t* __restrict__ zero_word) {
 }
 
 // The cell-ordered points with room for a chunk's over-read.  A z beyond the limit (a NaN's bits are
-// above every number's) turns the plan off.
-__global__ __launch_bounds__(256) void k_tree_gather(const float* __restrict__ sx, const float* __restrict__ sy,
+// above every number's) turns the plan off, as does a leaf of too many points, before any is summed.
+__global__ __launch_bounds__(256) void k_tree_gather(Job job, const float* __restrict__ sx, const float* __restrict__ sy,
                                                      const int32_t* __restrict__ sidx, const float* __restrict__ z,
-                                                     int n, int npad, float* __restrict__ tx, float* __restrict__ ty,
-                                                     float* __restrict__ tz, Plan* __restrict__ plan) {
+                                                     int npad, float* __restrict__ tx, float* __restrict__ ty,
+                                                     float* __restrict__ tz) {
+  const int n = job.n;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   uint32_t b = 0u;
+  bool dense = false;
   if (i < npad) {
     const bool in = i < n;
     const float v = in ? z[sidx[i]] : 0.0f;
+    dense = dense_leaf_at(job, i);
     tx[i] = in ? sx[i] : 0.0f;
     ty[i] = in ? sy[i] : 0.0f;
     tz[i] = v;
     b = __float_as_uint(v) & 0x7fffffffu;
   }
   // only values in reach of the limit are reported
-  if (__any(b >= __float_as_uint(kZLimit)) && (threadIdx.x & 63) == 0) plan->bad = 1;
+  if (__any(dense || b >= __float_as_uint(kZLimit)) && (threadIdx.x & 63) == 0) job.plan->bad = 1;
 }
 
 // ---------------------------------------------------------------- moments
@@ -284,12 +287,12 @@ __device__ inline void store_moments(float* __restrict__ rec, int q, double v) {
 }
 
 // The points of columns [c0, c1), rows [r0, r1) of the grid about (cx, cy) (add_points); returns their count.
-// More than kDenseLeaf, which turn the plan off, are not summed: a wavefront sums 16 in a microsecond, and one
+// More than `limit`, which turn the plan off, are not summed: a wavefront sums 16 in a microsecond, and one
 // far outlier can put all points into a leaf (2^18 and 16,384 queries: 34.2 -> 2.3 ms, every pair 1.1).
 __device__ __forceinline__ int add_cells(const float* __restrict__ tx, const float* __restrict__ ty,
                                          const float* __restrict__ tz, const int32_t* __restrict__ cell_start, int ncol,
                                          int c0, int c1, int r0, int r1, float cx, float cy, float ih,
-                                         float* __restrict__ tab, double* __restrict__ acc, double& sabs) {
+                                         float* __restrict__ tab, double* __restrict__ acc, double& sabs, int limit) {
   const int lane = threadIdx.x & 63;
   int count = 0;
   for (int rb = r0; rb < r1; rb += 64) {
@@ -306,7 +309,7 @@ __device__ __forceinline__ int add_cells(const float* __restrict__ tx, const flo
     }
     const int total = __builtin_amdgcn_readlane(incl, 63), nrows = min(64, r1 - rb);
     count += total;
-    if ((uint32_t)count > kDenseLeaf) return count;
+    if (count > limit) return count;
     sabs += add_points<kOrder>(tx, ty, tz, lo, incl, len, nrows, total, cx, cy, ih, tab, acc);
   }
   return count;
@@ -370,9 +373,9 @@ __global__ __launch_bounds__(256, 5) void k_tree_p2m(Jobs jobs, const float* __r
       for (int q = lane; q < 4 * kCoefs; q += 64) acc[q] = 0.0;
       wave_sync();
       if (pass == 0)
-        count = add_cells(tx, ty, tz, cell_start, ncol, c0, c1, r0, r1, cx0, cy0, ih0, s_sum[w].tab, acc, sabs);
+        count = add_cells(tx, ty, tz, cell_start, ncol, c0, c1, r0, r1, cx0, cy0, ih0, s_sum[w].tab, acc, sabs, job.dense);
       else
-        add_cells(tx, ty, tz, cell_start, ncol, c0, c1, r0, r1, cx1, cy1, 0.5f * ih0, s_sum[w].tab, acc, unused);
+        add_cells(tx, ty, tz, cell_start, ncol, c0, c1, r0, r1, cx1, cy1, 0.5f * ih0, s_sum[w].tab, acc, unused, job.dense);
       if (pass == 0) {
         for (int o = 32; o > 0; o >>= 1) sabs += __shfl_xor(sabs, o, 64);
         if (live) {
@@ -390,7 +393,7 @@ __global__ __launch_bounds__(256, 5) void k_tree_p2m(Jobs jobs, const float* __r
         if (lane == 0) {
           s_abs[w] = sabs;
           s_cnt[w] = count;
-          if ((uint32_t)count > kDenseLeaf) plan->bad = 1;
+          if (count > job.dense) plan->bad = 1;
         }
       }
     }
@@ -542,7 +545,7 @@ __device__ __forceinline__ void fine_squares(Plan* __restrict__ plan, const int3
     for (int q = lane; q < 4 * kCoefs; q += 64) sum.acc[q] = 0.0;
     wave_sync();
     double sabs = 0.0;
-    const int n = add_cells(tx, ty, tz, cell_start, plan->ncol, c0, c1, r0, r1, cx, cy, ih, sum.tab, sum.acc, sabs);
+    const int n = add_cells(tx, ty, tz, cell_start, plan->ncol, c0, c1, r0, r1, cx, cy, ih, sum.tab, sum.acc, sabs, kDenseLeaf);
     for (int o = 32; o > 0; o >>= 1) sabs += __shfl_xor(sabs, o, 64);
     const int idx = pool + 4 * id + w;
     float* rec = nodes + (size_t)idx * kRec;
@@ -1233,8 +1236,29 @@ static Thresholds class_bounds() {
   return t;
 }
 
-void tree::fill_job(Job* j, int64_t n, const double* levels) {
+// The largest leaf that hierarchical sums are kept for, by times in us: the pairs (5.2e12 a second, and the 8 % and
+// the launches that a plan which turns out off adds) against the sums, for even data 110 + 4e-4 m + 3e-4 n and
+// for each point of the largest leaf 0.2 + 6e-7 n: one wavefront forms a leaf's moments, and a group of queries
+// pays for every point near it.  Half as many points again are let pass, for the sums are more exact.  Whole
+// runs, every pair / hierarchical, mixtures of 16 | 8 | 3 | 1 components, whose largest leaves hold some 1000 | 2000 |
+// 3700 | 11,000 points; behind || they are off:
+//   45,000 x 45,000:   624/547 | 634/700 || 700/1067 | 846/2276     200,000 x 20,000: 1084/783 | 1078/1000 || 1155/1480 | 1253/3625
+//   262,144 x 30,000:  1882/912 | 1951/1249 | 1998/1685 || 2094/4070  2^20 x 9000: 2423/2071 | 2446/2632 || 2487/4109 | 2649/10421
+//   100,000 x 100,000: 2269/752 | 2312/928 | 2348/1266 | 2611/2664  2^20 x 20,000: 4657/2025 | 4653/2349 | 4735/3977 || 4915/8826
+// Jobs that share their launches hide each other's chains: pairs are then those of all of them, and a job's own are set
+// against 0.0115 a point of the largest leaf (a replay of 40 jobs of 16,384 x 16,384, every pair / hierarchical: 2637/1379
+// even, 2975/2086 with 8 components, 3861/4349 with 1).
+static int dense_leaf(int64_t n, int64_t m, double pairs) {
+  const double room = 1.08 * pairs / 5.2e6 - 50.0 - 4e-4 * (double)m - 3e-4 * (double)n;
+  const double own = fmax(0.9 * (double)n * (double)m / 5.2e6 - 14.0, 29.0);
+  const double most = fmin(1.5 * room / (0.2 + 6e-7 * (double)n), own / 0.0115);
+  return (int)fmin(fmax(most, (double)kRefine), (double)kDenseLeaf);
+}
+
+void tree::fill_job(Job* j, int64_t n, int64_t m, double pairs, const double* levels) {
   j->n = (int32_t)n;
+  j->m = (int32_t)m;
+  j->dense = dense_leaf(n, m, pairs);
   j->node_cap = node_capacity(n);
   // levels of a square box's tree, and two more for other shapes; a longer strip's top level simply
   // has more squares
@@ -1290,8 +1314,7 @@ hipError_t launch_tree_build(const tree::Job& job, const float* sx, const float*
                              const float* z, float* tx, float* ty, float* tz, uint32_t* zero_word, hipStream_t s) {
   launch_plan(OneJob{job}, 1, zero_word, s);
   const int npad = tree::padded_points(job.n);
-  hipLaunchKernelGGL(k_tree_gather, dim3(div_up(npad, 256)), dim3(256), 0, s, sx, sy, sidx, z, job.n, npad, tx, ty, tz,
-                     job.plan);
+  hipLaunchKernelGGL(k_tree_gather, dim3(div_up(npad, 256)), dim3(256), 0, s, job, sx, sy, sidx, z, npad, tx, ty, tz);
   launch_moments(OneJob{job}, 1, job.n, job.level_cap, tx, ty, tz, s);
   return hipGetLastError();
 }

@@ -46,7 +46,7 @@ constexpr int kGroup = 64;               // queries per group (one per lane)
 constexpr int kClasses = 9;              // alpha classes 0 (general), 1 .. 8
 constexpr int kSplitPoints = 6000;       // near points from which a group is worth splitting
 constexpr int kFarCost = 3000;           // a group's far squares in pair evaluations
-constexpr uint32_t kDenseLeaf = 1 << 14; // points in one leaf above which the direct sums are used
+constexpr int kDenseLeaf = 1 << 14;      // most points that any job's leaf may hold
 
 // A square's record: count, sum |z|, centre x, centre y, then for each (l, m) the real numbers
 // (num, den) for l = 0, (num re, num im, den re, den im) for l > 0.  The first line (64 bytes) ends
@@ -121,12 +121,27 @@ struct Job {
   const int32_t* cell_start;  // the job's cells; their entries index the common point arrays
   float* nodes;               // node_cap records
   int32_t n, node_cap, level_cap;
+  int32_t dense;              // points in one leaf above which the direct sums are used
   int32_t q0, m;              // its queries: positions [q0, q0 + m) of the query order
   int32_t group0;             // its first group of kGroup queries
   uint32_t fast_mask;         // integer alpha classes that have their own weights
   int64_t out0;               // double2 output: query q at out0 + q
   float thr0[kTiers];         // log2 bounds of the orders for a group of general alpha
 };
+
+// Whether leaf i of a job holds too many points; i from the number of leaves on: false.  (Leaves of many rows, as very
+// fine grids have them, are left to the kernel that forms the moments.)
+__device__ inline bool dense_leaf_at(const Job& job, int i) {
+  const Plan* p = job.plan;
+  const int nx = p->nx[0], bs = p->bs;
+  if (i >= nx * p->ny[0] || bs > 5) return false;
+  const int iy = i / nx, ix = i - iy * nx;
+  const int c0 = ix << bs, c1 = min(p->ncol, (ix + 1) << bs), r1 = min(p->nrow, (iy + 1) << bs);
+  int count = 0;
+  for (int r = iy << bs; r < r1; ++r)
+    count += job.cell_start[(int64_t)r * p->ncol + c1] - job.cell_start[(int64_t)r * p->ncol + c0];
+  return count > job.dense;
+}
 
 // Centre of a square, the same float32 values wherever they are needed.
 __device__ inline void centre(const Plan* p, int lvl, int ix, int iy, float& cx, float& cy) {

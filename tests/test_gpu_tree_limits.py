@@ -247,3 +247,27 @@ def test_usual_data_are_summed_hierarchically(T, n, m, kind):
     qz, alpha, _ = aidw.run(*d, p, want_alpha=True)
     assert not T.equal(qz, every_pair(lambda: aidw.run(*d, p)))
     assert error(T, qz, *d, alpha, 128) <= TREE_TOL
+
+
+@pytest.mark.parametrize("occupancy", [0.5, 2.0, 8.0])
+def test_dense_leaves(T, occupancy):
+    """Clusters of thousands of points in a leaf are summed hierarchically, with squares below the leaves, where the queries
+    are many (on), and pair by pair where they are few (off)."""
+    aidw = aidw_mod()
+    rng = np.random.default_rng(61)
+
+    def places(n):
+        p = rng.random((n, 2))
+        c = rng.integers(0, 4, n // 2)
+        p[: n // 2] = np.array([[0.2, 0.3], [0.7, 0.2], [0.25, 0.8], [0.5, 0.5]])[c] + rng.normal(0, 1, (n // 2, 2)) * (
+            np.array([0.002, 0.004, 0.008, 0.016])[c, None])
+        return W.quantise(p[rng.permutation(n)].clip(0, 1))
+
+    p, q = places(60000), places(400000)
+    d = dev(T, p[:, 0], p[:, 1], np.sin(9 * p[:, 0]) + np.cos(7 * p[:, 1]) + 0.3, q[:, 0], q[:, 1])
+    prm = aidw.Params(k=10, occupancy=occupancy)
+    qz, alpha, _ = aidw.run(*d, prm, want_alpha=True)
+    assert not T.equal(qz, every_pair(lambda: aidw.run(*d, prm)))
+    assert error(T, qz, *d, alpha) <= TREE_TOL
+    few = d[:3] + [v[:30000].contiguous() for v in d[3:]]
+    assert T.equal(aidw.run(*few, prm), every_pair(lambda: aidw.run(*few, prm)))
