@@ -546,7 +546,15 @@ aidw_status knn_impl(const aidw_grid* g, const float* qx, const float* qy, int64
   // in a dense cell.  us with 1 | 4 | 8 lanes, uniform and an 8-component mixture: 4096 queries
   // - | 51 | 52 and - | 108 | 78; 65,536: - | 67 | 73 and - | 113 | 106; 262,144: 102 | 111 | - and
   // 198 | 173 | -, with indices 129 | 156 | - and 270 | 293 | -; 2^20: 213 | 278 | - and 325 | 395 | -.
-  if (nn_idx ? m >= (1 << 17) : m > (1 << 18))
+  // With indices one lane walks its cells twice, which costs more than a list with indices where k is
+  // small, or the cells are full and crowded with queries: 20,000 points in 16 components, 200,000 queries, 1 | 4 lanes,
+  // k = 1 at 2 points a cell 176 | 106, k = 10 at 8 points a cell 381 | 233; uniform 78 | 80 and 120 | 126 (2^18 points
+  // and queries, k = 10 at 20 a cell: 199 | 248).  Without, only in very full cells: 2^20, k = 1, 20 points a cell
+  // 403 | 388 and 1398 | 644.
+  const double per_cell = g->host_valid ? (double)g->n / (double)g->host.ncells : 0.0;
+  const bool one = nn_idx ? m >= (1 << 17) && k > 4 && (m > (1 << 18) || m < 4 * g->n || per_cell < 0.75 * k)
+                          : m > (1 << 18) && per_cell < 16.0 * k;
+  if (one)
     HIP_TRY(launch_knn(g->dev, g->cell_start, g->sx, g->sy, g->sidx, qx, qy, order, nullptr, (int)m, k, r_obs, d1sq,
                        nn_idx, s),
             "kNN kernel");

@@ -74,3 +74,25 @@ def test_queries_that_are_no_numbers(m):
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
         assert got[2] is None or torch.equal(got[2], want[2])
     grid.close()
+
+
+@pytest.mark.parametrize("k", [1, 4, 5, 10])
+@pytest.mark.parametrize("occupancy", [2.0, 4.5, 9.0, 100.0])
+def test_full_cells_match_brute_force(occupancy, k):
+    """On both sides of the lines between one and four lanes a query that k and the points a cell draw."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1601_05904_amd as aidw
+    aidw.load(build_if_missing=False)
+    rng = np.random.default_rng(k)
+    x, y = (torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda() for a in layout("gap", rng, 3000))
+    qx, qy = (torch.from_numpy(a).cuda() for a in rng.random((2, 270001)).astype(np.float32))
+    want = aidw.knn_bruteforce(x, y, qx, qy, k, want_idx=True)
+    grid = aidw.build_grid(x, y, qx, qy, aidw.Params(k=k, occupancy=occupancy))
+    for m in (131071, 131072, 262144, 270001):
+        for idx in (False, True):
+            r, d1, ix = aidw.knn(grid, qx[:m], qy[:m], k, want_idx=idx)
+            assert torch.equal(r, want[0][:m]) and torch.equal(d1, want[1][:m]), (m, idx)
+            assert ix is None or torch.equal(ix, want[2][:m]), m
+    grid.close()
