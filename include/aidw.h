@@ -211,12 +211,17 @@ aidw_status aidw_nn_statistic(const aidw_grid* g, const float* qx, const float* 
  * streamed through the chip in tiles shared by every query of a wavefront, the
  * per-tile float32 partial sums are folded into compensated (two-sum) pairs,
  * and the final numerator / denominator are combined in float64.
- * Large jobs (from about n m = 2e9 pairs, levels <= 8) are summed hierarchically:
- * points near a query pair by pair as above, distant squares of points through
- * their moments to the order (at most 16) that keeps the neglected terms of a
- * square below 2^-22 of the query's sums.  The sums then cost O((n + m) log n)
- * instead of O(n m); their error is that of the float32 weights (measured
- * against float64: root mean square 5e-8, as with every pair evaluated).
+ * Large jobs (n m >= 1.25e9 + 6500 n + 1650 m, n >= 4096, m >= 64, levels <= 8;
+ * 40,000 x 40,000, or 2^20 x 8000) are summed hierarchically: points near a
+ * query pair by pair as above, distant squares of points through their moments
+ * to the order (at most 16) whose first neglected terms of a square are below
+ * 2^-22 of the query's sums (the later ones add at most three times as much).
+ * The sums then cost O((n + m) log n) instead of O(n m); their error is that of
+ * the float32 weights (measured against float64: root mean square 5e-8, no
+ * more than with every pair evaluated).  Every pair is evaluated all the same
+ * where z reaches 2^100, where float32 coordinates are coarser than the
+ * squares, where the data crowd into so few of these that the moments would
+ * cost more than they save, or where memory for them is short.
  * aidw_set_interp_config with a launch shape of the caller's evaluates every pair.
  * A query with d1sq[j] == 0 coincides with data points and gets the mean z of
  * those points (the limit of Eq. 1).
@@ -453,9 +458,10 @@ aidw_status aidw_learned_routes(const float* x, const float* y, int64_t n, const
  * data points) from a list ordered by decreasing cost until it is exhausted.
  * Every item writes its own float64 partial sums and a last pass adds a
  * query's partials in a fixed order, so results are bitwise reproducible.
- * Where it saves a plan from about 2e9 pairs, jobs of at least 8192 data points
- * and several thousand queries (levels <= 8, with integer_powers) are summed
- * hierarchically, as aidw_interpolate describes.
+ * Where it saves a plan 1.5e9 pairs and more, jobs of at least 8192 data points
+ * and 256 queries whose pairs exceed 6000 n + 2000 m (levels <= 8, with
+ * integer_powers) are summed hierarchically, as aidw_interpolate describes; one
+ * that it evaluates every pair of keeps the plan's data ranges.
  * Each job's outputs are those aidw_run gives for the job alone (bitwise, for a
  * job whose every pair is evaluated, when aidw_run uses the same pair-kernel
  * shape: q, and split = the job's number of data ranges, see split_points).

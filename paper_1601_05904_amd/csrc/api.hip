@@ -573,7 +573,7 @@ void choose_interp_config(int64_t n, int64_t m, int* q, int* split) {
   // Fine splits keep the chip full when the queries are few (measured at 2^18 clustered
   // with one launch per class: 8 splits 64 % of the roofline, 128 splits 82 %; at 2^20
   // uniform 32 -> 64 splits 86.0 -> 86.2 %).  Where that leaves few workgroups it is split on, for a
-  // lone wavefront takes 45 ns a point (1000 points, 257 queries: 45 -> 9 us; 4096 x 4096: 88 -> 9 us), the
+  // lone wavefront takes 45 ns a point (1000 points, 257 queries: 45 -> 9 us; 4096 x 4096: 88 -> 15 us), the
   // less finely the more workgroups there are, as the partials cost more then: us of aidw_interpolate
   // with 1 | 2 | 4 | 8 | 16 splits, 2000 x 9000: 197 | 160 | 138 | 127 | 122; 700 x 50,000: 142 | 133 | 130 |
   // 132 | 132; 300 x 100,000: 126 | 131 | 130; 4000 x 150,000: 328 | 280 | 268 | 257 | 255; 700 x 300,000:
@@ -610,7 +610,7 @@ uint32_t integer_levels(const aidw_params* p) {
 // expansion's error bounds cover, and enough pairs to pay for the moments and the query order.
 // The direct sums cost n m / 5.2e12 s; the hierarchical ones 0.25 ms at the least, plus the moments (1.2 us
 // per 1000 data points where these are uneven, which also makes few queries' groups wide) and 0.3-1 us per
-// 1000 queries.  Whole runs in us, every pair / hierarchical, uniform | 8-component mixture:
+// 1000 queries.  (Data too uneven for these sizes turn the plan off on the device, see dense_leaf.)  Whole runs in us, every pair / hierarchical, uniform | 8-component mixture:
 //   8192 x 200,000:  542/483 | 593/625    32,768 x 32,768: 418/335 | 437/469    700,001 x 5003: 990/839 | 1051/1569
 //   8192 x 400,000:  869/563 | 958/741    32,768 x 50,000: 540/372 | 567/525    2^20 x 8192:   2226/866 | 2317/2182
 //   4096 x 500,000:  639/590 | 714/781    131,072 x 16,384: 674/373 | 704/597   262,144 x 8192: 700/482 | 737/930
@@ -623,8 +623,9 @@ bool tree_pays(int64_t n, int64_t m, const aidw_params* p) {
 }
 
 // Eq. 1 by hierarchical summation.  points: the grid of exactly these data points (a run's own);
-// null: a grid is built here.  AIDW_ENOMEM (no memory, or no grid of these points) only before anything
-// that writes an output is queued: every pair is evaluated then.
+// null: a grid is built here.  AIDW_ENOMEM only before anything that writes an output is queued: every pair
+// is evaluated then.  Where the plan turns out off on the device (no grid of these points, z out of range, a
+// leaf that costs more than the sums save) the pair kernel is queued behind it.
 aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t n, const float* qx, const float* qy,
                         int64_t m, const float* r_obs, const float* d1sq, const aidw_params* p, const aidw_grid* g,
                         float* qz, float* alpha_out, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end, int* used_q,
@@ -640,7 +641,7 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
     // points a cell make leaves of 32 (9,000,000 x 9000 points: 5.1 ms with the host waiting, 4.3 so, 5.9 with 4.5 a cell).
     while (occupancy_budget(n, gp.occupancy) > kBandMaxCells) gp.occupancy *= gp.occupancy < 32.0 ? 4.0 : 1.0625;
     aidw_status st = build_grid_impl(x, y, n, nullptr, nullptr, 0, &gp, s, true, &own, &t, nullptr, false);
-    if (st != AIDW_OK) return AIDW_ENOMEM;  // no grid (points on a line, for one): not what the caller asked for
+    if (st != AIDW_OK) return st;
     points = own;
   }
   aidw_status st = [&]() -> aidw_status {
@@ -737,7 +738,7 @@ aidw_status interp_impl(const float* x, const float* y, const float* z, int64_t 
     const aidw_status st = interp_tree(x, y, z, n, qx, qy, m, r_obs, d1sq, p, g, qz, alpha_out, s, ev_begin, ev_end,
                                        used_q, used_split, alpha_in, points, ap);
     if (st != AIDW_ENOMEM) return st;
-    g_detail.clear();  // no room for the moments, or no grid: every pair is evaluated
+    g_detail.clear();  // no room for the moments: every pair is evaluated
   }
   int q, split;
   choose_interp_config(n, m, &q, &split);

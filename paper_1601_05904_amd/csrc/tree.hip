@@ -2,7 +2,7 @@
 // expansion.  The squares are blocks of the even grid's cells, so their points are runs of the
 // cell-ordered arrays and need no further sort.
 //
-// Steps: k_tree_plan (geometry), k_tree_gather (z in cell order), k_tree_p2m (moments of the
+// Steps: k_tree_plan (geometry), k_tree_gather (z in cell order, and whether the sums pay), k_tree_p2m (moments of the
 // leaves and of the level above, from the points), k_tree_up (each further level from the one below,
 // and the squares inside dense leaves), the queries ordered along the Hilbert curve, k_tree_eval (the sums).
 #include <float.h>
@@ -904,7 +904,7 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 // A group whose box holds many points (queries on both sides of a gap) is taken in parts; in a dense
 // place it starts below the leaves instead: the near points of a leaf of 700 cost 60,000
 // instructions a query, the squares of 176 inside it and their near points 34,000.
-// What bounds it: the vector instructions of the pairs and expansions (about 25,000 per query at
+// What bounds it: the vector instructions of the pairs and expansions (about 40,000 per query at
 // 2^20 uniform, against 11 million for all pairs) and the latency of the scalar and header loads,
 // which four wavefronts a SIMD do not hide altogether (three, five and six were slower: 1.47 ms of
 // summation with four, 1.60 with three, 1.51 with five and six, whose registers spill).
