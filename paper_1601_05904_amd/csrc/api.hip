@@ -178,7 +178,7 @@ size_t block_size_class(size_t bytes) {
 
 bool capturing(hipStream_t s) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+  return s && hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;  // (the null stream never)
 }
 
 hipError_t dmalloc_async(void** p, size_t bytes, hipStream_t s) {
@@ -192,27 +192,27 @@ hipError_t dmalloc_async(void** p, size_t bytes, hipStream_t s) {
   {
     std::lock_guard<std::mutex> lock(g_cache_mu);
     auto& cache = block_cache();
-    auto smallest = [&](size_t limit, bool own, bool reserved) {
-      int best = -1;
-      for (int i = 0; i < (int)cache.size(); ++i) {
-        const CachedBlock& b = cache[i];
-        if (b.busy || b.device != dev || b.bytes < want || b.bytes > limit || (own && b.stream != s) ||
-            b.reserved != reserved)
-          continue;
-        if (best < 0 || b.bytes < cache[best].bytes || (b.bytes == cache[best].bytes && b.stream == s)) best = i;
-      }
-      return best;
+    // best: the smallest that suffices, at most twice as large; own, again: the smallest of the stream's own,
+    // however large, of those and of the reserved ones
+    int best = -1, own = -1, again = -1;
+    auto better = [&](int i, int than) {
+      return than < 0 || cache[i].bytes < cache[than].bytes || (cache[i].bytes == cache[than].bytes && cache[i].stream == s);
     };
-    int best = smallest(2 * want, false, false);
+    for (int i = 0; i < (int)cache.size(); ++i) {
+      const CachedBlock& b = cache[i];
+      if (b.busy || b.device != dev || b.bytes < want) continue;
+      if (b.reserved) {
+        if (b.stream == s && better(i, again)) again = i;
+      } else {
+        if (b.bytes <= 2 * want && better(i, best)) best = i;
+        if (b.stream == s && better(i, own)) own = i;
+      }
+    }
     // While s is captured nothing can be allocated and no other stream waited for.  The smallest of the
     // stream's own blocks that suffices, however large, then always leaves enough for the requests
     // that an earlier call of the same sizes met; those of earlier captures come first, so that
     // captures one after the other do not reserve ever more.
-    const int again = smallest(~(size_t)0, true, true);
-    if ((best < 0 || cache[best].stream != s || again >= 0) && capturing(s)) {
-      const int own = again >= 0 ? again : smallest(~(size_t)0, true, false);
-      if (own >= 0) best = own;
-    }
+    if ((again >= 0 || (own >= 0 && best != own)) && capturing(s)) best = again >= 0 ? again : own;
     if (best >= 0) {
       CachedBlock& b = cache[best];
       if (b.stream != s && b.done && (e = hipStreamWaitEvent(s, b.done->event, 0)) != hipSuccess) return e;

@@ -680,30 +680,34 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   qoff[njobs] = (int32_t)sm;
   bstart[njobs] = (int32_t)sb;
 
-  // ---- work items, longest first; those of hierarchically summed jobs, for a plan that turns out off, last ----
-  std::vector<WorkItem> items;
+  // ---- work items, longest first; those of hierarchically summed jobs, for a plan that turns out off, last,
+  // unsorted (a job's items are as long as each other but for the last ranges), by the length of their ranges ----
+  std::vector<WorkItem> items, sorted;
   std::vector<int64_t> cost;
-  for (int j = 0; j < njobs; ++j) {
+  auto add_items = [&](int j, std::vector<WorkItem>& to, bool costs) {
     const BatchJob& J = hj[j];
     const int nqb = (J.m + qb - 1) / qb;
     for (int b = 0; b < nqb; ++b) {
       const int64_t nq = std::min(qb, J.m - b * qb);
       for (int s = 0; s < J.splits; ++s) {
         const int64_t np = std::min(J.chunk, J.n - s * J.chunk);
-        items.push_back(WorkItem{j, b, s, 0});
-        cost.push_back(nq * np);
+        to.push_back(WorkItem{j, b, s, 0});
+        if (costs) cost.push_back(nq * np);
       }
     }
-  }
+  };
+  for (int j = 0; j < njobs; ++j)
+    if (hj[j].tree < 0) add_items(j, items, true);
   if (items.size() >= (size_t)INT32_MAX) return fail(AIDW_ECAPACITY, "too many work items");
   std::vector<int32_t> by_cost(items.size());
   for (size_t i = 0; i < by_cost.size(); ++i) by_cost[i] = (int32_t)i;
-  auto direct = [&](int32_t i) { return hj[items[i].job].tree < 0; };
-  std::stable_sort(by_cost.begin(), by_cost.end(), [&](int32_t a, int32_t b) {
-    return direct(a) != direct(b) ? direct(a) : cost[a] > cost[b];
-  });
-  std::vector<WorkItem> sorted(items.size());
-  for (size_t i = 0; i < by_cost.size(); ++i) sorted[i] = items[by_cost[i]];
+  std::stable_sort(by_cost.begin(), by_cost.end(), [&](int32_t a, int32_t b) { return cost[a] > cost[b]; });
+  for (size_t i = 0; i < by_cost.size(); ++i) sorted.push_back(items[by_cost[i]]);
+  const int nplain = (int)sorted.size();
+  std::vector<int> owners = tree_owner;
+  std::stable_sort(owners.begin(), owners.end(), [&](int a, int b) { return hj[a].chunk > hj[b].chunk; });
+  for (int j : owners) add_items(j, sorted, false);
+  if (sorted.size() >= (size_t)INT32_MAX) return fail(AIDW_ECAPACITY, "too many work items");
 
   aidw_batch* b = new aidw_batch();
   b->njobs = njobs;
@@ -723,7 +727,7 @@ aidw_status create_plan(const aidw_job* jobs, int32_t njobs, const aidw_batch_co
   b->sum_cap = (int)scap;
   b->nbblocks = (int)sb;
   b->nitems = (int)sorted.size();
-  b->nplain = (int)std::count_if(by_cost.begin(), by_cost.end(), direct);
+  b->nplain = nplain;
   b->sum_partial = spart;
   b->sum_pairs = pairs;
   b->cell_bits = bits_for(scap);
