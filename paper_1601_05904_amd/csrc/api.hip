@@ -176,9 +176,10 @@ size_t block_size_class(size_t bytes) {
   return (bytes + g - 1) / g * g;
 }
 
+// (The null stream cannot be captured.)
 bool capturing(hipStream_t s) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  return s && hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;  // (the null stream never)
+  return s && hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
 }
 
 hipError_t dmalloc_async(void** p, size_t bytes, hipStream_t s) {
@@ -196,7 +197,8 @@ hipError_t dmalloc_async(void** p, size_t bytes, hipStream_t s) {
     // however large, of those and of the reserved ones
     int best = -1, own = -1, again = -1;
     auto better = [&](int i, int than) {
-      return than < 0 || cache[i].bytes < cache[than].bytes || (cache[i].bytes == cache[than].bytes && cache[i].stream == s);
+      return than < 0 || cache[i].bytes < cache[than].bytes ||
+             (cache[i].bytes == cache[than].bytes && cache[i].stream == s);
     };
     for (int i = 0; i < (int)cache.size(); ++i) {
       const CachedBlock& b = cache[i];
@@ -610,7 +612,8 @@ uint32_t integer_levels(const aidw_params* p) {
 // expansion's error bounds cover, and enough pairs to pay for the moments and the query order.
 // The direct sums cost n m / 5.2e12 s; the hierarchical ones 0.25 ms at the least, plus the moments (1.2 us
 // per 1000 data points where these are uneven, which also makes few queries' groups wide) and 0.3-1 us per
-// 1000 queries.  (Data too uneven for these sizes turn the plan off on the device, see dense_leaf.)  Whole runs in us, every pair / hierarchical, uniform | 8-component mixture:
+// 1000 queries.  (Data too uneven for these sizes turn the plan off on the device, see dense_leaf.)  Whole
+// runs in us, every pair / hierarchical, uniform | 8-component mixture:
 //   8192 x 200,000:  542/483 | 593/625    32,768 x 32,768: 418/335 | 437/469    700,001 x 5003: 990/839 | 1051/1569
 //   8192 x 400,000:  869/563 | 958/741    32,768 x 50,000: 540/372 | 567/525    2^20 x 8192:   2226/866 | 2317/2182
 //   4096 x 500,000:  639/590 | 714/781    131,072 x 16,384: 674/373 | 704/597   262,144 x 8192: 700/482 | 737/930
@@ -638,7 +641,8 @@ aidw_status interp_tree(const float* x, const float* y, const float* z, int64_t 
     aidw_params gp;
     aidw_params_default(&gp);
     // Within the banded build's cells: beyond them the host would wait for the grid's scalars.  2, 8 and 32
-    // points a cell make leaves of 32 (9,000,000 x 9000 points: 5.1 ms with the host waiting, 4.3 so, 5.9 with 4.5 a cell).
+    // points a cell make leaves of 32 (9,000,000 x 9000 points: 5.1 ms with the host waiting, 4.3 so, 5.9 with
+    // 4.5 a cell).
     while (occupancy_budget(n, gp.occupancy) > kBandMaxCells) gp.occupancy *= gp.occupancy < 32.0 ? 4.0 : 1.0625;
     aidw_status st = build_grid_impl(x, y, n, nullptr, nullptr, 0, &gp, s, true, &own, &t, nullptr, false);
     if (st != AIDW_OK) return st;

@@ -367,7 +367,8 @@ __device__ __forceinline__ void b_item(int pos0, int posend, const uint32_t* __r
 // exit test on every round.
 template <int Q>
 __global__ __launch_bounds__(pair::kThreads) void k_b_interp(
-    const BatchJob* __restrict__ jobs, const WorkItem* __restrict__ items, uint32_t* __restrict__ counter, const GridScalars* __restrict__ gs, const float* __restrict__ xp,
+    const BatchJob* __restrict__ jobs, const WorkItem* __restrict__ items, uint32_t* __restrict__ counter,
+    const GridScalars* __restrict__ gs, const float* __restrict__ xp,
     const float* __restrict__ yp, const float* __restrict__ zp, const float* __restrict__ cqx,
     const float* __restrict__ cqy, const float* __restrict__ alpha_f, const float* __restrict__ d1sq,
     const uint32_t* __restrict__ perm, const uint32_t* __restrict__ skeys, uint32_t fast_mask,

@@ -554,8 +554,8 @@ __global__ __launch_bounds__(kLocalThreads) void k_band_local(const GridScalars*
   if (!query && band == nb - 1 && tid == 0) cell_start[g.ncells] = (int32_t)e;
   __syncthreads();
   if (s_max == e - s && !one_chunk) {
-    // All in one cell, as far outliers leave them: the segment's order is the cell's (mean of 2^18 and 2^20 points: 2.05 -> 0.70 ms
-    // against the rounds of the ballot path).
+    // All in one cell, as far outliers leave them: the segment's order is the cell's (mean of 2^18 and 2^20
+    // points: 2.05 -> 0.70 ms against the rounds of the ballot path).
     for (uint32_t p0 = s + tid; p0 < e; p0 += 8 * kLocalThreads) {
       uint32_t pid[8];
       float ax[8], ay[8];

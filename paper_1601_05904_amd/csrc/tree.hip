@@ -130,7 +130,8 @@ __global__ void k_tree_plan(Jobs jobs, uint32_t* __restrict__ zero_word) {
   // an opened square's coordinates have 14 bits on the stack
   p.fine = p.nx[0] <= kMaxSide / 2 && p.ny[0] <= kMaxSide / 2 ? min(bs, kFine) : 0;
   // how far points lie from the centres (Plan::widen)
-  const float far = fmaxf(fmaxf(fabsf(g.minx), fabsf(g.maxx)), fmaxf(fabsf(g.miny), fabsf(g.maxy))) + 2.0f * (float)p.h[0];
+  const float far = fmaxf(fmaxf(fabsf(g.minx), fabsf(g.maxx)), fmaxf(fabsf(g.miny), fabsf(g.maxy))) +
+                    2.0f * (float)p.h[0];
   const float spacing = __builtin_amdgcn_ldexpf(1.0f, __builtin_amdgcn_frexp_expf(far) - 24);
   const float cells = __builtin_amdgcn_ldexpf(1.0f, bs);  // of a leaf's side
   const float off0 = (spacing * g.inv_cw + 2.0f * (float)slack_cells(g.ncol, g.nrow)) / cells;
@@ -373,9 +374,11 @@ __global__ __launch_bounds__(256, 5) void k_tree_p2m(Jobs jobs, const float* __r
       for (int q = lane; q < 4 * kCoefs; q += 64) acc[q] = 0.0;
       wave_sync();
       if (pass == 0)
-        count = add_cells(tx, ty, tz, cell_start, ncol, c0, c1, r0, r1, cx0, cy0, ih0, s_sum[w].tab, acc, sabs, job.dense);
+        count = add_cells(tx, ty, tz, cell_start, ncol, c0, c1, r0, r1, cx0, cy0, ih0, s_sum[w].tab, acc, sabs,
+                          job.dense);
       else
-        add_cells(tx, ty, tz, cell_start, ncol, c0, c1, r0, r1, cx1, cy1, 0.5f * ih0, s_sum[w].tab, acc, unused, job.dense);
+        add_cells(tx, ty, tz, cell_start, ncol, c0, c1, r0, r1, cx1, cy1, 0.5f * ih0, s_sum[w].tab, acc, unused,
+                  job.dense);
       if (pass == 0) {
         for (int o = 32; o > 0; o >>= 1) sabs += __shfl_xor(sabs, o, 64);
         if (live) {
@@ -545,7 +548,8 @@ __device__ __forceinline__ void fine_squares(Plan* __restrict__ plan, const int3
     for (int q = lane; q < 4 * kCoefs; q += 64) sum.acc[q] = 0.0;
     wave_sync();
     double sabs = 0.0;
-    const int n = add_cells(tx, ty, tz, cell_start, plan->ncol, c0, c1, r0, r1, cx, cy, ih, sum.tab, sum.acc, sabs, kDenseLeaf);
+    const int n = add_cells(tx, ty, tz, cell_start, plan->ncol, c0, c1, r0, r1, cx, cy, ih, sum.tab, sum.acc, sabs,
+                            kDenseLeaf);
     for (int o = 32; o > 0; o >>= 1) sabs += __shfl_xor(sabs, o, 64);
     const int idx = pool + 4 * id + w;
     float* rec = nodes + (size_t)idx * kRec;
@@ -1236,18 +1240,21 @@ static Thresholds class_bounds() {
   return t;
 }
 
-// The largest leaf that hierarchical sums are kept for, by times in us: the pairs (5.2e12 a second, and the 8 % and
-// the launches that a plan which turns out off adds) against the sums, for even data 110 + 4e-4 m + 3e-4 n and
-// for each point of the largest leaf 0.2 + 6e-7 n: one wavefront forms a leaf's moments, and a group of queries
-// pays for every point near it.  Half as many points again are let pass, for the sums are more exact.  Whole
-// runs, every pair / hierarchical, mixtures of 16 | 8 | 3 | 1 components, whose largest leaves hold some 1000 | 2000 |
-// 3700 | 11,000 points; behind || they are off:
-//   45,000 x 45,000:   624/547 | 634/700 || 700/1067 | 846/2276     200,000 x 20,000: 1084/783 | 1078/1000 || 1155/1480 | 1253/3625
-//   262,144 x 30,000:  1882/912 | 1951/1249 | 1998/1685 || 2094/4070  2^20 x 9000: 2423/2071 | 2446/2632 || 2487/4109 | 2649/10421
-//   100,000 x 100,000: 2269/752 | 2312/928 | 2348/1266 | 2611/2664  2^20 x 20,000: 4657/2025 | 4653/2349 | 4735/3977 || 4915/8826
-// Jobs that share their launches hide each other's chains: pairs are then those of all of them, and a job's own are set
-// against 0.0115 a point of the largest leaf (a replay of 40 jobs of 16,384 x 16,384, every pair / hierarchical: 2637/1379
-// even, 2975/2086 with 8 components, 3861/4349 with 1).
+// The largest leaf that hierarchical sums are kept for, by times in us: the pairs (5.2e12 a second, and the 8 %
+// and the launches that a plan which turns out off adds) against the sums, for even data 110 + 4e-4 m + 3e-4 n
+// and for each point of the largest leaf 0.2 + 6e-7 n: one wavefront forms a leaf's moments, and a group of
+// queries pays for every point near it.  Half as many points again are let pass, for the sums are more exact.
+// Whole runs, every pair / hierarchical, mixtures of 16 | 8 | 3 | 1 components, whose largest leaves hold some
+// 1000 | 2000 | 3700 | 11,000 points; behind || they are off:
+//   45,000 x 45,000:    624/547  | 634/700   || 700/1067  | 846/2276
+//   100,000 x 100,000:  2269/752 | 2312/928  | 2348/1266  | 2611/2664
+//   200,000 x 20,000:   1084/783 | 1078/1000 || 1155/1480 | 1253/3625
+//   262,144 x 30,000:   1882/912 | 1951/1249 | 1998/1685  || 2094/4070
+//   2^20 x 9000:       2423/2071 | 2446/2632 || 2487/4109 | 2649/10421
+//   2^20 x 20,000:     4657/2025 | 4653/2349 | 4735/3977  || 4915/8826
+// Jobs that share their launches hide each other's chains: pairs are then those of all of them, and a job's own
+// are set against 0.0115 a point of the largest leaf (a replay of 40 jobs of 16,384 x 16,384, every pair /
+// hierarchical: 2637/1379 even, 2975/2086 with 8 components, 3861/4349 with 1).
 static int dense_leaf(int64_t n, int64_t m, double pairs) {
   const double room = 1.08 * pairs / 5.2e6 - 50.0 - 4e-4 * (double)m - 3e-4 * (double)n;
   const double own = fmax(0.9 * (double)n * (double)m / 5.2e6 - 14.0, 29.0);

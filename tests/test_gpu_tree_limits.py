@@ -71,8 +71,8 @@ def error(T, qz, x, y, z, qx, qy, alpha, sample=384):
 
 
 @pytest.mark.parametrize("level", [None, 5.0, 7.5])
-@pytest.mark.parametrize("offset,extent", [(5e6, 25.0), (5e6, 30.0), (120.0, 3.8e-4), (5e6, 50.0), (5e6, 100.0), (5e6, 200.0),
-                                           (5e6, 400.0)])
+@pytest.mark.parametrize("offset,extent", [(5e6, 25.0), (5e6, 30.0), (120.0, 3.8e-4), (5e6, 50.0), (5e6, 100.0),
+                                           (5e6, 200.0), (5e6, 400.0)])
 def test_coarse_coordinates(T, offset, extent, level):
     """Coordinates whose float32 spacing is 0.9 to 0.05 of a leaf's side: a square's centre is rounded to
     them too, and its points lie that much farther from it."""
@@ -236,8 +236,8 @@ def test_sizes_of_the_summation(T, n):
     assert T.equal(call(m, p), every_pair(lambda: call(m, p)))
 
 
-@pytest.mark.parametrize("n,m,kind", [(40961, 50009, "uniform"), (65537, 40001, "mixture"), ((1 << 20) + 13, 9001, "mixture"),
-                                      (4099, (1 << 19) + 77, "uniform"), (50003, 45001, "uniform")])
+@pytest.mark.parametrize("n,m,kind", [(40961, 50009, "uniform"), (65537, 40001, "mixture"),
+                                      ((1 << 20) + 13, 9001, "mixture"), (4099, (1 << 19) + 77, "uniform"), (50003, 45001, "uniform")])
 def test_usual_data_are_summed_hierarchically(T, n, m, kind):
     """Sizes and kinds that other tests of the summation rest on: the plan is on."""
     aidw = aidw_mod()
@@ -251,8 +251,8 @@ def test_usual_data_are_summed_hierarchically(T, n, m, kind):
 
 @pytest.mark.parametrize("occupancy", [0.5, 2.0, 8.0])
 def test_dense_leaves(T, occupancy):
-    """Clusters of thousands of points in a leaf are summed hierarchically, with squares below the leaves, where the queries
-    are many (on), and pair by pair where they are few (off)."""
+    """Clusters of thousands of points in a leaf are summed hierarchically, with squares below the leaves, where
+    the queries are many, and pair by pair where they are few."""
     aidw = aidw_mod()
     rng = np.random.default_rng(61)
 
@@ -271,3 +271,33 @@ def test_dense_leaves(T, occupancy):
     assert error(T, qz, *d, alpha) <= TREE_TOL
     few = d[:3] + [v[:30000].contiguous() for v in d[3:]]
     assert T.equal(aidw.run(*few, prm), every_pair(lambda: aidw.run(*few, prm)))
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e33])
+def test_captured_on_and_off(T, scale):
+    """A captured aidw_interpolate decides anew at every replay whether its plan is on: fields in and out of the
+    moments' range in turn, against eager calls."""
+    aidw = aidw_mod()
+    ds = W.make(50000, 40000, 10, 853, "uniform", 8)
+    x, y, z, qx, qy = dev(T, ds.x, ds.y, ds.z, ds.qx, ds.qy)
+    grid = aidw.build_grid(x, y, qx, qy, aidw.Params(k=10))
+    r, d1, _ = aidw.knn(grid, qx, qy, 10)
+    p = aidw.Params(k=10, area=grid.describe()["area"])
+    grid.close()
+    side = T.cuda.Stream()
+    z0 = z.clone()
+    z.mul_(scale)
+    T.cuda.synchronize()
+    aidw.interpolate(x, y, z, qx, qy, r, d1, p, stream=side)
+    T.cuda.synchronize()
+    graph = T.cuda.CUDAGraph()
+    with T.cuda.graph(graph, stream=side):
+        out = aidw.interpolate(x, y, z, qx, qy, r, d1, p, stream=side)
+    for factor in (1.0, 1e33, 1e33, 1.5, 2e33):
+        z.copy_(z0 * factor)
+        T.cuda.synchronize()
+        graph.replay()
+        T.cuda.synchronize()
+        call = lambda: aidw.interpolate(x, y, z, qx, qy, r, d1, p)  # noqa: E731
+        assert T.equal(out, call())
+        assert T.equal(out, every_pair(call)) == (factor > 1e30)
